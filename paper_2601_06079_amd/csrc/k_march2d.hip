@@ -1,0 +1,280 @@
+// k_march2d.hip -- node operators of the 2-D weak forms, streamed row by row.
+//
+// The strip-and-row layout of k_jvp2d.hip (one 64-lane wave per strip of columns and
+// chunk of rows, x-neighbours by DPP, rows in registers, four rows in flight) for the
+// operators and epilogues of march.hpp: each element row's Gauss points are evaluated
+// once, where the node-centric kernels evaluate each four times.  The pointwise inputs
+// of an epilogue are prefetched with the rows.  MOP_SCHUR chains two stencils (two halo
+// lanes per side): the inner product never reaches memory.
+#include <algorithm>
+#include <cmath>
+
+#include "device.hpp"
+#include "kernels.hpp"
+#include "march.hpp"
+#include "stream2d.hpp"
+
+namespace pfk {
+namespace {
+
+template <typename T>
+struct MC2 {
+    T a, b, c;  // GRAD: q (a + q (b + c q)); JVP, SCHUR: (a + q (b + c q)) v  (|J| folded in)
+    T kv;       // times (9 v - box v), nodal: (4 v - nbrs)
+    T kw;       // SCHUR: the outer stencil
+    T s0, s1, s2;
+};
+
+// 9 v - box3x3 v of row r - 1 (nodal: 4 v - axis neighbours) as rows are pushed, from
+// differences of neighbouring values (which FP32 forms exactly where the field is smooth:
+// with 9 v - box v the rounding floor of the residual was 6 times higher at 2048^2, and
+// Newton took one more correction): with e = 2 v - v(x-1) - v(x+1),
+//   3 (2 v - v(y-1) - v(y+1)) + e(y-1) + e + e(y+1)
+template <typename T, bool NODAL>
+struct Lap2 {
+    T v1 = 0, d1 = 0, e1 = 0, e2 = 0;  // v at row r-1; v(r-1) - v(r-2); e of rows r-1, r-2
+    __device__ __forceinline__ T push(T v)
+    {
+        const T e = (v - from_left(v)) + (v - from_right(v));
+        const T d = v - v1;
+        T lap;
+        if constexpr (NODAL)
+            lap = e1 + (d1 - d);
+        else
+            lap = fmaT((T)3, d1 - d, (e2 + e1) + e);
+        e2 = e1;
+        e1 = e;
+        d1 = d;
+        v1 = v;
+        return lap;
+    }
+};
+
+// quadrature sum of node row r - 1 as rows of u (and v) are pushed
+template <typename T, bool WITHV, bool NODAL>
+struct Quad2 {
+    T xlu = 0, xru = 0, xlv = 0, xrv = 0;  // x-interpolants of row r-1 (nodal: u, v of row r-1 in xlu, xlv)
+    T guL = 0, guR = 0;                    // upward scatter of element row (r-2, r-1)
+
+    __device__ __forceinline__ T push(T u, T v, const MC2<T>& k)
+    {
+        const T gp = (T)GP, gm = (T)GM;
+        auto F = [&](T q, T p) { return fmaT(fmaT(k.c, q, k.b), q, k.a) * (WITHV ? p : q); };
+        if constexpr (NODAL) {
+            const T r = F(xlu, xlv);
+            xlu = u;
+            xlv = v;
+            return r;
+        } else {
+            const T du = from_right(u) - u;
+            const T xlu0 = fmaT(gm, du, u), xru0 = fmaT(gp, du, u);
+            const T eu0 = xlu0 - xlu, eu1 = xru0 - xru;
+            T xlv0 = 0, xrv0 = 0, ev0 = 0, ev1 = 0;
+            if constexpr (WITHV) {
+                const T dv = from_right(v) - v;
+                xlv0 = fmaT(gm, dv, v);
+                xrv0 = fmaT(gp, dv, v);
+                ev0 = xlv0 - xlv;
+                ev1 = xrv0 - xrv;
+            }
+            const T PL0 = F(fmaT(gm, eu0, xlu), fmaT(gm, ev0, xlv));
+            const T PL1 = F(fmaT(gp, eu0, xlu), fmaT(gp, ev0, xlv));
+            const T PR0 = F(fmaT(gm, eu1, xru), fmaT(gm, ev1, xrv));
+            const T PR1 = F(fmaT(gp, eu1, xru), fmaT(gp, ev1, xrv));
+            const T dL = PL0 - PL1, dR = PR0 - PR1;
+            const T HL = guL + fmaT(gp, dL, PL1), HR = guR + fmaT(gp, dR, PR1);
+            guL = fmaT(gm, dL, PL1);
+            guR = fmaT(gm, dR, PR1);
+            const T dH = HL - HR;
+            xlu = xlu0;
+            xru = xru0;
+            xlv = xlv0;
+            xrv = xrv0;
+            return fmaT(gp, dH, HR) + from_left(fmaT(gm, dH, HR));
+        }
+    }
+};
+
+constexpr int MPF = 4;  // rows in flight per field
+
+template <typename T, int OP, int EPI, bool MIRROR, bool NODAL>
+__global__ __launch_bounds__(256) void k_march2d(March<T> p, int nx, int ny, int nstrips, int nwaves, int ty,
+                                                 unsigned bytes, MC2<T> k)
+{
+    constexpr int H = OP == MOP_SCHUR ? 2 : 1;
+    constexpr int OUTW = WAVE - 2 * H;
+    constexpr bool HASU = OP != MOP_STIFF, HASV = OP != MOP_GRAD || EPI == ME_CHRES;
+    constexpr bool USE0 = EPI == ME_MU || EPI == ME_BACK || EPI == ME_CHEB;
+    constexpr bool USE1 = EPI == ME_CHEB || EPI == ME_OUT || EPI == ME_CHRES, USE2 = EPI == ME_CHEB;
+    const int wid = uniform_wave();
+    if (wid >= nwaves) return;  // uniform per wave
+    const int strip = wid % nstrips, chunk = wid / nstrips;
+    const int y0 = chunk * ty, y1 = min(ny, y0 + ty);
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int xl = strip * OUTW - H + lane;
+    int x;
+    if constexpr (MIRROR) {
+        x = reflect(xl, nx);
+    } else {
+        x = xl % nx;
+        if (x < 0) x += nx;
+    }
+    const bool out_lane = lane >= H && lane < WAVE - H && xl < nx;
+    T xs = (T)1;
+    if (MIRROR && p.rows) xs = edge_count(x, nx) ? (T)0.5 : (T)1;
+    const int iters = (y1 - y0) + 2 * H;  // rows y0 - H .. y1 + H - 1
+    const int rowb = nx * (int)sizeof(T);
+    const int vx = x * (int)sizeof(T);
+    const auto ru = make_rsrc(HASU ? p.u : p.v, bytes);
+    const auto rv = make_rsrc(HASV ? p.v : p.u, bytes);
+    const auto ro = make_rsrc(p.out, bytes);
+    const auto ro2 = make_rsrc(EPI == ME_CHRES ? p.out2 : p.out, bytes);
+    const auto rb = make_rsrc(p.base ? p.base : p.out, bytes);
+    const auto r0 = make_rsrc(p.p0 ? p.p0 : p.out, bytes);
+    const auto r1 = make_rsrc(p.p1 ? p.p1 : p.out, bytes);
+    const auto r2 = make_rsrc(p.p2 ? p.p2 : p.out, bytes);
+    // rows read lie in [-H, ny + H - 1] and are wrapped or reflected once (the launcher
+    // keeps ny >= 2 H)
+    auto row_off = [&](int t) {
+        int r = min(y0 - H + t, y1 + H - 1);  // past the chunk the last row is read again (a cache hit)
+        if constexpr (MIRROR) {
+            r = r < 0 ? -r : (r >= ny ? 2 * (ny - 1) - r : r);
+        } else {
+            r = r < 0 ? r + ny : (r >= ny ? r - ny : r);
+        }
+        return r * rowb;
+    };
+    // output row of iteration t: y0 - 2 H + t
+    auto out_off = [&](int t) { return min(max(y0 - 2 * H + t, y0), y1 - 1) * rowb; };
+    T fu[MPF], fv[MPF], fb[MPF], f0[MPF], f1[MPF], f2[MPF];
+    auto fetch = [&](int t, int i) {
+        const int off = row_off(t);
+        fu[i] = HASU ? bload<T>(ru, vx, off) : (T)0;
+        fv[i] = HASV ? bload<T>(rv, vx, off) : (T)0;
+        const int oo = out_off(t);
+        fb[i] = p.base ? bload<T>(rb, vx, oo) : (T)0;
+        f0[i] = USE0 ? bload<T>(r0, vx, oo) : (T)0;
+        f1[i] = USE1 && p.p1 ? bload<T>(r1, vx, oo) : (T)0;
+        f2[i] = USE2 && p.p2 ? bload<T>(r2, vx, oo) : (T)0;
+    };
+#pragma unroll
+    for (int i = 0; i < MPF; ++i) fetch(i, i);
+    constexpr bool VARG = OP != MOP_GRAD;  // the operator's argument is v
+    Quad2<T, VARG, NODAL> qd;
+    Lap2<T, NODAL> lp, lw;
+    T c1 = 0, c2 = 0;  // the operator's argument at rows r-1, r-2
+    // whole groups of MPF rows: the pushes past the chunk compute rows nobody stores
+    for (int t0 = 0; t0 < iters; t0 += MPF) {
+#pragma unroll
+        for (int i = 0; i < MPF; ++i) {
+            const int t = t0 + i;
+            const T u = fu[i], v = fv[i], eb = fb[i], e0 = f0[i], e1 = f1[i], e2 = f2[i];
+            fetch(t + MPF, i);
+            T s = 0;
+            if constexpr (HASU) s = qd.push(u, v, k);
+            const T lap = lp.push(VARG ? v : u);
+            const T v1 = lw.v1;  // ME_CHRES: v at the output row
+            T lapv = 0;
+            if constexpr (EPI == ME_CHRES) lapv = lw.push(v);
+            T o = HASU ? fmaT(k.kv, lap, s) : k.kv * lap;
+            if constexpr (OP == MOP_SCHUR) o = k.kw * lw.push(o);
+            const T cc = H == 2 ? c2 : c1;
+            c2 = c1;
+            c1 = VARG ? v : u;
+            if (t >= 2 * H && t < iters && out_lane) {
+                const int yo = y0 - 2 * H + t;
+                T ib = xs;
+                if (MIRROR && p.rows) ib = (yo == 0 || yo == ny - 1) ? xs * (T)0.5 : xs;
+                const T c = p.base ? eb : cc;
+                T r;
+                if constexpr (EPI == ME_OUT) r = (k.s0 != (T)0 ? fmaT(k.s0, c - e1, o) : o) * ib;
+                else if constexpr (EPI == ME_SUB) r = c - o * ib;
+                else if constexpr (EPI == ME_MU) r = fmaT(k.s0, e0, -o) * ib;
+                else if constexpr (EPI == ME_CHRES) {
+                    bstore(fmaT(k.s0, v1, -o) * ib, ro2, vx, yo * rowb);
+                    r = (k.s1 != (T)0 ? fmaT(k.kw, lapv, k.s1 * (c - e1)) : k.kw * lapv) * ib;
+                } else if constexpr (EPI == ME_BACK) r = fmaT(k.s0 / ib, e0, o);
+                else r = fmaT(k.s1, c - e2, c) + k.s2 * e1 * (e0 - fmaT(k.s0, c, o) * ib);
+                bstore(r, ro, vx, yo * rowb);
+            }
+        }
+    }
+}
+
+int march2_cus()
+{
+    static const int n = [] {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
+            (void)hipGetLastError();
+            return 256;
+        }
+        return cus;
+    }();
+    return n;
+}
+
+}  // namespace
+
+template <typename T>
+bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s)
+{
+    // 32-bit buffer offsets; the Gauss-integrated mass has no streaming form
+    if (g.dim != 2 || g.cm || (size_t)g.N * sizeof(T) >= (size_t(1) << 31)) return false;
+    const int H = op == MOP_SCHUR ? 2 : 1;
+    const int nx = g.n[0], ny = g.n[1], outw = WAVE - 2 * H;
+    if (ny < 2 * H) return false;
+    const int nstrips = (nx + outw - 1) / outw;
+    // chunks for about four waves per SIMD, never shorter than 8 rows (as k_jvp2d)
+    long long nch = std::max<long long>(1, 16ll * march2_cus() / nstrips);
+    nch = std::min<long long>(nch, std::max(1, ny / 8));
+    const int tov = tune_stream2d_rows();
+    const int ty = tov > 0 ? std::min(tov, ny) : (int)((ny + nch - 1) / nch);
+    const long long nwaves = (long long)nstrips * ((ny + ty - 1) / ty);
+    if (nwaves > (1ll << 30)) return false;
+    const double mm = g.h * g.h, w = m.nq * (g.quad ? mm : 0.25 * mm), ks = g.quad ? 1.0 : 1.0 / 3.0;
+    MC2<T> k{};
+    if (op == MOP_GRAD) {
+        k.a = (T)(w * f.a1); k.b = (T)(w * f.a2); k.c = (T)(w * f.a3);
+    } else {
+        k.a = (T)(w * f.b0); k.b = (T)(w * f.b1); k.c = (T)(w * f.b2);
+    }
+    k.kv = (T)(m.kv * ks);
+    k.kw = (T)(m.kw * ks);
+    k.s0 = (T)m.s0;
+    k.s1 = (T)m.s1;
+    k.s2 = (T)m.s2;
+    const unsigned blocks = (unsigned)((nwaves + 3) / 4), bytes = (unsigned)((size_t)g.N * sizeof(T));
+#define M2Q(OP, EPI, MIR)                                                                                        \
+    do {                                                                                                         \
+        if (g.quad)                                                                                              \
+            k_march2d<T, OP, EPI, MIR, true><<<blocks, 256, 0, s>>>(m, nx, ny, nstrips, (int)nwaves, ty, bytes, k);  \
+        else                                                                                                     \
+            k_march2d<T, OP, EPI, MIR, false><<<blocks, 256, 0, s>>>(m, nx, ny, nstrips, (int)nwaves, ty, bytes, k); \
+    } while (0)
+#define M2(OP, EPI)                                                                                              \
+    do {                                                                                                         \
+        if (g.bc) M2Q(OP, EPI, true); else M2Q(OP, EPI, false);                                                  \
+    } while (0)
+    switch (op * 8 + epi) {
+        case MOP_GRAD * 8 + ME_OUT: M2(MOP_GRAD, ME_OUT); return true;
+        case MOP_GRAD * 8 + ME_CHRES: M2(MOP_GRAD, ME_CHRES); return true;
+        case MOP_JVP * 8 + ME_OUT: M2(MOP_JVP, ME_OUT); return true;
+        case MOP_JVP * 8 + ME_BACK: M2(MOP_JVP, ME_BACK); return true;
+        case MOP_JVP * 8 + ME_CHEB: M2(MOP_JVP, ME_CHEB); return true;
+        case MOP_STIFF * 8 + ME_OUT: M2(MOP_STIFF, ME_OUT); return true;
+        case MOP_STIFF * 8 + ME_SUB: M2(MOP_STIFF, ME_SUB); return true;
+        case MOP_STIFF * 8 + ME_CHEB: M2(MOP_STIFF, ME_CHEB); return true;
+        case MOP_SCHUR * 8 + ME_OUT: M2(MOP_SCHUR, ME_OUT); return true;
+        case MOP_SCHUR * 8 + ME_CHEB: M2(MOP_SCHUR, ME_CHEB); return true;
+        default: return false;
+    }
+#undef M2
+#undef M2Q
+}
+
+template bool launch_march2d<float>(const Geom&, int, int, const FreeEnergy&, const March<float>&, hipStream_t);
+template bool launch_march2d<double>(const Geom&, int, int, const FreeEnergy&, const March<double>&, hipStream_t);
+
+}  // namespace pfk

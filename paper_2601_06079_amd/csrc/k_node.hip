@@ -338,6 +338,45 @@ void launch_residual(const Geom& g, int model, const FreeEnergy& f, double kappa
                      const T* U, T* r, hipStream_t s, const T* Uold, double inv_dt)
 {
     const double detJ = std::pow(0.5 * g.h, g.dim), m = std::pow(g.h, g.dim);
+    if (!g.cm) {
+        // marching kernels: every Gauss point once.  In 3-D the Cahn-Hilliard rows take two
+        // passes (they share no quadrature); both fit or neither does.
+        March<T> a;
+        a.u = U;
+        a.rows = 1;
+        if (model == 0) {
+            a.out = r;
+            a.nq = mob;
+            a.kv = mob * kappa;
+            a.s0 = Uold ? inv_dt * m : 0.0;
+            a.p1 = Uold;
+            if (launch_march<T>(g, MOP_GRAD, ME_OUT, f, a, s)) return;
+        } else if (g.dim == 2) {
+            a.v = U + g.N;
+            a.out = r;
+            a.out2 = r + g.N;
+            a.kv = kappa;
+            a.kw = mob;
+            a.s0 = m;
+            a.s1 = Uold ? inv_dt * m : 0.0;
+            a.p1 = Uold;
+            if (launch_march2d<T>(g, MOP_GRAD, ME_CHRES, f, a, s)) return;
+        } else {
+            a.out = r + g.N;
+            a.p0 = U + g.N;
+            a.kv = kappa;
+            a.s0 = m;
+            March<T> b;
+            b.v = U + g.N;
+            b.base = U;
+            b.p1 = Uold;
+            b.out = r;
+            b.kv = mob;
+            b.s0 = Uold ? inv_dt * m : 0.0;
+            b.rows = 1;
+            if (launch_march<T>(g, MOP_GRAD, ME_MU, f, a, s) && launch_march<T>(g, MOP_STIFF, ME_OUT, f, b, s)) return;
+        }
+    }
     DIM_SWITCH(g, {
         if (model == 0)
             k_residual<T, D, 0><<<grid_for(g), 256, 0, s>>>(U, Uold, r, g, cub_of<T>(f, 1.0),
@@ -399,6 +438,12 @@ void launch_chem(const Geom& g, const FreeEnergy& f, double kappa, const T* c, T
                  hipStream_t s)
 {
     const double detJ = std::pow(0.5 * g.h, g.dim), m = std::pow(g.h, g.dim);
+    March<T> a;
+    a.u = c;
+    a.out = mu;
+    a.nq = 1.0 / m;
+    a.kv = kappa / m;
+    if (launch_march<T>(g, MOP_GRAD, ME_OUT, f, a, s)) return;
     DIM_SWITCH(g, {
         k_chem<T, D><<<grid_for(g), 256, 0, s>>>(c, mu, g, cub_of<T>(f, 1.0), (T)detJ, (T)kappa,
                                                   (T)(1.0 / m));
@@ -409,6 +454,12 @@ template <typename T>
 void launch_ch_update(const Geom& g, double dtM, const T* c, const T* mu, T* c_out, hipStream_t s)
 {
     const double m = std::pow(g.h, g.dim);
+    March<T> a;
+    a.v = mu;
+    a.base = c;
+    a.out = c_out;
+    a.kv = dtM / m;
+    if (launch_march<T>(g, MOP_STIFF, ME_SUB, FreeEnergy{}, a, s)) return;
     DIM_SWITCH(g, { k_ch_update<T, D><<<grid_for(g), 256, 0, s>>>(c, mu, c_out, g, (T)(dtM / m)); });
 }
 
@@ -417,6 +468,12 @@ void launch_ac_step(const Geom& g, const FreeEnergy& f, double kappa, double dtL
                     T* eta_out, hipStream_t s)
 {
     const double detJ = std::pow(0.5 * g.h, g.dim), m = std::pow(g.h, g.dim);
+    March<T> a;
+    a.u = eta;
+    a.out = eta_out;
+    a.nq = dtL / m;
+    a.kv = dtL * kappa / m;
+    if (launch_march<T>(g, MOP_GRAD, ME_SUB, f, a, s)) return;
     DIM_SWITCH(g, {
         k_ac_step<T, D><<<grid_for(g), 256, 0, s>>>(eta, eta_out, g, cub_of<T>(f, 1.0), (T)detJ,
                                                      (T)kappa, (T)(dtL / m));

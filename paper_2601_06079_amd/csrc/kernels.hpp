@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "march.hpp"
+
 namespace pfk {
 
 // Geometry of a structured grid (x fastest).  bc 0: periodic; bc 1: no-flux
@@ -115,6 +117,19 @@ void launch_gg_energy2d(const Geom& g, int P, double kappa, double gamma, const 
 template <typename T>
 void launch_jvp3d(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,
                   double inv_dt, const T* U, const T* v, T* Jv, hipStream_t s, int trans);
+// One marching pass over a 3-D grid (k_march3d.hip; operators and epilogues in
+// march.hpp): lumped mass, both quadratures, fields below 2 GiB.  False (nothing
+// launched) where it does not apply.
+template <typename T>
+bool launch_march3d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s);
+// the same over a 2-D grid, streamed by rows (k_march2d.hip), and whichever fits g.dim
+template <typename T>
+bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s);
+template <typename T>
+inline bool launch_march(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s)
+{
+    return g.dim == 3 ? launch_march3d<T>(g, op, epi, f, m, s) : launch_march2d<T>(g, op, epi, f, m, s);
+}
 // (block-)Jacobi inverse of dR/dU at U: N (Allen-Cahn) or 4N (Cahn-Hilliard) values
 template <typename T>
 void launch_prec(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,

@@ -261,10 +261,12 @@ bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
         case MOP_GRAD * 8 + ME_OUT: M2(MOP_GRAD, ME_OUT); return true;
         case MOP_GRAD * 8 + ME_CHRES: M2(MOP_GRAD, ME_CHRES); return true;
         case MOP_JVP * 8 + ME_OUT: M2(MOP_JVP, ME_OUT); return true;
+        case MOP_JVP * 8 + ME_SUB: M2(MOP_JVP, ME_SUB); return true;
         case MOP_JVP * 8 + ME_BACK: M2(MOP_JVP, ME_BACK); return true;
         case MOP_JVP * 8 + ME_CHEB: M2(MOP_JVP, ME_CHEB); return true;
         case MOP_STIFF * 8 + ME_OUT: M2(MOP_STIFF, ME_OUT); return true;
         case MOP_STIFF * 8 + ME_SUB: M2(MOP_STIFF, ME_SUB); return true;
+        case MOP_STIFF * 8 + ME_BACK: M2(MOP_STIFF, ME_BACK); return true;
         case MOP_STIFF * 8 + ME_CHEB: M2(MOP_STIFF, ME_CHEB); return true;
         case MOP_SCHUR * 8 + ME_OUT: M2(MOP_SCHUR, ME_OUT); return true;
         case MOP_SCHUR * 8 + ME_CHEB: M2(MOP_SCHUR, ME_CHEB); return true;

@@ -411,10 +411,12 @@ bool launch_r(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T
         case MOP_GRAD * 8 + ME_SUB: M3(MOP_GRAD, ME_SUB); return true;
         case MOP_GRAD * 8 + ME_MU: M3(MOP_GRAD, ME_MU); return true;
         case MOP_JVP * 8 + ME_OUT: M3(MOP_JVP, ME_OUT); return true;
+        case MOP_JVP * 8 + ME_SUB: M3(MOP_JVP, ME_SUB); return true;
         case MOP_JVP * 8 + ME_BACK: M3(MOP_JVP, ME_BACK); return true;
         case MOP_JVP * 8 + ME_CHEB: M3(MOP_JVP, ME_CHEB); return true;
         case MOP_STIFF * 8 + ME_OUT: M3(MOP_STIFF, ME_OUT); return true;
         case MOP_STIFF * 8 + ME_SUB: M3(MOP_STIFF, ME_SUB); return true;
+        case MOP_STIFF * 8 + ME_BACK: M3(MOP_STIFF, ME_BACK); return true;
         case MOP_STIFF * 8 + ME_CHEB: M3(MOP_STIFF, ME_CHEB); return true;
         default: return false;
     }

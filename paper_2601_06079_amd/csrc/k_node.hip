@@ -83,6 +83,33 @@ __global__ __launch_bounds__(256) void k_prec(const T* __restrict__ U, T* __rest
     }
 }
 
+// Point preconditioner of the Cahn-Hilliard Newton system with mu eliminated (see
+// newton.hip), S = inv_dt m + (mob / m) K [N'(c) + kappa K], rows / 2^b on no-flux grids:
+//   pinv = 1 / (theta diag S),
+// with the diagonal of K N'(c) taken as if f'' were constant around the node (cn f''(c))
+// and that of K K (ck); a preconditioner may be approximate.  Where f'' < 0 outweighs
+// the rest the diagonal is held at a tenth of its positive part.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_prec_schur(const T* __restrict__ U, T* __restrict__ pinv, Geom g, Lin<T> F,
+                                                    T d0, T cn, T theta)
+{
+    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    int i, j, k;
+    if (!node_of<D>(g, idx, i, j, k)) return;
+    const T d = max(fmaT(cn, F(U[idx], (T)1), d0), (T)0.1 * d0);
+    pinv[idx] = (T)bfactor<D>(g, i, j, k) / (theta * d);
+}
+
+// y = scale 2^b x (2^b: the boundary factor of the node's rows)
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_unrow(const T* __restrict__ x, T* __restrict__ y, Geom g, T scale)
+{
+    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    int i, j, k;
+    if (!node_of<D>(g, idx, i, j, k)) return;
+    y[idx] = scale * (T)bfactor<D>(g, i, j, k) * x[idx];
+}
+
 // Jv for R = inv_dt M (U - U_old) + r(U)
 // TRANS = 1 gives the transpose product w^T dR/dU (differs from J only for
 // Cahn-Hilliard):  [inv_dt m w_c - (N'(c) + kappa K) w_mu ;  M K w_c + m w_mu].
@@ -433,6 +460,38 @@ void launch_prec(const Geom& g, int model, const FreeEnergy& f, double kappa, do
     });
 }
 
+// Centre entries and sums of products of the unit Q1 stencils: K_aa, the diagonals of
+// K K and of K M (M the Gauss-integrated mass over m), and the largest symbol of K;
+// 2-D h-free, 3-D per h (K K: per h^2)
+struct StencilDiag { double kd, kk, km, kmax; };
+inline StencilDiag stencil_diag(const Geom& g)
+{
+    // nodal: 5/7-point K, M the identity.  Gauss: 2-D entries 8/3, -1/3 (8 neighbours) and
+    // mass (4 1 4 1 16 ...)/36; 3-D entries 8/3, 0 (faces), -1/6 (12 edges), -1/12 (8
+    // corners) and mass 8/27, 2/27, 1/54, 1/216; the symbol is largest at one axis' Nyquist
+    // wave (4), nodal at all of them (8 / 12)
+    if (g.quad) return g.dim == 2 ? StencilDiag{4.0, 20.0, 4.0, 8.0} : StencilDiag{6.0, 42.0, 6.0, 12.0};
+    return g.dim == 2 ? StencilDiag{8.0 / 3.0, 8.0, 1.0, 4.0}
+                      : StencilDiag{8.0 / 3.0, 7.5, 8.0 / 3.0 * 8.0 / 27.0 - 2.0 / 54.0 - 8.0 / 12.0 / 216.0, 4.0};
+}
+
+template <typename T>
+void launch_prec_schur(const Geom& g, const FreeEnergy& f, double kappa, double mob, double inv_dt, double theta,
+                       const T* U, T* pinv, hipStream_t s)
+{
+    const double m = std::pow(g.h, g.dim), hk = g.dim == 3 ? g.h : 1.0;
+    const StencilDiag d = stencil_diag(g);
+    const Lin<T> F{(T)f.b0, (T)f.b1, (T)f.b2};
+    const double d0 = inv_dt * m + mob / m * kappa * d.kk * hk * hk, cn = mob * d.km * hk;
+    DIM_SWITCH(g, { k_prec_schur<T, D><<<grid_for(g), 256, 0, s>>>(U, pinv, g, F, (T)d0, (T)cn, (T)theta); });
+}
+
+template <typename T>
+void launch_unrow(const Geom& g, double scale, const T* x, T* y, hipStream_t s)
+{
+    DIM_SWITCH(g, { k_unrow<T, D><<<grid_for(g), 256, 0, s>>>(x, y, g, (T)scale); });
+}
+
 template <typename T>
 void launch_chem(const Geom& g, const FreeEnergy& f, double kappa, const T* c, T* mu,
                  hipStream_t s)
@@ -496,6 +555,9 @@ void launch_energy(const Geom& g, const FreeEnergy& f, double kappa, const T* c,
                                 const T*, const T*, T*, hipStream_t, int, int);                   \
     template void launch_prec<T>(const Geom&, int, const FreeEnergy&, double, double, double,      \
                                  const T*, T*, hipStream_t);                                      \
+    template void launch_prec_schur<T>(const Geom&, const FreeEnergy&, double, double, double, double, const T*, \
+                                       T*, hipStream_t);                                          \
+    template void launch_unrow<T>(const Geom&, double, const T*, T*, hipStream_t);                 \
     template void launch_chem<T>(const Geom&, const FreeEnergy&, double, const T*, T*, hipStream_t); \
     template void launch_ch_update<T>(const Geom&, double, const T*, const T*, T*, hipStream_t);   \
     template void launch_ac_step<T>(const Geom&, const FreeEnergy&, double, double, const T*, T*,  \

@@ -134,6 +134,13 @@ inline bool launch_march(const Geom& g, int op, int epi, const FreeEnergy& f, co
 template <typename T>
 void launch_prec(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,
                  double inv_dt, const T* U, T* pinv, hipStream_t s);
+// 1 / (theta diag S) of the Cahn-Hilliard Newton system with mu eliminated (N values)
+template <typename T>
+void launch_prec_schur(const Geom& g, const FreeEnergy& f, double kappa, double mob, double inv_dt, double theta,
+                       const T* U, T* pinv, hipStream_t s);
+// y = scale 2^b x over the nodes (b boundary faces of a no-flux grid)
+template <typename T>
+void launch_unrow(const Geom& g, double scale, const T* x, T* y, hipStream_t s);
 // mu = [N(c) + kappa K c] / m
 template <typename T>
 void launch_chem(const Geom& g, const FreeEnergy& f, double kappa, const T* c, T* mu,

@@ -174,7 +174,17 @@ int d2h(void* dst, const void* src, size_t bytes, hipStream_t s)
     return PF_OK;
 }
 
-// The linear operator handed to GMRES: J = dR/dU at U (or its transpose).
+// The linear operator handed to GMRES: J = dR/dU at U (or its transpose), or, for
+// Cahn-Hilliard with the lumped mass, the same system with mu eliminated.  Its mu row is
+// linear and diagonal in x_mu,
+//   ib (inv_dt m x_c + M K x_mu) = b_c,   ib (m x_mu - A x_c) = b_mu,   A = N'(c) + kappa K
+// (ib = 1 / 2^b on no-flux rows), so
+//   S x_c = ib (inv_dt m x_c + (M / m) K A x_c) = b_c - ib (M / m) K (2^b b_mu),
+//   x_mu = (2^b b_mu + A x_c) / m.
+// Vectors of N instead of 2N entries, and about half the iterations: block Jacobi couples
+// the two planes only through their diagonals.  The residual of S is that of the whole
+// system (its mu row is solved exactly), so the stop tests keep their meaning.
+// Transposed: S^T l_c = b_c + ib A (2^b b_mu) / m, l_mu = (2^b b_mu - M K l_c) / m.
 template <typename T>
 struct LinOp {
     const pf_problem* p;
@@ -183,14 +193,97 @@ struct LinOp {
     double inv_dt;
     const T* U;
     int trans;
+    bool schur = false;
+    T* tmp = nullptr;  // N values between the two stencils of S
+    double mass() const { return std::pow(g.h, g.dim); }
     void apply(const T* v, T* out, hipStream_t s) const
     {
         if (p->model == PF_COUPLED)
             pfk::launch_cp_jvp<T>(g, p->kappa, p->mobility, p->mobility_eta, inv_dt, U, v, out, s);
         else if (p->model == PF_GRAIN)
             pfk::launch_gg_jvp2d<T>(g, p->nfields, p->mobility, p->kappa, p->gamma, inv_dt, U, v, out, s);
+        else if (schur)
+            schur_pass(pfk::ME_OUT, v, out, s);
         else
             pfk::launch_jvp<T>(g, p->model, f, p->kappa, p->mobility, inv_dt, U, v, out, s, trans, 0);
+    }
+    // out = S v
+    void schur_pass(int epi, const T* v, T* out, hipStream_t s) const
+    {
+        const double m = mass();
+        pfk::March<T> a, b;
+        b.out = out;
+        b.s0 = inv_dt * m;
+        b.rows = 1;
+        if (!trans && g.dim == 2) {
+            b.u = U;
+            b.v = v;
+            b.nq = 1.0 / m;
+            b.kv = p->kappa / m;
+            b.kw = p->mobility;
+            if (pfk::launch_march<T>(g, pfk::MOP_SCHUR, epi, f, b, s)) return;
+        }
+        b.base = v;
+        b.v = tmp;
+        a.v = v;
+        a.out = tmp;
+        if (!trans) {
+            a.u = U;
+            a.nq = 1.0 / m;
+            a.kv = p->kappa / m;
+            b.kv = p->mobility;
+            pfk::launch_march<T>(g, pfk::MOP_JVP, pfk::ME_OUT, f, a, s);
+            pfk::launch_march<T>(g, pfk::MOP_STIFF, epi, f, b, s);
+        } else {
+            a.kv = p->mobility / m;
+            b.u = U;
+            b.nq = 1.0;
+            b.kv = p->kappa;
+            pfk::launch_march<T>(g, pfk::MOP_STIFF, pfk::ME_OUT, f, a, s);
+            pfk::launch_march<T>(g, pfk::MOP_JVP, epi, f, b, s);
+        }
+    }
+    // out = the right-hand side of S for (b_c, b_mu) = b
+    void schur_rhs(const T* b, T* out, hipStream_t s) const
+    {
+        const double m = mass();
+        const T* bm = b + g.N;
+        if (g.bc) {
+            pfk::launch_unrow<T>(g, 1.0, bm, tmp, s);
+            bm = tmp;
+        }
+        pfk::March<T> a;
+        a.v = bm;
+        a.base = b;
+        a.out = out;
+        a.rows = 1;
+        if (!trans) {
+            a.kv = p->mobility / m;
+        } else {
+            a.u = U;
+            a.nq = -1.0 / m;
+            a.kv = -p->kappa / m;
+        }
+        pfk::launch_march<T>(g, trans ? pfk::MOP_JVP : pfk::MOP_STIFF, pfk::ME_SUB, f, a, s);
+    }
+    // x_mu (behind x_c in x) from x_c and b
+    void schur_back(const T* b, T* x, hipStream_t s) const
+    {
+        const double m = mass();
+        pfk::March<T> a;
+        a.v = x;
+        a.out = x + g.N;
+        a.p0 = b + g.N;
+        a.s0 = 1.0 / m;
+        a.rows = 1;
+        if (!trans) {
+            a.u = U;
+            a.nq = 1.0 / m;
+            a.kv = p->kappa / m;
+        } else {
+            a.kv = -p->mobility / m;
+        }
+        pfk::launch_march<T>(g, trans ? pfk::MOP_STIFF : pfk::MOP_JVP, pfk::ME_BACK, f, a, s);
     }
     // out = J v with the per-block partial sums of v . out in part2 (at most max_blocks),
     // their count in *nb; false (nothing launched) where the operator has no such fused
@@ -203,17 +296,27 @@ struct LinOp {
     }
 };
 
-// Solve J x = b (x overwritten, starting from 0) to ||b - J x|| <= tol_abs.
+// The elimination needs a diagonal mass, the point preconditioner (its absence is a
+// request for the bare system) and the marching kernels (fields below 2 GiB).
+template <typename T>
+bool schur_ok(const pf_problem* p, const pfk::Geom& g, const Opts& o)
+{
+    return p->model == PF_CAHN_HILLIARD && !g.cm && o.precond == PF_PRECOND_JACOBI &&
+           (size_t)g.N * sizeof(T) < (size_t(1) << 31);
+}
+
+// Solve J x = b (L.x overwritten, starting from 0; n unknowns) to ||b - J x|| <= tol_abs.
 // The preconditioner (if any) must already be in L.pinv.  Returns PF status;
 // *its receives the Arnoldi steps taken, *res the last residual estimate.
 template <typename T>
-int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, long long n, int m, int max_its, bool prec,
+int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long long n, int m, int max_its, bool prec,
           double bnorm, double tol_abs, int* its, double* res, hipStream_t s)
 {
-    // grain growth: point Jacobi over all p N unknowns (the Krylov kernels' point model)
-    const bool grain = A.p->model == PF_GRAIN;
-    const int model = grain ? 0 : A.p->model;
-    const long long Nn = grain ? n : A.g.N;
+    // grain growth and the eliminated Cahn-Hilliard system: point Jacobi over all n unknowns
+    // (the Krylov kernels' point model)
+    const bool point = A.p->model == PF_GRAIN || A.schur;
+    const int model = point ? 0 : A.p->model;
+    const long long Nn = point ? n : A.g.N;
     const T* pinv = prec ? L.pinv : nullptr;
     const int tr = A.trans;
     double* dh1 = L.dev + DEV_H1;
@@ -235,10 +338,10 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, long long n, int 
     for (;;) {
         // v0 = r / ||r||, z = P^-1 v0 with r = b - J x (= b on the first cycle)
         if (first) {
-            pfk::kr_norm2<T>(L.b, nullptr, n, L.part, dnrm, s);
+            pfk::kr_norm2<T>(b, nullptr, n, L.part, dnrm, s);
         } else {
             A.apply(L.x, L.w, s);
-            pfk::kr_rsub<T>(L.b, L.w, n, s);
+            pfk::kr_rsub<T>(b, L.w, n, s);
             pfk::kr_norm2<T>(L.w, nullptr, n, L.part, dnrm, s, rb->scal_dev());
             if (int rc = rb->wait_scalars(s)) return rc;
             beta = std::sqrt(rb->scal()[0]);
@@ -246,7 +349,7 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, long long n, int 
             if (!std::isfinite(beta)) return fail(PF_ENONFINITE, "GMRES residual is not finite");
             if (beta <= tol_abs || total >= max_its) break;
         }
-        pfk::kr_normalize_prec<T>(model, first ? L.b : L.w, dnrm, L.V, L.z, pinv, Nn, 1.0, s, tr);
+        pfk::kr_normalize_prec<T>(model, first ? b : L.w, dnrm, L.V, L.z, pinv, Nn, 1.0, s, tr);
         first = false;
         std::fill(gv.begin(), gv.end(), 0.0);
         gv[0] = beta;
@@ -318,6 +421,24 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, long long n, int 
     }
     *its = total;
     return check_launch("gmres");
+}
+
+// The whole Cahn-Hilliard correction (or adjoint) J x = L.b through the eliminated
+// system: L.x receives both planes.  L.R holds the right-hand side meanwhile (the
+// caller evaluates the residual anew afterwards).
+template <typename T>
+int gmres_schur(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, int m, int max_its, double tol_abs, int* its,
+                double* res, hipStream_t s)
+{
+    const long long N = A.g.N;
+    A.schur_rhs(L.b, L.R, s);
+    pfk::kr_norm2<T>(L.R, nullptr, N, L.part, L.dev + DEV_NRM, s, rb->scal_dev());
+    if (int rc = rb->wait_scalars(s)) return rc;
+    const double bn = std::sqrt(rb->scal()[0]);
+    if (!std::isfinite(bn)) return fail(PF_ENONFINITE, "right-hand side is not finite");
+    if (int rc = gmres<T>(rb, A, L, L.R, N, m, max_its, true, bn, tol_abs, its, res, s)) return rc;
+    A.schur_back(L.b, L.x, s);
+    return check_launch("eliminated system");
 }
 
 // Preconditioned CG on J x = b (x overwritten, starting from 0) to
@@ -419,7 +540,9 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
         R.reason = -2;
         status = fail(PF_ENONFINITE, "initial residual is not finite");
     }
-    const LinOp<T> A{p, g, f, inv_dt, U, 0};
+    LinOp<T> A{p, g, f, inv_dt, U, 0};
+    A.schur = schur_ok<T>(p, g, o);
+    A.tmp = L.z + g.N;  // (with mu eliminated the solver's vectors fill half their space)
     int k = 0;
     double dmax = 0.0, umax = 0.0;
     while (status == PF_OK) {
@@ -445,6 +568,8 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
             else if (p->model == PF_GRAIN)
                 pfk::launch_gg_tile2d<T>(g, p->nfields, p->mobility, p->kappa, p->gamma, 0.0, U, L.pinv, 2, s,
                                          nullptr, inv_dt);
+            else if (A.schur)
+                pfk::launch_prec_schur<T>(g, f, p->kappa, p->mobility, inv_dt, 1.0, U, L.pinv, s);
             else
                 pfk::launch_prec<T>(g, p->model, f, p->kappa, p->mobility, inv_dt, U, L.pinv, s);
         }
@@ -454,8 +579,8 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
         double lres = 0.0;
         const bool jac = o.precond == PF_PRECOND_JACOBI;
         if (int rc = o.krylov == PF_KRYLOV_CG ? pcg<T>(rb, A, L, n, o.max_its, jac, rk, lin * rk, &its, &lres, s)
-                                              : gmres<T>(rb, A, L, n, o.m, o.max_its, jac, rk, lin * rk, &its,
-                                                         &lres, s)) {
+                     : A.schur ? gmres_schur<T>(rb, A, L, o.m, o.max_its, lin * rk, &its, &lres, s)
+                               : gmres<T>(rb, A, L, L.b, n, o.m, o.max_its, jac, rk, lin * rk, &its, &lres, s)) {
             status = rc;
             R.reason = -2;
             break;
@@ -527,7 +652,12 @@ int newton_adjoint_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T*
     const long long n = ndof(p);
     NWS<T> L = layout<T>(p, ws);
     const double inv_dt = 1.0 / dt;
-    if (o.precond == PF_PRECOND_JACOBI)
+    LinOp<T> At{p, g, f, inv_dt, U, 1};
+    At.schur = schur_ok<T>(p, g, o);
+    At.tmp = L.z + g.N;
+    if (At.schur)
+        pfk::launch_prec_schur<T>(g, f, p->kappa, p->mobility, inv_dt, 1.0, U, L.pinv, s);
+    else if (o.precond == PF_PRECOND_JACOBI)
         pfk::launch_prec<T>(g, p->model, f, p->kappa, p->mobility, inv_dt, U, L.pinv, s);
     if (hipMemcpyAsync(L.b, vbar, (size_t)n * sizeof(T), hipMemcpyDeviceToDevice, s) != hipSuccess)
         return check_launch("adjoint rhs copy");
@@ -536,7 +666,6 @@ int newton_adjoint_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T*
     if (int rc = d2h(&nn, L.dev + DEV_NRM, sizeof(double), s)) return rc;
     const double bn = std::sqrt(nn);
     if (!std::isfinite(bn)) return fail(PF_ENONFINITE, "adjoint right-hand side is not finite");
-    const LinOp<T> At{p, g, f, inv_dt, U, 1};
     int its = 0;
     double res = 0.0;
     // the adjoint solve is taken to the field-precision floor, not an inexact-Newton tolerance
@@ -544,8 +673,8 @@ int newton_adjoint_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T*
     const bool jac = o.precond == PF_PRECOND_JACOBI;
     // (Allen-Cahn's Jacobian is symmetric: CG solves the transposed system as well)
     if (int rc = o.krylov == PF_KRYLOV_CG ? pcg<T>(&rbv, At, L, n, o.max_its * 4, jac, bn, tol, &its, &res, s)
-                                          : gmres<T>(&rbv, At, L, n, o.m, o.max_its * 4, jac, bn, tol, &its, &res,
-                                                     s))
+                 : At.schur ? gmres_schur<T>(&rbv, At, L, o.m, o.max_its * 4, tol, &its, &res, s)
+                            : gmres<T>(&rbv, At, L, L.b, n, o.m, o.max_its * 4, jac, bn, tol, &its, &res, s))
         return rc;
     // Ubar (mass rows) += (m/dt) lambda ; theta_bar -= (dr/dtheta)^T lambda
     pfk::launch_mass_axpy<T>(g, inv_dt, L.x, Ubar, s);

@@ -280,7 +280,11 @@ int pf_jvp(pf_ctx* ctx, const pf_problem* p, double inv_dt, const void* U, const
 /* ---------------------------------------------------------------------- */
 /* Backward-Euler Newton step (Eqs. 13-14, Sec. 2.3)                        */
 /* ---------------------------------------------------------------------- */
-enum { PF_PRECOND_NONE = 0, PF_PRECOND_JACOBI = 1 /* point (AC) / 2x2 block (CH) */ };
+/* PF_PRECOND_JACOBI: the point (AC), 2x2 (CH) or 3x3 block (coupled) diagonal.  With the
+ * lumped mass and GMRES, Cahn-Hilliard eliminates mu and takes the point diagonal of what
+ * remains, and both models raise the diagonal to a Chebyshev polynomial where the spectrum
+ * is known to be positive (AC: dt L W < 1; CH: dt M W^2 < 4 kappa; positive parameters). */
+enum { PF_PRECOND_NONE = 0, PF_PRECOND_JACOBI = 1 };
 /* Linear solver of each Newton correction.  PF_KRYLOV_CG (preconditioned
  * conjugate gradients, device-resident scalars) needs a symmetric positive
  * definite Jacobian: Allen-Cahn only, and dt * mobility * W < 1 (then
@@ -293,10 +297,12 @@ typedef struct pf_newton_opts {
     double atol;            /* or ||R||_2 <= atol (default 0) */
     int32_t max_newton;     /* Newton corrections (default 20) */
     int32_t gmres_restart;  /* Krylov dimension m of GMRES(m), 1..64 (default 30) */
-    int32_t gmres_max_its;  /* Arnoldi steps per Newton correction (default 600) */
+    int32_t gmres_max_its;  /* Krylov iterations per Newton correction (default 600) */
     int32_t precond;        /* PF_PRECOND_* (default PF_PRECOND_JACOBI) */
     double lin_rtol_max;    /* inexact-Newton forcing: linear rtol = clamp(0.1 ||R_k||/||R_0||, */
-    double lin_rtol_min;    /*   lin_rtol_min, lin_rtol_max) (defaults 1e-2, 1e-6) */
+    double lin_rtol_min;    /*   lin_rtol_min, lin_rtol_max) (defaults 1e-2, 1e-6), never below what
+                             * leaves 1/100 of the rtol / atol stop, and (stagnation = 1)
+                             * lin_rtol_max once ||R|| is at the field precision's rounding floor */
     int32_t stagnation;     /* 1: also stop at the field precision's rounding floor: after
                              * >= 2 corrections ||R_k|| > ||R_{k-1}||/2 while the last
                              * correction is <= 8 eps max|U|, or ||R_k|| > 0.9 ||R_{k-1}||
@@ -307,7 +313,9 @@ typedef struct pf_newton_opts {
 
 typedef struct pf_newton_report {
     int32_t newton_its;      /* corrections applied */
-    int32_t gmres_its;       /* Krylov iterations over all corrections (Arnoldi steps or CG) */
+    int32_t gmres_its;       /* Krylov iterations over all corrections: products with J in CG or
+                              * in the Arnoldi steps (with a polynomial preconditioner, its
+                              * degree counted with each step) */
     int32_t converged;       /* 1 if a stop test passed */
     int32_t reason;          /* 0 rtol, 1 atol, 2 rounding floor, -1 max_newton, -2 non-finite */
     double res_norm[33];     /* ||R||_2 per iterate (FP64), entries 0..newton_its (<= 32 kept) */

@@ -477,6 +477,29 @@ __global__ __launch_bounds__(KB) void k_update(const T* __restrict__ V, long lon
     }
 }
 
+// w = V y, z = pinv w
+template <typename T>
+__global__ __launch_bounds__(KB) void k_combine(const T* __restrict__ V, long long ld, int k,
+                                                const double* __restrict__ y, const T* __restrict__ pinv,
+                                                T* __restrict__ w, T* __restrict__ z, long long n)
+{
+    const long long i = (long long)blockIdx.x * KB + threadIdx.x;
+    if (i >= n) return;
+    double s = 0.0;
+    for (int j = 0; j < k; ++j) s = fma(y[j], (double)V[j * ld + i], s);
+    const T t = (T)s;
+    w[i] = t;
+    z[i] = t * pinv[i];
+}
+
+// x += y
+template <typename T>
+__global__ __launch_bounds__(KB) void k_add(T* __restrict__ x, const T* __restrict__ y, long long n)
+{
+    const long long i = (long long)blockIdx.x * KB + threadIdx.x;
+    if (i < n) x[i] += y[i];
+}
+
 // w = b - w   (turns J x into the residual b - J x), elementwise
 template <typename T>
 __global__ __launch_bounds__(KB) void k_rsub(const T* __restrict__ b, T* __restrict__ w, long long n)
@@ -852,6 +875,19 @@ void kr_update(int model, const T* V, long long ld, int k, const double* y, cons
 }
 
 template <typename T>
+void kr_combine(const T* V, long long ld, int k, const double* y, const T* pinv, T* w, T* z, long long n,
+                hipStream_t s)
+{
+    k_combine<T><<<grid1(n), KB, 0, s>>>(V, ld, k, y, pinv, w, z, n);
+}
+
+template <typename T>
+void kr_add(T* x, const T* y, long long n, hipStream_t s)
+{
+    k_add<T><<<grid1(n), KB, 0, s>>>(x, y, n);
+}
+
+template <typename T>
 void kr_rsub(const T* b, T* w, long long n, hipStream_t s)
 {
     k_rsub<T><<<grid1(n), KB, 0, s>>>(b, w, n);
@@ -880,6 +916,8 @@ void kr_add_maxabs(T* x, const T* y, long long n, double* part, double* out, hip
                                        double, hipStream_t, int);                               \
     template void kr_update<T>(int, const T*, long long, int, const double*, const T*, T*,       \
                                long long, hipStream_t, int);                                    \
+    template void kr_combine<T>(const T*, long long, int, const double*, const T*, T*, T*, long long, hipStream_t); \
+    template void kr_add<T>(T*, const T*, long long, hipStream_t);                               \
     template void kr_rsub<T>(const T*, T*, long long, hipStream_t);                              \
     template void kr_scale<T>(const T*, T*, double, long long, hipStream_t);                     \
     template void kr_add_maxabs<T>(T*, const T*, long long, double*, double*, hipStream_t, double*);

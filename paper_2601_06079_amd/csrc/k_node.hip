@@ -54,12 +54,12 @@ __global__ __launch_bounds__(256) void k_residual(const T* __restrict__ U, const
 }
 
 // (Block-)Jacobi preconditioner of dR/dU at U:
-//   Allen-Cahn:    pinv[a] = 1 / (inv_dt m + L (N'_aa + kappa K_aa))
+//   Allen-Cahn:    pinv[a] = 1 / (theta (inv_dt m + L (N'_aa + kappa K_aa)))
 //   Cahn-Hilliard: pinv[4a..4a+3] = inverse of [[inv_dt m, M K_aa], [-(N'_aa + kappa K_aa), m]]
 // (row-major), with N'_aa = sum_e sum_q |J| f''(u_q) phi_a(q)^2.
 template <typename T, int D, int MODEL>
 __global__ __launch_bounds__(256) void k_prec(const T* __restrict__ U, T* __restrict__ pinv, Geom g,
-                                              Lin<T> F, T detJ, T kappa, T mob, T m, T inv_dt)
+                                              Lin<T> F, T detJ, T kappa, T mob, T m, T inv_dt, double theta)
 {
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     int i, j, k;
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) void k_prec(const T* __restrict__ U, T* __rest
     const double kd = g.quad ? (double)stiff_lob_diag<T, D>((T)g.h) : (double)stiff_diag<T, D>((T)g.h);
     const double ib = 1.0 / bfactor<D>(g, i, j, k);  // no-flux rows (1 on periodic grids)
     if constexpr (MODEL == 0) {
-        pinv[idx] = (T)(1.0 / (ib * ((double)inv_dt * m + (double)mob * (nd + (double)kappa * kd))));
+        pinv[idx] = (T)(1.0 / (theta * ib * ((double)inv_dt * m + (double)mob * (nd + (double)kappa * kd))));
     } else {
         const double a = ib * (double)inv_dt * m, b = ib * (double)mob * kd;
         const double c = -ib * (nd + (double)kappa * kd), d = ib * (double)m;
@@ -446,33 +446,18 @@ void launch_jvp(const Geom& g, int model, const FreeEnergy& f, double kappa, dou
 
 template <typename T>
 void launch_prec(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,
-                 double inv_dt, const T* U, T* pinv, hipStream_t s)
+                 double inv_dt, const T* U, T* pinv, hipStream_t s, double theta)
 {
     const double detJ = std::pow(0.5 * g.h, g.dim), m = std::pow(g.h, g.dim);
     Lin<T> F{(T)f.b0, (T)f.b1, (T)f.b2};
     DIM_SWITCH(g, {
         if (model == 0)
             k_prec<T, D, 0><<<grid_for(g), 256, 0, s>>>(U, pinv, g, F, (T)detJ, (T)kappa, (T)mob,
-                                                         (T)m, (T)inv_dt);
+                                                         (T)m, (T)inv_dt, theta);
         else
             k_prec<T, D, 1><<<grid_for(g), 256, 0, s>>>(U, pinv, g, F, (T)detJ, (T)kappa, (T)mob,
-                                                         (T)m, (T)inv_dt);
+                                                         (T)m, (T)inv_dt, 1.0);
     });
-}
-
-// Centre entries and sums of products of the unit Q1 stencils: K_aa, the diagonals of
-// K K and of K M (M the Gauss-integrated mass over m), and the largest symbol of K;
-// 2-D h-free, 3-D per h (K K: per h^2)
-struct StencilDiag { double kd, kk, km, kmax; };
-inline StencilDiag stencil_diag(const Geom& g)
-{
-    // nodal: 5/7-point K, M the identity.  Gauss: 2-D entries 8/3, -1/3 (8 neighbours) and
-    // mass (4 1 4 1 16 ...)/36; 3-D entries 8/3, 0 (faces), -1/6 (12 edges), -1/12 (8
-    // corners) and mass 8/27, 2/27, 1/54, 1/216; the symbol is largest at one axis' Nyquist
-    // wave (4), nodal at all of them (8 / 12)
-    if (g.quad) return g.dim == 2 ? StencilDiag{4.0, 20.0, 4.0, 8.0} : StencilDiag{6.0, 42.0, 6.0, 12.0};
-    return g.dim == 2 ? StencilDiag{8.0 / 3.0, 8.0, 1.0, 4.0}
-                      : StencilDiag{8.0 / 3.0, 7.5, 8.0 / 3.0 * 8.0 / 27.0 - 2.0 / 54.0 - 8.0 / 12.0 / 216.0, 4.0};
 }
 
 template <typename T>
@@ -554,7 +539,7 @@ void launch_energy(const Geom& g, const FreeEnergy& f, double kappa, const T* c,
     template void launch_jvp<T>(const Geom&, int, const FreeEnergy&, double, double, double,       \
                                 const T*, const T*, T*, hipStream_t, int, int);                   \
     template void launch_prec<T>(const Geom&, int, const FreeEnergy&, double, double, double,      \
-                                 const T*, T*, hipStream_t);                                      \
+                                 const T*, T*, hipStream_t, double);                              \
     template void launch_prec_schur<T>(const Geom&, const FreeEnergy&, double, double, double, double, const T*, \
                                        T*, hipStream_t);                                          \
     template void launch_unrow<T>(const Geom&, double, const T*, T*, hipStream_t);                 \

@@ -131,9 +131,25 @@ inline bool launch_march(const Geom& g, int op, int epi, const FreeEnergy& f, co
     return g.dim == 3 ? launch_march3d<T>(g, op, epi, f, m, s) : launch_march2d<T>(g, op, epi, f, m, s);
 }
 // (block-)Jacobi inverse of dR/dU at U: N (Allen-Cahn) or 4N (Cahn-Hilliard) values
+// (Allen-Cahn: divided by theta)
 template <typename T>
 void launch_prec(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,
-                 double inv_dt, const T* U, T* pinv, hipStream_t s);
+                 double inv_dt, const T* U, T* pinv, hipStream_t s, double theta = 1.0);
+// Centre entries and sums of products of the unit Q1 stencils: K_aa, the diagonals of
+// K K and of K M (M the Gauss-integrated mass over m), and the largest symbol of K;
+// 2-D h-free, 3-D per h (K K: per h^2)
+struct StencilDiag { double kd, kk, km, kmax; };
+inline StencilDiag stencil_diag(const Geom& g)
+{
+    // nodal: 5/7-point K, M the identity.  Gauss: 2-D entries 8/3, -1/3 (8 neighbours) and
+    // mass (4 1 4 1 16 ...)/36; 3-D entries 8/3, 0 (faces), -1/6 (12 edges), -1/12 (8
+    // corners) and mass 8/27, 2/27, 1/54, 1/216; the symbol is largest at one axis' Nyquist
+    // wave (4), nodal at all of them (8 / 12)
+    if (g.quad) return g.dim == 2 ? StencilDiag{4.0, 20.0, 4.0, 8.0} : StencilDiag{6.0, 42.0, 6.0, 12.0};
+    return g.dim == 2 ? StencilDiag{8.0 / 3.0, 8.0, 1.0, 4.0}
+                      : StencilDiag{8.0 / 3.0, 7.5, 8.0 / 3.0 * 8.0 / 27.0 - 2.0 / 54.0 - 8.0 / 12.0 / 216.0, 4.0};
+}
+
 // 1 / (theta diag S) of the Cahn-Hilliard Newton system with mu eliminated (N values)
 template <typename T>
 void launch_prec_schur(const Geom& g, const FreeEnergy& f, double kappa, double mob, double inv_dt, double theta,

@@ -44,6 +44,13 @@ void kr_normalize_prec(int model, const T* w, const double* nrm2, T* v, T* z, co
 template <typename T>
 void kr_update(int model, const T* V, long long ld, int k, const double* y, const T* pinv, T* x,
                long long N, hipStream_t s, int tr = 0);
+// w = V y, z = pinv w (n entries, point preconditioner)
+template <typename T>
+void kr_combine(const T* V, long long ld, int k, const double* y, const T* pinv, T* w, T* z, long long n,
+                hipStream_t s);
+// x += y
+template <typename T>
+void kr_add(T* x, const T* y, long long n, hipStream_t s);
 // w = b - w
 template <typename T>
 void kr_rsub(const T* b, T* w, long long n, hipStream_t s);

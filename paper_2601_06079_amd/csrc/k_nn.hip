@@ -2,7 +2,7 @@
 // this library adds; the paper has none).
 //
 // Network (width 32, 3x3 periodic convolutions, NHWC activations):
-//   a0 = (c, M, kappa, 0 ... 0)                      16 channels, bf16
+//   a0 = (c, M, kappa, 0 ... 0)                      16 channels, bf16 (formed in LDS)
 //   a_l = bf16(relu(conv(a_{l-1}; W_l) + b_l)), l = 1..3   32 channels, bf16
 //   d = conv(a_3; W_4) + b_4                          1 channel, fp32
 //   c_hat = c + d - mean(d)                           per sample (exact mass)
@@ -46,7 +46,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned short u16;
 
 constexpr int TW = 32;        // pixels per wave row
-constexpr int TR = 4;         // rows per wgrad tile (one per wave)
 constexpr int CR = 4;         // rows per forward/dgrad tile (CR / 4 per wave)
 constexpr int NBLK = 256;
 
@@ -80,14 +79,14 @@ __device__ __forceinline__ int halo_row(int i, int n)
 // LDS tile: (ROWS + 2) rows x (TW + 2) pixels, CIN channels, pixel stride padded by
 // 16 bytes: a stride of 4k banks with k odd (k = 5 for 32 channels, 3 for 16) puts
 // the 16-byte reads of 8 consecutive pixels on 8 disjoint bank quads
-template <int CIN, int ROWS = TR>
+template <int CIN, int ROWS>
 struct Tile {
     static constexpr int PSTRIDE = CIN * 2 + 16;  // bytes per pixel in LDS
     static constexpr int BYTES = (ROWS + 2) * (TW + 2) * PSTRIDE;
 };
 
 // stage the halo tile of rows y0-1 .. y0+ROWS, pixels x0-1 .. x0+TW (periodic)
-template <int CIN, int ROWS = TR>
+template <int CIN, int ROWS>
 __device__ __forceinline__ void stage_tile(const u16* __restrict__ act, int b, int H, int W, int y0,
                                            int x0, unsigned char* lds)
 {
@@ -112,6 +111,9 @@ __device__ __forceinline__ void stage_tile(const u16* __restrict__ act, int b, i
 //         M and kappa are constant over a sample, so their channels reduce to the
 //         bias beff = b1 + bf16(M) sum_tap W1[tap][1] + bf16(kappa) sum_tap W1[tap][2];
 //         a1 never reaches memory
+// MODE 5: as MODE 0 for the first layer (CIN = 16: c, M, kappa and 13 zero channels),
+//         the tile's pixel records packed while staging from the c plane and the
+//         sample's M and kappa (4 bytes per pixel read instead of 32 from a packed input)
 // MODE 3: as MODE 0 for the last hidden layer, followed by the output layer's
 //         channel contraction: instead of a3 it stores the 9 planes
 //         P[tap][p] = sum_ci W4[tap][ci] a3[p][ci] (FP32), which a gather sums over
@@ -122,7 +124,7 @@ __device__ __forceinline__ void stage_tile(const u16* __restrict__ act, int b, i
 // blockIdx.x, blockIdx.x + gridDim.x, ...; the next tile's global loads are
 // issued into registers before the current tile's MFMAs, so staging overlaps
 // compute.  Every output is the same MFMA chain as with one tile per block.
-struct InPlanes {  // MODE 4 only
+struct InPlanes {  // MODE 4 and 5
     const float* c;      // [B][H][W]
     const float* M;      // [B]
     const float* kappa;  // [B]
@@ -216,6 +218,13 @@ __global__ __launch_bounds__(NBLK, 3) void k_conv_mfma(const u16* __restrict__ i
             }                                                                                               \
             break;                                                                                          \
         }                                                                                                   \
+        if (MODE == 5) {                                                                                    \
+            int i_ = threadIdx.x;                                                                           \
+            i_ = i_ < (CR + 2) * (TW + 2) ? i_ : (CR + 2) * (TW + 2) - 1;                                   \
+            const int gy = halo_row(y0_ - 1 + i_ / (TW + 2), H), gx = wrapi(x0_ - 1 + i_ % (TW + 2), W);   \
+            cs0 = ip.c[((size_t)b_ * H + gy) * W + gx];                                                     \
+            break;                                                                                          \
+        }                                                                                                   \
         uint4* dst_[4] = {&s0, &s1, &s2, &s3};                                                              \
         _Pragma("unroll") for (int q = 0; q < PER; ++q)                                                     \
         {                                                                                                   \
@@ -238,6 +247,15 @@ __global__ __launch_bounds__(NBLK, 3) void k_conv_mfma(const u16* __restrict__ i
             if (threadIdx.x < 32) {
                 const int bt = t / (tiles_x * tiles_y);
                 sbeff[co] = l1b + bf16_val(bf16_bits(ip.M[bt])) * l1s1 + bf16_val(bf16_bits(ip.kappa[bt])) * l1s2;
+            }
+        } else if constexpr (MODE == 5) {
+            static_assert(MODE != 5 || (CIN == 16 && (CR + 2) * (TW + 2) <= NBLK), "one pixel per thread");
+            if (threadIdx.x < (CR + 2) * (TW + 2)) {
+                const int bt = t / (tiles_x * tiles_y);
+                const unsigned m0 = bf16_bits(ip.M[bt]), k0 = bf16_bits(ip.kappa[bt]);
+                uint4* dst = reinterpret_cast<uint4*>(lds + threadIdx.x * PS);
+                dst[0] = make_uint4(bf16_bits(cs0) | (m0 << 16), k0, 0u, 0u);
+                dst[1] = make_uint4(0u, 0u, 0u, 0u);
             }
         } else {
             const uint4 src[4] = {s0, s1, s2, s3};
@@ -376,127 +394,232 @@ __global__ __launch_bounds__(NBLK, 3) void k_conv_mfma(const u16* __restrict__ i
 #undef PF_CONV_FETCH
 }
 
-// wgrad of a hidden layer: part[block][tap][ci][co] = sum over this block's pixel
-// tiles of a_in(p + tap)[ci] g(p)[co]; partb[block][co] = sum g(p)[co].
-// CIN = 16 (first layer, channels 16..31 of the M tile are zero) or 32.
-template <int CIN>
-__global__ __launch_bounds__(NBLK) void k_wgrad_mfma(const u16* __restrict__ ain,
-                                                     const u16* __restrict__ g, float* __restrict__ part,
-                                                     float* __restrict__ partb, int B, int H, int W)
+// ---- weight gradients (K = pixels) --------------------------------------------
+// Both operands of the product need 8 consecutive pixels of one channel per lane, while
+// memory and LDS hold pixels of 32 channels.  ds_read_tr16_b64 transposes while it reads:
+// of 16 lanes reading 8 bytes each, lane i receives 16-bit column i % 4 of the lanes
+// 4 j + i / 4 (j = 0..3), so with lane s reading pixel s / 4, channels 4 (s % 4) .. + 3,
+// lane i receives channel i of 4 consecutive pixels.  Two reads make an operand; eight
+// 2-byte reads and their packing did before, and bound the kernel (252 us per 32-channel
+// call on 16 x 512^2).  The pixel stride is 64 bytes without padding: the 32 lanes of a
+// half wave then read 256 contiguous bytes.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x8 read_pixels8(const u16* p)
 {
-    __shared__ __align__(16) unsigned char la[Tile<CIN>::BYTES];
-    __shared__ __align__(16) u16 lg[TR * TW * 32 + 8];
+    auto tr = [](const u16* q) {
+        return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(q));
+    };
+    const s16x4 lo = tr(p), hi = tr(p + 4 * 32);
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+}
+// this lane's (pixel, channel) offset inside a 16-pixel x 32-channel operand
+__device__ __forceinline__ int tr_offset(int lane)
+{
+    const int blk = lane >> 4, s = lane & 15;
+    return ((blk >> 1) * 8 + (s >> 2)) * 32 + (blk & 1) * 16 + 4 * (s & 3);
+}
+
+constexpr int WR = 4;                              // rows per weight-gradient tile
+constexpr int GCH = WR * TW * 4;                   // 16-byte chunks of a tile's g
+constexpr int ACH = (WR + 2) * (TW + 2) * 4;       // of its input halo (32 channels)
+constexpr int GPER = (GCH + NBLK - 1) / NBLK, APER = (ACH + NBLK - 1) / NBLK;
+constexpr int WROW = 9 * 32 * 32 + 32;             // a partial: W then b, as in the parameters
+constexpr int WROW1 = 9 * 3 * 32 + 32;             // the first layer's
+
+// (a native vector: arrays of HIP's uint4 struct end up in scratch memory)
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+// chunk q of the gradient tile (zeros in rows past H)
+__device__ __forceinline__ u32x4 fetch_g(const u16* __restrict__ g, int b, int H, int W, int y0, int x0, int q)
+{
+    const int ch = q & 3, pix = q >> 2, r = pix / TW, px = pix % TW;
+    const int y = y0 + r;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(
+        g + ((((size_t)b * H + min(y, H - 1)) * W + x0 + px) * 32 + ch * 8));
+    return y < H ? v : u32x4{0u, 0u, 0u, 0u};
+}
+// Weight and bias gradient of a 32-channel layer: part[block][tap][ci][co] = the sum over
+// the block's tiles of a_in(p + tap)[ci] g(p)[co], then part[block][9216 + co] = sum g(p)[co].
+// Wave wv owns taps wv, wv + 4, wv + 8; the next tile's chunks are loaded into registers
+// during the products.  Four blocks per CU hide what is left of the staging.
+// 16 x 512^2: 252 -> 150 us, 4.6 TB/s of the 695 MB the tiles and their halos read.
+__global__ __launch_bounds__(NBLK, 4) void k_wgrad32(const u16* __restrict__ ain, const u16* __restrict__ g,
+                                                     float* __restrict__ part, int B, int H, int W)
+{
+    __shared__ __align__(16) u16 la[ACH * 8];
+    __shared__ __align__(16) u16 lg[GCH * 8];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int m = lane & 31, kh = lane >> 5;
-    const int tiles_x = W / TW, tiles_y = (H + TR - 1) / TR;
-    const int ntiles = tiles_x * tiles_y * B;
-    // wave wv owns taps wv, wv + 4, wv + 8
+    const int tiles_x = W / TW, tiles_y = (H + WR - 1) / WR, ntiles = tiles_x * tiles_y * B;
     f32x16 acc[3] = {{}, {}, {}};
     float db = 0.0f;
-    for (int t0 = blockIdx.x; t0 < ntiles; t0 += gridDim.x) {
-        int t = t0;
-        const int tx = t % tiles_x;
-        t /= tiles_x;
-        const int ty = t % tiles_y;
-        const int b = t / tiles_y;
-        const int x0 = tx * TW, y0 = ty * TR;
-        __syncthreads();
-        stage_tile<CIN>(ain, b, H, W, y0, x0, la);
-        for (int q = threadIdx.x; q < TR * TW * 4; q += NBLK) {  // 16-byte chunks of g
-            const int ch = q & 3, pix = q >> 2;
-            const int r = pix / TW, px = pix % TW;
-            uint4 v = {0, 0, 0, 0};
-            if (y0 + r < H)
-                v = *reinterpret_cast<const uint4*>(g + ((((size_t)b * H + y0 + r) * W + x0 + px) * 32 + ch * 8));
-            *reinterpret_cast<uint4*>(lg + pix * 32 + ch * 8) = v;
-        }
-        __syncthreads();
-        // K loop over the tile's 128 pixels, 16 at a time (rows past H hold g = 0)
-#pragma unroll 1
-        for (int k0 = 0; k0 < TR * TW; k0 += 16) {
-            // B operand: g[pixel k0 + 8 kh + j][co = m]
-            bf16x8 bg;
+    struct Staged {
+        u32x4 a[APER], g[GPER];
+    };
+    auto fetch = [&](int t) {
+        Staged f;
+        const int x0 = t % tiles_x * TW, y0 = t / tiles_x % tiles_y * WR, b = t / (tiles_x * tiles_y);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const u16 bits = lg[(k0 + 8 * kh + j) * 32 + m];
-                bg[j] = __builtin_bit_cast(__bf16, bits);
-                if (wv == 0) db += bf16_val(bits);  // the bias gradient: lane (co, kh) sums its half
-            }
+        for (int i = 0; i < APER; ++i) {
+            const int q = min((int)threadIdx.x + i * NBLK, ACH - 1);
+            const int ch = q & 3, pix = q >> 2, ry = pix / (TW + 2), px = pix % (TW + 2);
+            const int gy = halo_row(y0 - 1 + ry, H), gx = wrapi(x0 - 1 + px, W);
+            f.a[i] = *reinterpret_cast<const u32x4*>(ain + (((size_t)b * H + gy) * W + gx) * 32 + ch * 8);
+        }
+#pragma unroll
+        for (int i = 0; i < GPER; ++i) f.g[i] = fetch_g(g, b, H, W, y0, x0, threadIdx.x + i * NBLK);
+        return f;
+    };
+    static_assert(GCH % NBLK == 0, "whole rounds of g chunks");
+    const int to = tr_offset(lane);
+    int t = blockIdx.x;
+    Staged st = fetch(min(t, ntiles - 1));
+    for (; t < ntiles; t += gridDim.x) {
+        __syncthreads();  // the previous tile's reads are done
+#pragma unroll
+        for (int i = 0; i < APER; ++i) {
+            const int q = threadIdx.x + i * NBLK;
+            if (q < ACH) reinterpret_cast<u32x4*>(la)[q] = st.a[i];
+        }
+#pragma unroll
+        for (int i = 0; i < GPER; ++i) reinterpret_cast<u32x4*>(lg)[threadIdx.x + i * NBLK] = st.g[i];
+        __syncthreads();
+        st = fetch(min(t + (int)gridDim.x, ntiles - 1));  // (past the end: a valid dummy)
+#pragma unroll 2
+        for (int k0 = 0; k0 < WR * TW; k0 += 16) {
+            const int r = k0 / TW, px = k0 % TW;
+            const bf16x8 bg = read_pixels8(lg + k0 * 32 + to);
+            if (wv == 0)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) db += (float)bg[j];
 #pragma unroll
             for (int s = 0; s < 3; ++s) {
                 const int tap = wv + 4 * s;
                 if (tap < 9) {
-                    const int dy = tap / 3, dx = tap % 3;
-                    bf16x8 aa;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const int p = k0 + 8 * kh + j;  // pixel of the tile: row p / TW, column p % TW
-                        const int r = p / TW, px = p % TW;
-                        u16 bits = 0;
-                        if (m < CIN)
-                            bits = *reinterpret_cast<const u16*>(
-                                la + ((r + dy) * (TW + 2) + px + dx) * Tile<CIN>::PSTRIDE + m * 2);
-                        aa[j] = __builtin_bit_cast(__bf16, bits);
-                    }
+                    const bf16x8 aa = read_pixels8(la + ((r + tap / 3) * (TW + 2) + px + tap % 3) * 32 + to);
                     acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aa, bg, acc[s], 0, 0, 0);
                 }
             }
         }
     }
-    // lanes co and co + 32 of wave 0 hold the two halves of the pixels
-    db += __shfl_down(db, 32);
-    // write this block's partial: C[ci][co] tile per tap
-    float* pb = part + (size_t)blockIdx.x * 9 * 32 * 32;
+    db += __shfl_down(db, 32);  // lanes co and co + 32 of wave 0 hold the two halves of the pixels
+    float* pb = part + (size_t)blockIdx.x * WROW;
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
         const int tap = wv + 4 * s;
         if (tap < 9)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int ci = 8 * (i >> 2) + 4 * kh + (i & 3);
-                pb[((size_t)tap * 32 + ci) * 32 + m] = acc[s][i];
-            }
+            for (int i = 0; i < 16; ++i) pb[(tap * 32 + 8 * (i >> 2) + 4 * kh + (i & 3)) * 32 + m] = acc[s][i];
     }
-    if (wv == 0 && lane < 32) partb[(size_t)blockIdx.x * 32 + lane] = db;
+    if (wv == 0 && lane < 32) pb[9 * 32 * 32 + lane] = db;
 }
 
-// out[i] = sum over blocks of part[block][i]  (i < n), fixed order: a block
-// owns 32 columns; its 8 thread groups sum every 8th partial row (coalesced
-// 128-byte row segments), then one fixed 8-way combine.
+// The first layer's: its inputs are c, M and kappa (bf16), M and kappa constant over a
+// sample, so one product per 16 pixels forms all of W1's gradient: the rows of the A operand
+// are the nine taps of c, then M and kappa (the same for every tap).  part[block] is laid
+// out as W1, b1.  c's tile is kept in three copies shifted by one pixel, so that a tap's 8
+// pixels are one aligned 16-byte read.  Wave 0 computes; the others help to stage.
+// 16 x 512^2: 302 (nine products and a 16-channel packed input) -> 70 us for g's 268 MB.
+__global__ __launch_bounds__(NBLK) void k_wgrad1(const float* __restrict__ c, const float* __restrict__ Mv,
+                                                 const float* __restrict__ kv, const u16* __restrict__ g,
+                                                 float* __restrict__ part, int B, int H, int W)
+{
+    __shared__ __align__(16) u16 lg[GCH * 8];
+    __shared__ __align__(16) u16 lc[3][WR + 2][TW];
+    __shared__ float red[12][32];
+    constexpr int CN = (WR + 2) * (TW + 2);
+    static_assert(CN <= NBLK, "one value of c per thread");
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int m = lane & 31, kh = lane >> 5;
+    const int tiles_x = W / TW, tiles_y = (H + WR - 1) / WR, ntiles = tiles_x * tiles_y * B;
+    const int cr = min((int)threadIdx.x, CN - 1) / (TW + 2), cx = min((int)threadIdx.x, CN - 1) % (TW + 2);
+    f32x16 acc = {};
+    float db = 0.0f, fc = 0.0f;
+    u32x4 fg[GPER];
+    auto fetch = [&](int t) {
+        const int x0 = t % tiles_x * TW, y0 = t / tiles_x % tiles_y * WR, b = t / (tiles_x * tiles_y);
+        const int gy = halo_row(y0 - 1 + cr, H), gx = wrapi(x0 - 1 + cx, W);
+        fc = c[((size_t)b * H + gy) * W + gx];
+#pragma unroll
+        for (int i = 0; i < GPER; ++i) fg[i] = fetch_g(g, b, H, W, y0, x0, threadIdx.x + i * NBLK);
+    };
+    const int to = tr_offset(lane);
+    const int dy = m < 9 ? m / 3 : 0, dx = m < 9 ? m % 3 : 0;
+    int t = blockIdx.x;
+    if (t < ntiles) fetch(t);
+    for (; t < ntiles; t += gridDim.x) {
+        const int b = t / (tiles_x * tiles_y);
+        __syncthreads();  // the previous tile's reads are done
+        if (threadIdx.x < CN) {
+            const u16 v = bf16_bits(fc);
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+                if (cx >= s && cx < TW + s) lc[s][cr][cx - s] = v;
+        }
+#pragma unroll
+        for (int i = 0; i < GPER; ++i) reinterpret_cast<u32x4*>(lg)[threadIdx.x + i * NBLK] = fg[i];
+        __syncthreads();
+        if (t + (int)gridDim.x < ntiles) fetch(t + gridDim.x);
+        if (wv == 0) {
+            const u16 cst = m == 9 ? bf16_bits(Mv[b]) : m == 10 ? bf16_bits(kv[b]) : (u16)0;
+            bf16x8 ca;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) ca[j] = __builtin_bit_cast(__bf16, cst);
+#pragma unroll
+            for (int k0 = 0; k0 < WR * TW; k0 += 16) {
+                const bf16x8 bg = read_pixels8(lg + k0 * 32 + to);
+                bf16x8 aa = *reinterpret_cast<const bf16x8*>(&lc[dx][k0 / TW + dy][k0 % TW + 8 * kh]);
+                if (m >= 9) aa = ca;
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aa, bg, acc, 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) db += (float)bg[j];
+            }
+        }
+    }
+    db += __shfl_down(db, 32);
+    if (wv == 0) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int row = 8 * (i >> 2) + 4 * kh + (i & 3);
+            if (row < 11) red[row][m] = acc[i];
+        }
+        if (lane < 32) red[11][lane] = db;
+    }
+    __syncthreads();
+    float* pb = part + (size_t)blockIdx.x * WROW1;
+    for (int i = threadIdx.x; i < WROW1; i += NBLK) {
+        const int q = i / 32, ci = q % 3;
+        pb[i] = red[q == 27 ? 11 : ci == 0 ? q / 3 : 8 + ci][i % 32];
+    }
+}
+
+// out[i] = sum over blocks of part[block][i]  (i < n), FP64, fixed order: a block owns 8
+// columns; its 32 thread groups sum every 32nd partial row, loads of 8 rows in flight, then
+// one combine in group order.  (32 columns and 8 groups left 288 blocks walking 128 rows
+// one load at a time: 36 us for 1024 rows of 9216.)
+constexpr int SPC = 8, SPG = NBLK / SPC;
 __global__ __launch_bounds__(NBLK) void k_sum_partials(const float* __restrict__ part, int nb,
                                                        int n, float* __restrict__ out)
 {
-    const int c = threadIdx.x & 31, grp = threadIdx.x >> 5;
-    const int i = blockIdx.x * 32 + c;
+    const int c = threadIdx.x % SPC, grp = threadIdx.x / SPC;
+    const int i = blockIdx.x * SPC + c, ic = min(i, n - 1);
     double s = 0.0;
-    if (i < n)
-        for (int b = grp; b < nb; b += NBLK / 32) s += (double)part[(size_t)b * n + i];
-    __shared__ double sh[NBLK / 32][32];
+    for (int b0 = grp; b0 < nb; b0 += 8 * SPG) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = part[(size_t)min(b0 + u * SPG, nb - 1) * n + ic];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += b0 + u * SPG < nb ? (double)v[u] : 0.0;
+    }
+    __shared__ double sh[SPG][SPC];
     sh[grp][c] = s;
     __syncthreads();
     if (grp == 0 && i < n) {
         double t = 0.0;
-        for (int q = 0; q < NBLK / 32; ++q) t += sh[q][c];
+        for (int q = 0; q < SPG; ++q) t += sh[q][c];
         out[i] = (float)t;
     }
-}
-
-// a0 = bf16 (c, M, kappa, 0 x 13) per pixel
-__global__ __launch_bounds__(NBLK) void k_pack_input(const float* __restrict__ c,
-                                                     const float* __restrict__ Mv,
-                                                     const float* __restrict__ kv, u16* __restrict__ a0,
-                                                     int B, int HW)
-{
-    const size_t p = (size_t)blockIdx.x * NBLK + threadIdx.x;
-    if (p >= (size_t)B * HW) return;
-    const int b = (int)(p / HW);
-    u16 v[16] = {};
-    v[0] = bf16_bits(c[p]);
-    v[1] = bf16_bits(Mv[b]);
-    v[2] = bf16_bits(kv[b]);
-    uint4* dst = reinterpret_cast<uint4*>(a0 + p * 16);
-    dst[0] = *reinterpret_cast<uint4*>(&v[0]);
-    dst[1] = *reinterpret_cast<uint4*>(&v[8]);
 }
 
 // FP32 master parameters -> bf16 B fragments.  Hidden layer l, use u (0 forward, 1 dgrad):
@@ -904,15 +1027,6 @@ __global__ __launch_bounds__(NBLK) void k_check_final(const double* __restrict__
     }
 }
 
-// first-layer weight gradient: dW1[tap][ci][co] = tile[tap][ci][co] for ci < 3
-__global__ __launch_bounds__(NBLK) void k_extract_w1(const float* __restrict__ tile, float* __restrict__ dw1)
-{
-    const int i = blockIdx.x * NBLK + threadIdx.x;
-    if (i >= 9 * 3 * 32) return;
-    const int co = i % 32, ci = (i / 32) % 3, tap = i / 96;
-    dw1[i] = tile[(tap * 32 + ci) * 32 + co];
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -922,11 +1036,6 @@ void nn_check(const float* chat, const float* cprev, const float* cstep, int B, 
     const int nbs = (HW + NBLK - 1) / NBLK;
     k_check_sums<<<B * nbs, NBLK, 0, s>>>(chat, cprev, cstep, HW, 1.0 / kdt, 1.0 / dt, part);
     k_check_final<<<B, NBLK, 0, s>>>(part, nbs, out);
-}
-
-void nn_extract_w1(const float* tile, float* dw1, hipStream_t s)
-{
-    k_extract_w1<<<(9 * 3 * 32 + NBLK - 1) / NBLK, NBLK, 0, s>>>(tile, dw1);
 }
 
 NNOffsets nn_offsets()
@@ -960,7 +1069,8 @@ NNFragOffsets nn_frag_offsets()
 
 int nn_wgrad_blocks(int B, int H, int W)
 {
-    const long long tiles = (long long)B * ((H + TR - 1) / TR) * (W / TW);
+    // split-K: four blocks per CU
+    const long long tiles = (long long)B * ((H + WR - 1) / WR) * (W / TW);
     return (int)(tiles < 1024 ? tiles : 1024);
 }
 
@@ -988,11 +1098,14 @@ void nn_prep_weights(const float* params, u16* frag, u16* w4, hipStream_t s)
     k_prep_weights<<<(n + NBLK - 1) / NBLK, NBLK, 0, s>>>(params, nn_offsets(), frag, fo, w4);
 }
 
-void nn_pack_input(const float* c, const float* M, const float* kappa, u16* a0, int B, int HW,
-                   hipStream_t s)
+void nn_conv1_planes(const float* c, const float* M, const float* kappa, const u16* frag, const float* bias,
+                     u16* out, int B, int H, int W, hipStream_t s)
 {
-    const size_t n = (size_t)B * HW;
-    k_pack_input<<<(unsigned)((n + NBLK - 1) / NBLK), NBLK, 0, s>>>(c, M, kappa, a0, B, HW);
+    const int nt = nn_conv_blocks(B, H, W);
+    const unsigned nb = (unsigned)std::max(1, std::min(nt, conv_resident_blocks<16, 5>()));
+    const InPlanes ip{c, M, kappa, nullptr, nullptr};
+    const TapPlanes np{nullptr, nullptr, 0};
+    k_conv_mfma<16, 5><<<nb, NBLK, 0, s>>>(nullptr, frag, bias, nullptr, out, B, H, W, nt, ip, np);
 }
 
 void nn_conv(int layer, int mode, const u16* in, const u16* frag, const float* bias, const u16* mask,
@@ -1002,10 +1115,7 @@ void nn_conv(int layer, int mode, const u16* in, const u16* frag, const float* b
     auto grid = [&](int resident) { return (unsigned)std::max(1, std::min(nt, resident)); };
     const InPlanes none{nullptr, nullptr, nullptr, nullptr, nullptr};
     const TapPlanes np{nullptr, nullptr, 0};
-    if (layer == 1)
-        k_conv_mfma<16, 0><<<grid(conv_resident_blocks<16, 0>()), NBLK, 0, s>>>(in, frag, bias, mask, out, B, H,
-                                                                               W, nt, none, np);
-    else if (mode == 0)
+    if (mode == 0)
         k_conv_mfma<32, 0><<<grid(conv_resident_blocks<32, 0>()), NBLK, 0, s>>>(in, frag, bias, mask, out, B, H,
                                                                                W, nt, none, np);
     else
@@ -1048,19 +1158,20 @@ void nn_out_taps_project(const float* P, const float* params, const float* c, fl
     }
 }
 
-void nn_wgrad(int layer, const u16* ain, const u16* g, float* part, float* partb, int B, int H, int W,
-              hipStream_t s)
+void nn_wgrad32(const u16* ain, const u16* g, float* part, int B, int H, int W, hipStream_t s)
 {
-    const int nb = nn_wgrad_blocks(B, H, W);
-    if (layer == 1)
-        k_wgrad_mfma<16><<<nb, NBLK, 0, s>>>(ain, g, part, partb, B, H, W);
-    else
-        k_wgrad_mfma<32><<<nb, NBLK, 0, s>>>(ain, g, part, partb, B, H, W);
+    k_wgrad32<<<nn_wgrad_blocks(B, H, W), NBLK, 0, s>>>(ain, g, part, B, H, W);
+}
+
+void nn_wgrad1(const float* c, const float* M, const float* kappa, const u16* g, float* part, int B, int H, int W,
+               hipStream_t s)
+{
+    k_wgrad1<<<nn_wgrad_blocks(B, H, W), NBLK, 0, s>>>(c, M, kappa, g, part, B, H, W);
 }
 
 void nn_sum_partials(const float* part, int nb, int n, float* out, hipStream_t s)
 {
-    k_sum_partials<<<(n + 31) / 32, NBLK, 0, s>>>(part, nb, n, out);
+    k_sum_partials<<<(n + SPC - 1) / SPC, NBLK, 0, s>>>(part, nb, n, out);
 }
 
 void nn_out_fwd(const u16* a3, const u16* w4, const float* params, float* d, int B, int H, int W,

@@ -21,9 +21,10 @@ int nn_wgrad_blocks(int B, int H, int W);
 int nn_out_wgrad_blocks(int B, int H, int W);
 
 void nn_prep_weights(const float* params, unsigned short* frag, unsigned short* w4, hipStream_t s);
-void nn_pack_input(const float* c, const float* M, const float* kappa, unsigned short* a0, int B,
-                   int HW, hipStream_t s);
-// hidden layer `layer` (1..3): mode 0 forward (bias + relu), mode 1 input gradient (relu mask)
+// the first hidden layer (forward) from the c plane and the samples' M and kappa
+void nn_conv1_planes(const float* c, const float* M, const float* kappa, const unsigned short* frag,
+                     const float* bias, unsigned short* out, int B, int H, int W, hipStream_t s);
+// hidden layer 2 or 3: mode 0 forward (bias + relu), mode 1 input gradient (relu mask)
 void nn_conv(int layer, int mode, const unsigned short* in, const unsigned short* frag,
              const float* bias, const unsigned short* mask, unsigned short* out, int B, int H, int W,
              hipStream_t s);
@@ -41,9 +42,12 @@ void nn_conv3_taps(const unsigned short* in, const unsigned short* frag, const f
 // 16-byte aligned)
 void nn_out_taps_project(const float* P, const float* params, const float* c, float* d, double* part,
                          double* mean, float* chat, int B, int H, int W, hipStream_t s);
-// weight gradient partials of hidden layer `layer` (part: blocks x 9 x 32 x 32, partb: blocks x 32)
-void nn_wgrad(int layer, const unsigned short* ain, const unsigned short* g, float* part, float* partb,
-              int B, int H, int W, hipStream_t s);
+// weight and bias gradient partials of a 32-channel layer (part: blocks x 9248, laid out
+// W then b as in the parameters), and of the first layer (blocks x 896)
+void nn_wgrad32(const unsigned short* ain, const unsigned short* g, float* part, int B, int H, int W,
+                hipStream_t s);
+void nn_wgrad1(const float* c, const float* M, const float* kappa, const unsigned short* g, float* part, int B,
+               int H, int W, hipStream_t s);
 // out[i] = sum over nb blocks of part[block][i]
 void nn_sum_partials(const float* part, int nb, int n, float* out, hipStream_t s);
 void nn_out_fwd(const unsigned short* a3, const unsigned short* w4, const float* params, float* d,
@@ -61,7 +65,5 @@ void nn_adam(float* p, float* m, float* v, const float* g, int n, int t, double 
 // ||c_hat - c_prev|| / (K dt)); part: 3 B ceil(HW / 256) doubles
 void nn_check(const float* chat, const float* cprev, const float* cstep, int B, int HW, double kdt,
               double dt, double* part, double* out, hipStream_t s);
-// extract the first-layer gradient dW1[tap][ci < 3][co] from a [9][32][32] tile
-void nn_extract_w1(const float* tile, float* dw1, hipStream_t s);
 
 }  // namespace pfk

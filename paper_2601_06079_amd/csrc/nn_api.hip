@@ -12,8 +12,8 @@ namespace {
 inline size_t al(size_t b) { return (b + 255) & ~size_t(255); }
 
 struct NNWS {
-    unsigned short *a0, *a1, *a2, *a3, *ga, *gb, *frag, *w4;
-    float *d, *chat, *g, *r2, *part, *partb, *tile;
+    unsigned short *a1, *a2, *a3, *ga, *gb, *frag, *w4;
+    float *d, *chat, *g, *r2, *part;
     double *spart, *mean, *mean2;
     size_t bytes;
 };
@@ -30,7 +30,6 @@ NNWS nn_layout(int B, int H, int W, void* base)
     };
     const size_t P = (size_t)B * H * W;
     const pfk::NNFragOffsets fo = pfk::nn_frag_offsets();
-    L.a0 = (unsigned short*)take(P * 16 * 2);
     L.a1 = (unsigned short*)take(P * 32 * 2);
     L.a2 = (unsigned short*)take(P * 32 * 2);
     L.a3 = (unsigned short*)take(P * 32 * 2);
@@ -43,9 +42,7 @@ NNWS nn_layout(int B, int H, int W, void* base)
     L.g = (float*)take(P * 4);
     L.r2 = (float*)take(P * 4);
     const size_t nwg = (size_t)pfk::nn_wgrad_blocks(B, H, W), nog = (size_t)pfk::nn_out_wgrad_blocks(B, H, W);
-    L.part = (float*)take(std::max(nwg * 9 * 32 * 32, nog * 289) * 4);
-    L.partb = (float*)take(nwg * 32 * 4);
-    L.tile = (float*)take(9 * 32 * 32 * 4);
+    L.part = (float*)take(std::max(nwg * (9 * 32 * 32 + 32), nog * 289) * 4);
     const size_t nbs = ((size_t)H * W + 255) / 256;
     L.spart = (double*)take((size_t)B * nbs * 3 * 8);
     L.mean = (double*)take((size_t)B * 8);
@@ -63,16 +60,15 @@ int check_shape(int B, int H, int W)
 }
 
 // the forward pass (the weight fragments already prepared in L.frag, L.w4) into
-// chat; training (keep_a0) leaves a0..a3 and d in the workspace
+// chat; training (keep) leaves a1..a3 and d in the workspace
 void forward(const float* params, int B, int H, int W, const float* c, const float* M,
-             const float* kappa, const float* target, float* chat, NNWS& L, hipStream_t s, bool keep_a0)
+             const float* kappa, const float* target, float* chat, NNWS& L, hipStream_t s, bool keep)
 {
     const pfk::NNOffsets o = pfk::nn_offsets();
     const pfk::NNFragOffsets fo = pfk::nn_frag_offsets();
     const int HW = H * W;
-    if (keep_a0) {  // training: the weight gradients read a0, a1, a2 and a3
-        pfk::nn_pack_input(c, M, kappa, L.a0, B, HW, s);
-        pfk::nn_conv(1, 0, L.a0, L.frag + fo.f1, params + o.b1, nullptr, L.a1, B, H, W, s);
+    if (keep) {  // training: the weight gradients read a1, a2 and a3
+        pfk::nn_conv1_planes(c, M, kappa, L.frag + fo.f1, params + o.b1, L.a1, B, H, W, s);
         pfk::nn_conv(2, 0, L.a1, L.frag + fo.f2, params + o.b2, nullptr, L.a2, B, H, W, s);
         pfk::nn_conv(3, 0, L.a2, L.frag + fo.f3, params + o.b3, nullptr, L.a3, B, H, W, s);
         pfk::nn_out_fwd(L.a3, L.w4, params, L.d, B, H, W, s);
@@ -162,22 +158,18 @@ int pf_nn_backward(const float* params, int B, int H, int W, const float* c, con
         // output layer
         pfk::nn_out_bwd(L.a3, L.w4, L.g, L.ga, L.part, B, H, W, s);
         pfk::nn_sum_partials(L.part, pfk::nn_out_wgrad_blocks(B, H, W), 289, grad + o.w4, s);
+        // layer 3: ga = d pre3 (W and b lie side by side in the gradient as in a partial)
         const int nwg = pfk::nn_wgrad_blocks(B, H, W);
-        // layer 3: ga = d pre3
-        pfk::nn_wgrad(3, L.a2, L.ga, L.part, L.partb, B, H, W, s);
-        pfk::nn_sum_partials(L.part, nwg, 9 * 32 * 32, grad + o.w3, s);
-        pfk::nn_sum_partials(L.partb, nwg, 32, grad + o.b3, s);
+        pfk::nn_wgrad32(L.a2, L.ga, L.part, B, H, W, s);
+        pfk::nn_sum_partials(L.part, nwg, 9 * 32 * 32 + 32, grad + o.w3, s);
         pfk::nn_conv(3, 1, L.ga, L.frag + fo.d3, nullptr, L.a2, L.gb, B, H, W, s);  // gb = d pre2
         // layer 2
-        pfk::nn_wgrad(2, L.a1, L.gb, L.part, L.partb, B, H, W, s);
-        pfk::nn_sum_partials(L.part, nwg, 9 * 32 * 32, grad + o.w2, s);
-        pfk::nn_sum_partials(L.partb, nwg, 32, grad + o.b2, s);
+        pfk::nn_wgrad32(L.a1, L.gb, L.part, B, H, W, s);
+        pfk::nn_sum_partials(L.part, nwg, 9 * 32 * 32 + 32, grad + o.w2, s);
         pfk::nn_conv(2, 1, L.gb, L.frag + fo.d2, nullptr, L.a1, L.ga, B, H, W, s);  // ga = d pre1
-        // layer 1 (input channels padded 3 -> 16)
-        pfk::nn_wgrad(1, L.a0, L.ga, L.part, L.partb, B, H, W, s);
-        pfk::nn_sum_partials(L.part, nwg, 9 * 32 * 32, L.tile, s);
-        pfk::nn_extract_w1(L.tile, grad + o.w1, s);
-        pfk::nn_sum_partials(L.partb, nwg, 32, grad + o.b1, s);
+        // layer 1
+        pfk::nn_wgrad1(c, M, kappa, L.ga, L.part, B, H, W, s);
+        pfk::nn_sum_partials(L.part, nwg, 9 * 3 * 32 + 32, grad + o.w1, s);
         return check_launch("pf_nn_backward");
     });
 }

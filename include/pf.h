@@ -248,6 +248,15 @@ int pf_residual(pf_ctx* ctx, const pf_problem* p, const void* U, void* r, void* 
 int pf_step_explicit(pf_ctx* ctx, const pf_problem* p, double dt, int64_t nsteps, void* U, void* ws,
                      void* stream);
 
+/* nsteps single explicit steps of Allen-Cahn or Cahn-Hilliard (Eq. 12) that keep every
+ * state: states holds nsteps + 1 whole states of ndof elements, one after the other; the
+ * first is read, the others are written (bitwise what pf_step_explicit gives from the
+ * one before with nsteps = 1, in any number of calls).  Cahn-Hilliard: the mu plane of
+ * every state, the first included, receives [N(c) + kappa K c]/m.  Fields below 2 GiB,
+ * lumped mass; other models: PF_EUNSUPPORTED.  Asynchronous. */
+int pf_step_explicit_trajectory(pf_ctx* ctx, const pf_problem* p, double dt, int64_t nsteps, void* states,
+                                void* stream);
+
 /* out[0] = E_h(U) = sum_e sum_q |J| [ f(c_q) + kappa/2 |grad c_q|^2 ]  (Eqs. 5-6)
  *          (coupled model: [f_a(c_q)(1 - h(eta_q)) + f_b(c_q) h(eta_q) + kappa/2 |grad eta_q|^2],
  *          Eq. 7, with U the whole [c ; mu ; eta] state)
@@ -342,6 +351,7 @@ int pf_newton_step(pf_ctx* ctx, const pf_problem* p, double dt, const void* U_ol
 enum { PF_VJP_RESIDUAL = 0, PF_VJP_EXPLICIT_STEP = 1, PF_VJP_NEWTON_STEP = 2 };
 
 enum { PF_VJP_THETA_HOST = 1 }; /* pf_vjp flags: theta_bar is a host pointer */
+enum { PF_VJP_BEGIN = 1, PF_VJP_END = 2 }; /* flags of the adjoints that run in segments */
 /* Vector-Jacobian products of one building block, accumulated into Ubar and
  * theta_bar (3 doubles: mobility, kappa, W; a device pointer, or a host pointer
  * with flags = PF_VJP_THETA_HOST, which makes the call host-synchronous):
@@ -366,6 +376,17 @@ enum { PF_VJP_THETA_HOST = 1 }; /* pf_vjp flags: theta_bar is a host pointer */
  * pf_newton_step) and PF_VJP_THETA_HOST. */
 int pf_vjp(pf_ctx* ctx, const pf_problem* p, int kind, double dt, const void* U, const void* U_old,
            const void* vbar, void* Ubar, double* theta_bar, int flags, void* ws, void* stream);
+
+/* Adjoint of nsteps explicit steps along the states pf_step_explicit_trajectory left (the
+ * last one is not read): lam holds dO/dU of the final state on entry and of the first on
+ * return (Cahn-Hilliard: the c plane; the mu plane is not touched).  The sensitivities of
+ * theta = (mobility, kappa, W) accumulate in FP64 sums kept in ws: PF_VJP_BEGIN starts
+ * them, PF_VJP_END adds what they give to theta_bar (device, 3 doubles).  A trajectory
+ * processed in segments from the last to the first, BEGIN on the first call and END on
+ * the last, gives bitwise the one-call gradient.  ws: pf_workspace_size(PF_OP_VJP), kept
+ * between the calls of one trajectory.  Gauss quadrature.  Asynchronous. */
+int pf_vjp_explicit_trajectory(pf_ctx* ctx, const pf_problem* p, double dt, int64_t nsteps, const void* states,
+                               void* lam, double* theta_bar, int flags, void* ws, void* stream);
 
 /* ---------------------------------------------------------------------- */
 /* Ragged batches of independent 2-D problems (many samples in one launch) */
@@ -437,7 +458,6 @@ int pf_step_explicit_batched(pf_ctx* ctx, const pf_batch_info* info, const void*
  * every segment has an even number of steps).  Cahn-Hilliard plans:
  * PF_EUNSUPPORTED.  ws: pf_batch_workspace_size(PF_OP_VJP) of the same info,
  * kept between the calls of one trajectory.  Asynchronous. */
-enum { PF_VJP_BEGIN = 1, PF_VJP_END = 2 };
 int pf_vjp_explicit_batched(pf_ctx* ctx, const pf_batch_info* info, const void* plan, int64_t nsteps,
                             const void* states, void* lam, double* theta_bar, void* ws, int flags,
                             void* stream);

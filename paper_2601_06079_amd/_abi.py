@@ -33,7 +33,7 @@ TUNE_GG_STREAM = 9
 TUNE_JVP2D_STREAM = 10
 PRECOND_NONE, PRECOND_JACOBI = 0, 1
 VJP_RESIDUAL, VJP_EXPLICIT_STEP, VJP_NEWTON_STEP = 0, 1, 2
-VJP_BEGIN, VJP_END = 1, 2  # flags of pf_vjp_explicit_batched
+VJP_BEGIN, VJP_END = 1, 2  # flags of pf_vjp_explicit_batched and pf_vjp_explicit_trajectory
 
 
 class pf_problem(ct.Structure):
@@ -113,6 +113,8 @@ def lib():
         "pf_newton_step": (i32, [vp, P, f64, vp, vp, ct.POINTER(pf_newton_opts),
                                  ct.POINTER(pf_newton_report), vp, vp]),
         "pf_vjp": (i32, [vp, P, i32, f64, vp, vp, vp, vp, vp, i32, vp, vp]),
+        "pf_step_explicit_trajectory": (i32, [vp, P, f64, i64, vp, vp]),
+        "pf_vjp_explicit_trajectory": (i32, [vp, P, f64, i64, vp, vp, vp, i32, vp, vp]),
     }
     for name, (res, args) in sig.items():
         fn = getattr(L, name)

@@ -131,6 +131,18 @@ long long ndof(const pf_problem* p)
 
 size_t elem_size(const pf_problem* p) { return p->dtype == PF_F64 ? 8 : 4; }
 
+int explicit_trajectory_ok(const pf_problem* p, double dt, int64_t nsteps)
+{
+    if (p->model != PF_ALLEN_CAHN && p->model != PF_CAHN_HILLIARD)
+        return fail(PF_EUNSUPPORTED, "explicit trajectories: Allen-Cahn and Cahn-Hilliard only");
+    if (p->mass != PF_MASS_LUMPED) return fail(PF_EUNSUPPORTED, "explicit steps need the lumped mass");
+    if (!(dt > 0.0) || !std::isfinite(dt)) return fail(PF_EINVAL, "dt must be finite and > 0");
+    if (nsteps < 0) return fail(PF_EINVAL, "nsteps must be >= 0");
+    if ((size_t)geom_of(p).N * elem_size(p) >= (size_t(1) << 31))
+        return fail(PF_EUNSUPPORTED, "explicit trajectories: fields below 2 GiB");
+    return PF_OK;
+}
+
 // the grain-growth Jacobian product stages two sets of fields in LDS (<= 64 KB)
 int grain_implicit_ok(const pf_problem* p)
 {
@@ -229,11 +241,14 @@ int step_explicit_t(const pf_problem* p, int cus, double dt, int64_t nsteps, T* 
             std::swap(cur, other);
         }
     } else {
+        // an odd count's first step runs in place (the update reads c at its own node only),
+        // so that the last one ends in the caller's array
         T* mu = U + g.N;
         for (int64_t st = 0; st < nsteps; ++st) {
+            T* out = st == 0 && nsteps % 2 ? cur : other;
             pfk::launch_chem<T>(g, f, p->kappa, cur, mu, s);
-            pfk::launch_ch_update<T>(g, dt * p->mobility, cur, mu, other, s);
-            std::swap(cur, other);
+            pfk::launch_ch_update<T>(g, dt * p->mobility, cur, mu, out, s);
+            if (out != cur) std::swap(cur, other);
         }
     }
     if (int rc = check_launch("explicit step")) return rc;
@@ -243,6 +258,31 @@ int step_explicit_t(const pf_problem* p, int cus, double dt, int64_t nsteps, T* 
     }
     if (p->model == PF_CAHN_HILLIARD) pfk::launch_chem<T>(g, f, p->kappa, c, U + g.N, s);
     return check_launch("explicit step");
+}
+
+// nsteps single steps along states[0..nsteps], every state kept (see
+// pf_step_explicit_trajectory)
+template <typename T>
+int step_trajectory_t(const pf_problem* p, int cus, double dt, int64_t nsteps, T* states, hipStream_t s)
+{
+    const pfk::Geom g = geom_of(p);
+    const pfk::FreeEnergy f = pfk::make_free_energy(p->fe, p->W);
+    const long long nd = ndof(p);
+    const bool ch = p->model == PF_CAHN_HILLIARD;
+    const pfk::Stream2DConfig one{stream2d_rows(p, 1, cus), stream2d_depth(p), 1};
+    for (int64_t k = 0; k < nsteps; ++k) {
+        T* in = states + k * nd;
+        T* out = in + nd;
+        if (ch) pfk::launch_chem<T>(g, f, p->kappa, in, in + g.N, s);
+        if (p->dim == 2)
+            pfk::launch_explicit2d<T>(g, p->model, f, p->kappa, p->mobility, dt, in, out, one, s);
+        else if (ch)
+            pfk::launch_ch_update<T>(g, dt * p->mobility, in, in + g.N, out, s);
+        else
+            pfk::launch_ac_step<T>(g, f, p->kappa, dt * p->mobility, in, out, s);
+    }
+    if (ch) pfk::launch_chem<T>(g, f, p->kappa, states + nsteps * nd, states + nsteps * nd + g.N, s);
+    return check_launch("explicit trajectory");
 }
 
 // energy and sum m c of U, partial sums in `part` (energy_blocks(g) pairs)
@@ -483,6 +523,21 @@ int pf_step_explicit(pf_ctx* ctx, const pf_problem* p, double dt, int64_t nsteps
         hipStream_t s = (hipStream_t)stream;
         if (p->dtype == PF_F32) return step_explicit_t<float>(p, ctx->cus, dt, nsteps, (float*)U, (float*)ws, s);
         return step_explicit_t<double>(p, ctx->cus, dt, nsteps, (double*)U, (double*)ws, s);
+    });
+}
+
+int pf_step_explicit_trajectory(pf_ctx* ctx, const pf_problem* p, double dt, int64_t nsteps, void* states,
+                                void* stream)
+{
+    return guarded("pf_step_explicit_trajectory", [&]() -> int {
+        if (int rc = check_ctx(ctx)) return rc;
+        if (int rc = validate(p)) return rc;
+        if (int rc = explicit_trajectory_ok(p, dt, nsteps)) return rc;
+        if (int rc = check_ptr(states, p, "states")) return rc;
+        if (int rc = require_device(ctx)) return rc;
+        hipStream_t s = (hipStream_t)stream;
+        if (p->dtype == PF_F32) return step_trajectory_t<float>(p, ctx->cus, dt, nsteps, (float*)states, s);
+        return step_trajectory_t<double>(p, ctx->cus, dt, nsteps, (double*)states, s);
     });
 }
 

@@ -20,6 +20,8 @@ pfk::Geom geom_of(const pf_problem* p);
 long long ndof(const pf_problem* p);
 size_t elem_size(const pf_problem* p);
 int grain_implicit_ok(const pf_problem* p);
+// the explicit trajectory calls: model, mass, dt, step count, field size
+int explicit_trajectory_ok(const pf_problem* p, double dt, int64_t nsteps);
 
 // Runs an entry point's body; a C++ exception (a host allocation that failed, an
 // internal error) becomes PF_EDEVICE with a message instead of crossing the ABI.

@@ -240,13 +240,120 @@ void launch_mass_axpy(const Geom& g, double inv_dt, const T* lam, T* ub, hipStre
     DIM_SWITCH(g, { k_mass_axpy<T, D><<<nblk(g), AB, 0, s>>>(lam, ub, g, (T)(inv_dt * m), (T)inv_dt); });
 }
 
+// The marched adjoint of one explicit step.  With K symmetric and the quadrature of an
+// interpolated field linear, the parameter derivatives need no further stencil:
+//   Allen-Cahn    sum lam (K eta) = sum eta (K lam), sum lam N_1(eta) = sum_q |J| f1'(eta_q) lam_q
+//   Cahn-Hilliard the same with t = dt M K lam / m^2 for lam, and sum lam (K mu) = sum mu (K lam)
+// all over what the passes hold anyway.  part: the first third for the waves of the
+// Cahn-Hilliard pass over lam, the rest for the pass with the quadrature.
+// 72 x 65 x 60 Cahn-Hilliard: 5 launches of 42 us (node-centric, every Gauss point 8 times
+// for each of two polynomials) -> 2 of 14 us.
+template <typename T>
+bool launch_adjoint_step(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double dt,
+                         const T* U, const T* mu, const T* lam, T* lam_out, const T* add, T* t, double* part,
+                         long long part_max, int fresh, hipStream_t s)
+{
+    const double m = std::pow(g.h, g.dim);
+    const long long na = part_max / 3;
+    March<T> a, b;
+    b.u = U;
+    b.v = lam;
+    b.base = lam;
+    b.out = lam_out;
+    b.p1 = add;
+    b.nq = dt * mob / m;
+    b.kv = dt * mob * kappa / m;
+    b.part_max = part_max - na;
+    b.fresh = fresh;
+    b.scale = 1;
+    b.rows = 1;
+    if (!launch_march<T>(g, MOP_JVP, ME_ADJ, f, b, s)) return false;  // would it fit
+    if (model != 0) {
+        a.v = lam;
+        a.out = t;
+        a.p0 = mu;
+        a.kv = mob * dt / m / m;
+        a.part = part;
+        a.part_max = na;
+        a.fresh = fresh;
+        a.scale = 1;
+        a.rows = 1;
+        if (!launch_march<T>(g, MOP_STIFF, ME_ADJK, f, a, s)) return false;
+        b.v = t;
+        b.nq = 1.0;
+        b.kv = kappa;
+        b.scale = 0;
+    }
+    b.part = part + na;
+    return launch_march<T>(g, MOP_JVP, ME_ADJ, f, b, s);
+}
+
+namespace {
+// sums in a fixed order, then theta_bar += (c[0] SK + c[1] A + c[2] B, c[3] B, c[4] A)
+struct ThetaCoef { double c[5]; };
+constexpr int TB = 1024;
+__global__ __launch_bounds__(TB) void k_adjoint_theta(const double* __restrict__ pk, int nk,
+                                                      const double* __restrict__ pq, int nq, ThetaCoef k,
+                                                      double* __restrict__ theta)
+{
+    __shared__ double sh[3][TB];
+    double v[3] = {0.0, 0.0, 0.0};
+    for (int i = threadIdx.x; i < nk; i += TB) v[0] += pk[i];
+    for (int i = threadIdx.x; i < nq; i += TB) {
+        v[1] += pq[2 * i];
+        v[2] += pq[2 * i + 1];
+    }
+    for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] = v[q];
+    __syncthreads();
+    for (int st = TB / 2; st > 0; st >>= 1) {
+        if ((int)threadIdx.x < st)
+            for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + st];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        theta[0] += k.c[0] * sh[0][0] + (k.c[1] * sh[1][0] + k.c[2] * sh[2][0]);
+        theta[1] += k.c[3] * sh[2][0];
+        theta[2] += k.c[4] * sh[1][0];
+    }
+}
+}  // namespace
+
+template <typename T>
+void launch_adjoint_theta(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double dt,
+                          const double* part, long long part_max, double* theta_bar, hipStream_t s)
+{
+    const double m = std::pow(g.h, g.dim), J = std::pow(0.5 * g.h, g.dim);
+    const double ks = g.dim == 3 ? g.h / 12.0 : 1.0 / 3.0;  // the marching stencils' scale
+    const long long na = part_max / 3;
+    int nk = 0, nq = 0;
+    March<T> q;
+    q.part_max = part_max;
+    launch_march<T>(g, MOP_JVP, ME_ADJ, f, q, s, &nq);
+    ThetaCoef k{};
+    if (model == 0) {
+        const double w = -dt / m;
+        k = ThetaCoef{{0.0, w * f.W * J, w * kappa * ks, w * mob * ks, w * mob * J}};
+    } else {
+        launch_march<T>(g, MOP_STIFF, ME_ADJK, f, q, s, &nk);
+        k = ThetaCoef{{-dt / m * ks, 0.0, 0.0, -ks, -J}};
+    }
+    k_adjoint_theta<<<1, TB, 0, s>>>(part, nk, part + na, nq, k, theta_bar);
+}
+
 template <typename T>
 void launch_vjp_explicit(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,
                          double dt, const T* U, const T* vbar, T* ubar, T* scratch, double* part,
-                         double* theta_bar, hipStream_t s)
+                         long long part_max, double* theta_bar, hipStream_t s)
 {
     const double detJ = std::pow(0.5 * g.h, g.dim), m = std::pow(g.h, g.dim);
     const unsigned nb = nblk(g);
+    if (model != 0) launch_chem<T>(g, f, kappa, U, scratch, s);
+    if (launch_adjoint_step<T>(g, model, f, kappa, mob, dt, U, scratch, vbar, ubar, ubar, scratch + g.N, part,
+                               part_max, 1, s)) {
+        launch_adjoint_theta<T>(g, model, f, kappa, mob, dt, part, part_max, theta_bar, s);
+        return;
+    }
+    // fields of 2 GiB and more: node-centric
     const Lin<T> F2{(T)f.b0, (T)f.b1, (T)f.b2};
     if (model == 0) {
         DIM_SWITCH(g, {
@@ -258,7 +365,6 @@ void launch_vjp_explicit(const Geom& g, int model, const FreeEnergy& f, double k
     }
     T* mu = scratch;
     T* t = scratch + g.N;
-    launch_chem<T>(g, f, kappa, U, mu, s);
     DIM_SWITCH(g, {
         k_vjp_ch_a<T, D><<<nb, AB, 0, s>>>(mu, vbar, t, g, (T)(dt / m), (T)mob, (T)(1.0 / m), part);
     });
@@ -276,8 +382,13 @@ void launch_vjp_explicit(const Geom& g, int model, const FreeEnergy& f, double k
                                    const T*, double, double*, double*, hipStream_t);            \
     template void launch_mass_axpy<T>(const Geom&, double, const T*, T*, hipStream_t);           \
     template void launch_vjp_explicit<T>(const Geom&, int, const FreeEnergy&, double, double,    \
-                                         double, const T*, const T*, T*, T*, double*, double*,   \
-                                         hipStream_t);
+                                         double, const T*, const T*, T*, T*, double*, long long, \
+                                         double*, hipStream_t);                                  \
+    template bool launch_adjoint_step<T>(const Geom&, int, const FreeEnergy&, double, double, double, const T*, \
+                                         const T*, const T*, T*, const T*, T*, double*, long long, int, \
+                                         hipStream_t);                                           \
+    template void launch_adjoint_theta<T>(const Geom&, int, const FreeEnergy&, double, double, double, \
+                                          const double*, long long, double*, hipStream_t);
 INST_ADJ(float)
 INST_ADJ(double)
 

@@ -23,6 +23,7 @@ struct MC2 {
     T kv;       // times (9 v - box v), nodal: (4 v - nbrs)
     T kw;       // SCHUR: the outer stencil
     T s0, s1, s2;
+    T g1, g2, g3;  // ME_ADJ: f' at W = 1
 };
 
 // 9 v - box3x3 v of row r - 1 (nodal: 4 v - axis neighbours) as rows are pushed, from
@@ -51,15 +52,22 @@ struct Lap2 {
 };
 
 // quadrature sum of node row r - 1 as rows of u (and v) are pushed
-template <typename T, bool WITHV, bool NODAL>
+// (SUM: asum receives sum_q f1'(u_q) v_q of the element row (r-1, r) above it)
+template <typename T, bool WITHV, bool NODAL, bool SUM = false>
 struct Quad2 {
     T xlu = 0, xru = 0, xlv = 0, xrv = 0;  // x-interpolants of row r-1 (nodal: u, v of row r-1 in xlu, xlv)
     T guL = 0, guR = 0;                    // upward scatter of element row (r-2, r-1)
 
+    T asum = 0;
+
     __device__ __forceinline__ T push(T u, T v, const MC2<T>& k)
     {
         const T gp = (T)GP, gm = (T)GM;
-        auto F = [&](T q, T p) { return fmaT(fmaT(k.c, q, k.b), q, k.a) * (WITHV ? p : q); };
+        if constexpr (SUM) asum = 0;
+        auto F = [&](T q, T p) {
+            if constexpr (SUM) asum = fmaT(cubic(q, k.g1, k.g2, k.g3), p, asum);
+            return fmaT(fmaT(k.c, q, k.b), q, k.a) * (WITHV ? p : q);
+        };
         if constexpr (NODAL) {
             const T r = F(xlu, xlv);
             xlu = u;
@@ -104,8 +112,9 @@ __global__ __launch_bounds__(256) void k_march2d(March<T> p, int nx, int ny, int
     constexpr int H = OP == MOP_SCHUR ? 2 : 1;
     constexpr int OUTW = WAVE - 2 * H;
     constexpr bool HASU = OP != MOP_STIFF, HASV = OP != MOP_GRAD || EPI == ME_CHRES;
-    constexpr bool USE0 = EPI == ME_MU || EPI == ME_BACK || EPI == ME_CHEB;
-    constexpr bool USE1 = EPI == ME_CHEB || EPI == ME_OUT || EPI == ME_CHRES, USE2 = EPI == ME_CHEB;
+    constexpr bool ADJ = EPI == ME_ADJ || EPI == ME_ADJK;
+    constexpr bool USE0 = EPI == ME_MU || EPI == ME_BACK || EPI == ME_CHEB || EPI == ME_ADJK;
+    constexpr bool USE1 = EPI == ME_CHEB || EPI == ME_OUT || EPI == ME_CHRES || EPI == ME_ADJ, USE2 = EPI == ME_CHEB;
     const int wid = uniform_wave();
     if (wid >= nwaves) return;  // uniform per wave
     const int strip = wid % nstrips, chunk = wid / nstrips;
@@ -135,15 +144,18 @@ __global__ __launch_bounds__(256) void k_march2d(March<T> p, int nx, int ny, int
     const auto r2 = make_rsrc(p.p2 ? p.p2 : p.out, bytes);
     // rows read lie in [-H, ny + H - 1] and are wrapped or reflected once (the launcher
     // keeps ny >= 2 H)
-    auto row_off = [&](int t) {
+    auto row_of = [&](int t) {
         int r = min(y0 - H + t, y1 + H - 1);  // past the chunk the last row is read again (a cache hit)
         if constexpr (MIRROR) {
             r = r < 0 ? -r : (r >= ny ? 2 * (ny - 1) - r : r);
         } else {
             r = r < 0 ? r + ny : (r >= ny ? r - ny : r);
         }
-        return r * rowb;
+        return r;
     };
+    auto row_off = [&](int t) { return row_of(t) * rowb; };
+    const T vf = ADJ && MIRROR && p.scale && edge_count(x, nx) ? (T)2 : (T)1;  // 2^b of the lane's column
+    double sA = 0.0, sB = 0.0;
     // output row of iteration t: y0 - 2 H + t
     auto out_off = [&](int t) { return min(max(y0 - 2 * H + t, y0), y1 - 1) * rowb; };
     T fu[MPF], fv[MPF], fb[MPF], f0[MPF], f1[MPF], f2[MPF];
@@ -160,15 +172,23 @@ __global__ __launch_bounds__(256) void k_march2d(March<T> p, int nx, int ny, int
 #pragma unroll
     for (int i = 0; i < MPF; ++i) fetch(i, i);
     constexpr bool VARG = OP != MOP_GRAD;  // the operator's argument is v
-    Quad2<T, VARG, NODAL> qd;
+    Quad2<T, VARG, NODAL, EPI == ME_ADJ> qd;
     Lap2<T, NODAL> lp, lw;
     T c1 = 0, c2 = 0;  // the operator's argument at rows r-1, r-2
+    T u1 = 0;
     // whole groups of MPF rows: the pushes past the chunk compute rows nobody stores
     for (int t0 = 0; t0 < iters; t0 += MPF) {
 #pragma unroll
         for (int i = 0; i < MPF; ++i) {
             const int t = t0 + i;
-            const T u = fu[i], v = fv[i], eb = fb[i], e0 = f0[i], e1 = f1[i], e2 = f2[i];
+            const T u = fu[i], eb = fb[i], e0 = f0[i], e1 = f1[i], e2 = f2[i];
+            T v = fv[i];
+            if constexpr (ADJ && MIRROR) {
+                const int r = row_of(t);
+                if (p.scale) v *= (r == 0 || r == ny - 1) ? vf * (T)2 : vf;
+            }
+            const T ucen = u1;  // u at the output row (H = 1)
+            u1 = u;
             fetch(t + MPF, i);
             T s = 0;
             if constexpr (HASU) s = qd.push(u, v, k);
@@ -189,6 +209,14 @@ __global__ __launch_bounds__(256) void k_march2d(March<T> p, int nx, int ny, int
                 T r;
                 if constexpr (EPI == ME_OUT) r = (k.s0 != (T)0 ? fmaT(k.s0, c - e1, o) : o) * ib;
                 else if constexpr (EPI == ME_SUB) r = c - o * ib;
+                else if constexpr (EPI == ME_ADJ) {
+                    r = (c - o * ib) + e1;
+                    if (!MIRROR || (x < nx - 1 && yo < ny - 1)) sA += (double)qd.asum;
+                    sB += (double)ucen * (double)(lap * ib);
+                } else if constexpr (EPI == ME_ADJK) {
+                    r = o;
+                    sB += (double)e0 * (double)(lap * ib);
+                }
                 else if constexpr (EPI == ME_MU) r = fmaT(k.s0, e0, -o) * ib;
                 else if constexpr (EPI == ME_CHRES) {
                     bstore(fmaT(k.s0, v1, -o) * ib, ro2, vx, yo * rowb);
@@ -196,6 +224,20 @@ __global__ __launch_bounds__(256) void k_march2d(March<T> p, int nx, int ny, int
                 } else if constexpr (EPI == ME_BACK) r = fmaT(k.s0 / ib, e0, o);
                 else r = fmaT(k.s1, c - e2, c) + k.s2 * e1 * (e0 - fmaT(k.s0, c, o) * ib);
                 bstore(r, ro, vx, yo * rowb);
+            }
+        }
+    }
+    if constexpr (ADJ) {
+        for (int off = WAVE / 2; off > 0; off >>= 1) {
+            sA += __shfl_down(sA, off, WAVE);
+            sB += __shfl_down(sB, off, WAVE);
+        }
+        if (lane == 0) {
+            if constexpr (EPI == ME_ADJ) {
+                p.part[2 * wid] = p.fresh ? sA : p.part[2 * wid] + sA;
+                p.part[2 * wid + 1] = p.fresh ? sB : p.part[2 * wid + 1] + sB;
+            } else {
+                p.part[wid] = p.fresh ? sB : p.part[wid] + sB;
             }
         }
     }
@@ -218,7 +260,8 @@ int march2_cus()
 }  // namespace
 
 template <typename T>
-bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s)
+bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s,
+                    int* waves_out)
 {
     // 32-bit buffer offsets; the Gauss-integrated mass has no streaming form
     if (g.dim != 2 || g.cm || (size_t)g.N * sizeof(T) >= (size_t(1) << 31)) return false;
@@ -233,6 +276,11 @@ bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
     const int ty = tov > 0 ? std::min(tov, ny) : (int)((ny + nch - 1) / nch);
     const long long nwaves = (long long)nstrips * ((ny + ty - 1) / ty);
     if (nwaves > (1ll << 30)) return false;
+    if (epi == ME_ADJ || epi == ME_ADJK) {
+        if (g.quad || (epi == ME_ADJ ? 2 : 1) * nwaves > m.part_max) return false;
+        if (waves_out) *waves_out = (int)nwaves;
+        if (!m.part) return true;
+    }
     const double mm = g.h * g.h, w = m.nq * (g.quad ? mm : 0.25 * mm), ks = g.quad ? 1.0 : 1.0 / 3.0;
     MC2<T> k{};
     if (op == MOP_GRAD) {
@@ -245,6 +293,10 @@ bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
     k.s0 = (T)m.s0;
     k.s1 = (T)m.s1;
     k.s2 = (T)m.s2;
+    const FreeEnergy f1 = make_free_energy(f.fe, 1.0);
+    k.g1 = (T)f1.a1;
+    k.g2 = (T)f1.a2;
+    k.g3 = (T)f1.a3;
     const unsigned blocks = (unsigned)((nwaves + 3) / 4), bytes = (unsigned)((size_t)g.N * sizeof(T));
 #define M2Q(OP, EPI, MIR)                                                                                        \
     do {                                                                                                         \
@@ -257,6 +309,14 @@ bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
     do {                                                                                                         \
         if (g.bc) M2Q(OP, EPI, true); else M2Q(OP, EPI, false);                                                  \
     } while (0)
+    // (the adjoint of a step: Gauss quadrature only)
+#define M2A(OP, EPI)                                                                                             \
+    do {                                                                                                         \
+        if (g.bc)                                                                                                \
+            k_march2d<T, OP, EPI, true, false><<<blocks, 256, 0, s>>>(m, nx, ny, nstrips, (int)nwaves, ty, bytes, k);  \
+        else                                                                                                     \
+            k_march2d<T, OP, EPI, false, false><<<blocks, 256, 0, s>>>(m, nx, ny, nstrips, (int)nwaves, ty, bytes, k); \
+    } while (0)
     switch (op * 8 + epi) {
         case MOP_GRAD * 8 + ME_OUT: M2(MOP_GRAD, ME_OUT); return true;
         case MOP_GRAD * 8 + ME_CHRES: M2(MOP_GRAD, ME_CHRES); return true;
@@ -264,6 +324,8 @@ bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
         case MOP_JVP * 8 + ME_SUB: M2(MOP_JVP, ME_SUB); return true;
         case MOP_JVP * 8 + ME_BACK: M2(MOP_JVP, ME_BACK); return true;
         case MOP_JVP * 8 + ME_CHEB: M2(MOP_JVP, ME_CHEB); return true;
+        case MOP_JVP * 8 + ME_ADJ: M2A(MOP_JVP, ME_ADJ); return true;
+        case MOP_STIFF * 8 + ME_ADJK: M2A(MOP_STIFF, ME_ADJK); return true;
         case MOP_STIFF * 8 + ME_OUT: M2(MOP_STIFF, ME_OUT); return true;
         case MOP_STIFF * 8 + ME_SUB: M2(MOP_STIFF, ME_SUB); return true;
         case MOP_STIFF * 8 + ME_BACK: M2(MOP_STIFF, ME_BACK); return true;
@@ -272,11 +334,12 @@ bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
         case MOP_SCHUR * 8 + ME_CHEB: M2(MOP_SCHUR, ME_CHEB); return true;
         default: return false;
     }
+#undef M2A
 #undef M2
 #undef M2Q
 }
 
-template bool launch_march2d<float>(const Geom&, int, int, const FreeEnergy&, const March<float>&, hipStream_t);
-template bool launch_march2d<double>(const Geom&, int, int, const FreeEnergy&, const March<double>&, hipStream_t);
+template bool launch_march2d<float>(const Geom&, int, int, const FreeEnergy&, const March<float>&, hipStream_t, int*);
+template bool launch_march2d<double>(const Geom&, int, int, const FreeEnergy&, const March<double>&, hipStream_t, int*);
 
 }  // namespace pfk

@@ -36,6 +36,7 @@ struct MC3 {           // coefficients in the field type
     T a, b, c;         // GRAD: q (a + q (b + c q)); JVP: (a + q (b + c q)) v  (|J| folded in)
     T kv;              // times Lap3 (h / 12 folded in), nodal: times LapN3 (h folded in)
     T s0, s1, s2;
+    T g1, g2, g3;      // ME_ADJ: f' at W = 1
 };
 
 struct ML3 {           // launch geometry
@@ -127,8 +128,10 @@ __device__ __forceinline__ void interp_plane(const T (&a)[R + 2], T (&q)[R + 1][
 
 // The quadrature pipeline: push the newest plane z of u (and v) and get the sums of
 // plane z - 1.
-template <typename T, int R, int OP>
+// (SUM: asum[j] receives sum_q f1'(u_q) v_q of the element above node row j, planes z-1..z)
+template <typename T, int R, int OP, bool SUM = false>
 struct Quad3 {
+    T asum[SUM ? R : 1];
     T qu[R + 1][4], up[R + 1][4], qv[OP == MOP_JVP ? R + 1 : 1][4];
 
     __device__ __forceinline__ void init()
@@ -141,6 +144,11 @@ struct Quad3 {
                 if constexpr (OP == MOP_JVP) qv[e][i] = (T)0;
             }
     }
+    __device__ __forceinline__ void prime(const T (&u)[R + 2], const T (&v)[R + 2])
+    {
+        interp_plane<T, R>(u, qu);
+        if constexpr (OP == MOP_JVP) interp_plane<T, R>(v, qv);
+    }
     __device__ __forceinline__ void push(const T (&u)[R + 2], const T (&v)[R + 2], const MC3<T>& k, T (&s)[R])
     {
         const T gp = (T)GP, gm = (T)GM;
@@ -150,7 +158,7 @@ struct Quad3 {
         T dn[R + 1][2], hi[R + 1][2];  // y-scatter of plane z - 1: to the lower / upper node row (left, right)
 #pragma unroll
         for (int e = 0; e < R + 1; ++e) {
-            T h[4];
+            T h[4], as = (T)0;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const T du = nu[e][i] - qu[e][i];
@@ -161,8 +169,11 @@ struct Quad3 {
                     f1 *= u1;
                 } else {
                     const T dv = nv[e][i] - qv[e][i];
-                    f0 *= fmaT(gm, dv, qv[e][i]);
-                    f1 *= fmaT(gp, dv, qv[e][i]);
+                    const T v0 = fmaT(gm, dv, qv[e][i]), v1 = fmaT(gp, dv, qv[e][i]);
+                    f0 *= v0;
+                    f1 *= v1;
+                    if constexpr (SUM)
+                        as = fmaT(cubic(u1, k.g1, k.g2, k.g3), v1, fmaT(cubic(u0, k.g1, k.g2, k.g3), v0, as));
                     qv[e][i] = nv[e][i];
                 }
                 qu[e][i] = nu[e][i];
@@ -170,6 +181,8 @@ struct Quad3 {
                 h[i] = up[e][i] + fmaT(gp, d, f1);  // plane z - 1 complete
                 up[e][i] = fmaT(gm, d, f1);         // plane z, lower slab
             }
+            if constexpr (SUM)
+                if (e >= 1) asum[e - 1] = as;  // lower corner at node row e - 1 of the block
             const T dl = h[0] - h[1], dr = h[2] - h[3];
             dn[e][0] = fmaT(gp, dl, h[1]);
             hi[e][0] = fmaT(gm, dl, h[1]);
@@ -233,6 +246,14 @@ __global__ __launch_bounds__(256) void k_march3d(March<T> p, ML3 L, MC3<T> k)
         return z * planeb;
     };
     constexpr bool HASU = OP != MOP_STIFF, HASV = OP != MOP_GRAD;
+    constexpr bool ADJ = EPI == ME_ADJ || EPI == ME_ADJK;
+    T vf[ADJ && MIRROR ? R + 2 : 1];  // 2^b of the lane's column and rows
+    if constexpr (ADJ && MIRROR) {
+#pragma unroll
+        for (int j = 0; j < R + 2; ++j)
+            vf[j] = p.scale ? (T)(1 << (edge_count(x, L.nx) + edge_count(reflect(y0 - 1 + j, L.ny), L.ny))) : (T)1;
+    }
+    double sA = 0.0, sB = 0.0;
     const auto ru = make_rsrc(HASU ? p.u : p.v, L.bytes);
     const auto rv = make_rsrc(HASV ? p.v : p.u, L.bytes);
     const auto ro = make_rsrc(p.out, L.bytes);
@@ -241,7 +262,7 @@ __global__ __launch_bounds__(256) void k_march3d(March<T> p, ML3 L, MC3<T> k)
     const auto r1 = make_rsrc(p.p1 ? p.p1 : p.out, L.bytes);
     const auto r2 = make_rsrc(p.p2 ? p.p2 : p.out, L.bytes);
 
-    Quad3<T, R, NODAL ? MOP_STIFF : OP> qd;
+    Quad3<T, R, NODAL ? MOP_STIFF : OP, EPI == ME_ADJ> qd;
     using LapT = std::conditional_t<NODAL, LapN3<T, R>, Lap3<T, R>>;
     LapT lp;
     if constexpr (HASU && !NODAL) qd.init();
@@ -267,6 +288,12 @@ __global__ __launch_bounds__(256) void k_march3d(March<T> p, ML3 L, MC3<T> k)
             u[j] = HASU ? nu[j] : (T)0;
             v[j] = HASV ? nv[j] : (T)0;
         }
+        if constexpr (ADJ && MIRROR) {
+            const int zr = z < 0 ? -z : (z >= L.nz ? 2 * (L.nz - 1) - z : z);
+            const T zf = p.scale && edge_count(zr, L.nz) ? (T)2 : (T)1;
+#pragma unroll
+            for (int j = 0; j < R + 2; ++j) v[j] *= vf[j] * zf;
+        }
         fetch(min(z + 1, z1));  // past the chunk the last plane is read again (a cache hit)
         // what the epilogue reads of plane z - 1, in flight during the compute
         const bool emit = z > z0;
@@ -275,12 +302,16 @@ __global__ __launch_bounds__(256) void k_march3d(March<T> p, ML3 L, MC3<T> k)
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             eb[j] = p.base ? bload<T>(rb, vo[j + 1], so) : (T)0;
-            e0[j] = (EPI == ME_MU || EPI == ME_BACK || EPI == ME_CHEB) ? bload<T>(r0, vo[j + 1], so) : (T)0;
-            e1[j] = (EPI == ME_CHEB || (EPI == ME_OUT && p.p1)) ? bload<T>(r1, vo[j + 1], so) : (T)0;
+            e0[j] = (EPI == ME_MU || EPI == ME_BACK || EPI == ME_CHEB || EPI == ME_ADJK) ? bload<T>(r0, vo[j + 1], so) : (T)0;
+            e1[j] = (EPI == ME_CHEB || ((EPI == ME_OUT || EPI == ME_ADJ) && p.p1)) ? bload<T>(r1, vo[j + 1], so) : (T)0;
             e2[j] = EPI == ME_CHEB && p.p2 ? bload<T>(r2, vo[j + 1], so) : (T)0;
         }
         T s[R], lap[R];
-        if constexpr (NODAL) {
+        if (HASU && !NODAL && R <= 2 && z < z0) {
+            // the plane below the chunk: its interpolants only (at 4 rows the branch costs 30
+            // VGPRs and more than it saves)
+            qd.prime(u, v);
+        } else if constexpr (NODAL) {
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 if constexpr (OP == MOP_GRAD) s[j] = cubic(uc[j], k.a, k.b, k.c);
@@ -304,6 +335,14 @@ __global__ __launch_bounds__(256) void k_march3d(March<T> p, ML3 L, MC3<T> k)
                 T r;
                 if constexpr (EPI == ME_OUT) r = (k.s0 != (T)0 ? fmaT(k.s0, c - e1[j], o) : o) * ib;
                 else if constexpr (EPI == ME_SUB) r = c - o * ib;
+                else if constexpr (EPI == ME_ADJ) {
+                    r = (c - o * ib) + e1[j];
+                    if (!MIRROR || (x < L.nx - 1 && y0 + j < L.ny - 1 && z - 1 < L.nz - 1)) sA += (double)qd.asum[j];
+                    sB += (double)uc[j] * (double)(lap[j] * ib);
+                } else if constexpr (EPI == ME_ADJK) {
+                    r = o;
+                    sB += (double)e0[j] * (double)(lap[j] * ib);
+                }
                 else if constexpr (EPI == ME_MU) r = fmaT(k.s0, e0[j], -o) * ib;
                 else if constexpr (EPI == ME_BACK) r = fmaT(k.s0 / ib, e0[j], o);
                 else r = fmaT(k.s1, c - e2[j], c) + k.s2 * e1[j] * (e0[j] - fmaT(k.s0, c, o) * ib);
@@ -316,7 +355,26 @@ __global__ __launch_bounds__(256) void k_march3d(March<T> p, ML3 L, MC3<T> k)
             vc[j] = v[j + 1];
         }
     }
+    if constexpr (ADJ) {
+        for (int off = WAVE / 2; off > 0; off >>= 1) {
+            sA += __shfl_down(sA, off, WAVE);
+            sB += __shfl_down(sB, off, WAVE);
+        }
+        if (lane == 0) {
+            if constexpr (EPI == ME_ADJ) {
+                p.part[2 * wave] = p.fresh ? sA : p.part[2 * wave] + sA;
+                p.part[2 * wave + 1] = p.fresh ? sB : p.part[2 * wave + 1] + sB;
+            } else {
+                p.part[wave] = p.fresh ? sB : p.part[wave] + sB;
+            }
+        }
+    }
 }
+
+// rows per lane of ME_ADJ, whose pipeline holds two fields and two polynomials (4 rows: 236
+// VGPRs in FP32, spills in FP64)
+template <typename T>
+constexpr int ADJ_ROWS = sizeof(T) == 4 ? 2 : 1;
 
 int march_cus()
 {
@@ -368,7 +426,7 @@ static void march3d_shape(int nx, int ny, int nz, int R, int cus, int* G, int* p
 }
 
 template <typename T, int R>
-bool launch_r(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s)
+bool launch_r(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s, int* waves_out)
 {
     ML3 L{};
     L.nx = g.n[0];
@@ -380,6 +438,11 @@ bool launch_r(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T
     const long long items = (long long)L.nstrips * ((L.ny + R - 1) / R);
     const long long wpc = (items + L.G - 1) / L.G, waves = wpc * ((L.nz + L.pz - 1) / L.pz);
     if (waves > (1ll << 30)) return false;
+    if (epi == ME_ADJ || epi == ME_ADJK) {
+        if (g.quad || (epi == ME_ADJ ? 2 : 1) * waves > m.part_max) return false;
+        if (waves_out) *waves_out = (int)waves;
+        if (!m.part) return true;
+    }
     L.items = (int)items;
     L.wpc = (int)wpc;
     L.nwaves = (int)waves;
@@ -396,6 +459,10 @@ bool launch_r(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T
     k.s0 = (T)m.s0;
     k.s1 = (T)m.s1;
     k.s2 = (T)m.s2;
+    const FreeEnergy f1 = make_free_energy(f.fe, 1.0);
+    k.g1 = (T)f1.a1;
+    k.g2 = (T)f1.a2;
+    k.g3 = (T)f1.a3;
     const unsigned blocks = (unsigned)((waves + 3) / 4);
 #define M3Q(OP, EPI, MIR)                                                                  \
     do {                                                                                   \
@@ -406,7 +473,20 @@ bool launch_r(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T
     do {                                                                                   \
         if (g.bc) M3Q(OP, EPI, true); else M3Q(OP, EPI, false);                            \
     } while (0)
-    switch (op * 8 + epi) {
+#define M3A(OP, EPI)                                                                       \
+    do {                                                                                   \
+        if (g.bc) k_march3d<T, R, OP, EPI, true, false><<<blocks, 256, 0, s>>>(m, L, k);   \
+        else k_march3d<T, R, OP, EPI, false, false><<<blocks, 256, 0, s>>>(m, L, k);       \
+    } while (0)
+    if constexpr (R == ADJ_ROWS<T>) {
+        if (op == MOP_JVP && epi == ME_ADJ) {
+            M3A(MOP_JVP, ME_ADJ);
+            return true;
+        }
+    }
+    if constexpr (R == 1) return false;
+    else switch (op * 8 + epi) {
+        case MOP_STIFF * 8 + ME_ADJK: M3A(MOP_STIFF, ME_ADJK); return true;
         case MOP_GRAD * 8 + ME_OUT: M3(MOP_GRAD, ME_OUT); return true;
         case MOP_GRAD * 8 + ME_SUB: M3(MOP_GRAD, ME_SUB); return true;
         case MOP_GRAD * 8 + ME_MU: M3(MOP_GRAD, ME_MU); return true;
@@ -420,12 +500,14 @@ bool launch_r(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T
         case MOP_STIFF * 8 + ME_CHEB: M3(MOP_STIFF, ME_CHEB); return true;
         default: return false;
     }
+#undef M3A
 #undef M3
 #undef M3Q
 }
 
 template <typename T>
-bool launch_march3d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s)
+bool launch_march3d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s,
+                    int* waves_out)
 {
     // 32-bit buffer offsets, and the Gauss-integrated mass has no marching form
     if (g.dim != 3 || g.cm || (size_t)g.N * sizeof(T) >= (size_t(1) << 31)) return false;
@@ -433,10 +515,13 @@ bool launch_march3d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
     // the grid fills the chip; below about a million nodes more waves matter (explicit
     // Cahn-Hilliard step, FP32, 2 against 4 rows: 72 x 65 x 60 13.3 / 13.9 us, 130 x 121 x
     // 117 23.7 / 23.3 us, 256 x 200 x 180 68 / 66 us; FP64 at the last 112 / 99 us)
-    return g.N >= (1ll << 20) ? launch_r<T, 4>(g, op, epi, f, m, s) : launch_r<T, 2>(g, op, epi, f, m, s);
+    if (epi == ME_ADJ) return launch_r<T, ADJ_ROWS<T>>(g, op, epi, f, m, s, waves_out);
+    // (two fields in FP64 leave one wave per SIMD at 4 rows)
+    return g.N >= (1ll << 20) && !(op == MOP_JVP && sizeof(T) == 8) ? launch_r<T, 4>(g, op, epi, f, m, s, waves_out)
+                                : launch_r<T, 2>(g, op, epi, f, m, s, waves_out);
 }
 
-template bool launch_march3d<float>(const Geom&, int, int, const FreeEnergy&, const March<float>&, hipStream_t);
-template bool launch_march3d<double>(const Geom&, int, int, const FreeEnergy&, const March<double>&, hipStream_t);
+template bool launch_march3d<float>(const Geom&, int, int, const FreeEnergy&, const March<float>&, hipStream_t, int*);
+template bool launch_march3d<double>(const Geom&, int, int, const FreeEnergy&, const March<double>&, hipStream_t, int*);
 
 }  // namespace pfk

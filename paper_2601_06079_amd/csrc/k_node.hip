@@ -174,8 +174,8 @@ __global__ __launch_bounds__(256) void k_chem(const T* __restrict__ c, T* __rest
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(256) void k_ch_update(const T* __restrict__ c, const T* __restrict__ mu,
-                                                   T* __restrict__ cout, Geom g, T dtM_over_m)
+__global__ __launch_bounds__(256) void k_ch_update(const T* c, const T* __restrict__ mu, T* cout, Geom g,
+                                                   T dtM_over_m)
 {
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     int i, j, k;
@@ -420,6 +420,17 @@ template <typename T>
 void launch_jvp(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,
                 double inv_dt, const T* U, const T* v, T* Jv, hipStream_t s, int trans, int acc)
 {
+    if (g.dim == 3 && model == 0 && !acc) {
+        March<T> a;
+        a.u = U;
+        a.v = v;
+        a.out = Jv;
+        a.nq = mob;
+        a.kv = mob * kappa;
+        a.s0 = inv_dt * std::pow(g.h, 3);
+        a.rows = 1;
+        if (launch_march3d<T>(g, MOP_JVP, ME_OUT, f, a, s)) return;
+    }
     if (g.dim == 3 && !acc && !g.cm && !g.quad) {
         launch_jvp3d<T>(g, model, f, kappa, mob, inv_dt, U, v, Jv, s, trans);
         return;

@@ -118,17 +118,22 @@ template <typename T>
 void launch_jvp3d(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,
                   double inv_dt, const T* U, const T* v, T* Jv, hipStream_t s, int trans);
 // One marching pass over a 3-D grid (k_march3d.hip; operators and epilogues in
-// march.hpp): lumped mass, both quadratures, fields below 2 GiB.  False (nothing
-// launched) where it does not apply.
+// march.hpp): lumped mass, both quadratures (the adjoint's: Gauss), fields below 2 GiB.
+// False (nothing launched) where it does not apply.  waves_out (the adjoint's): the
+// number of waves, whose sums fill part.
 template <typename T>
-bool launch_march3d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s);
+bool launch_march3d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s,
+                    int* waves_out = nullptr);
 // the same over a 2-D grid, streamed by rows (k_march2d.hip), and whichever fits g.dim
 template <typename T>
-bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s);
+bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s,
+                    int* waves_out = nullptr);
 template <typename T>
-inline bool launch_march(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s)
+inline bool launch_march(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s,
+                         int* waves_out = nullptr)
 {
-    return g.dim == 3 ? launch_march3d<T>(g, op, epi, f, m, s) : launch_march2d<T>(g, op, epi, f, m, s);
+    return g.dim == 3 ? launch_march3d<T>(g, op, epi, f, m, s, waves_out)
+                      : launch_march2d<T>(g, op, epi, f, m, s, waves_out);
 }
 // (block-)Jacobi inverse of dR/dU at U: N (Allen-Cahn) or 4N (Cahn-Hilliard) values
 // (Allen-Cahn: divided by theta)
@@ -161,7 +166,7 @@ void launch_unrow(const Geom& g, double scale, const T* x, T* y, hipStream_t s);
 template <typename T>
 void launch_chem(const Geom& g, const FreeEnergy& f, double kappa, const T* c, T* mu,
                  hipStream_t s);
-// c_out = c - dt M K mu / m
+// c_out = c - dt M K mu / m (c_out may be c)
 template <typename T>
 void launch_ch_update(const Geom& g, double dtM, const T* c, const T* mu, T* c_out,
                       hipStream_t s);
@@ -214,12 +219,25 @@ void launch_dtheta(const Geom& g, int model, const FreeEnergy& f, double kappa, 
 // ubar[0..N) += inv_dt m lam[0..N)
 template <typename T>
 void launch_mass_axpy(const Geom& g, double inv_dt, const T* lam, T* ub, hipStream_t s);
+// Adjoint of one explicit step S at U, marched (Gauss quadrature, fields below 2 GiB;
+// Cahn-Hilliard: c planes, mu = [N + kappa K c] / m of U at mu): lam_out = S^T lam (+ add,
+// may be null), the theta sums of every wave added to part (set when fresh; at most
+// part_max doubles).  lam_out may be lam for Cahn-Hilliard only.  t: N values
+// (Cahn-Hilliard).  False (nothing launched) where it does not apply.
+template <typename T>
+bool launch_adjoint_step(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double dt,
+                         const T* U, const T* mu, const T* lam, T* lam_out, const T* add, T* t, double* part,
+                         long long part_max, int fresh, hipStream_t s);
+// theta_bar[0..3) += what those sums give (the same g, model and part_max)
+template <typename T>
+void launch_adjoint_theta(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double dt,
+                          const double* part, long long part_max, double* theta_bar, hipStream_t s);
 // one explicit step S at U: ubar += (dS/dU)^T vbar, theta_bar += (dS/dtheta)^T vbar
-// (Cahn-Hilliard: c planes only).  scratch: 2N values.
+// (Cahn-Hilliard: c planes only).  scratch: 2N values; part: part_max doubles.
 template <typename T>
 void launch_vjp_explicit(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,
                          double dt, const T* U, const T* vbar, T* ubar, T* scratch, double* part,
-                         double* theta_bar, hipStream_t s);
+                         long long part_max, double* theta_bar, hipStream_t s);
 
 // ---- fused 2-D explicit streaming kernels (k_stream2d.hip) ------------------
 struct Stream2DConfig {

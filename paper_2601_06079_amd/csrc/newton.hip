@@ -741,9 +741,39 @@ int vjp_simple_t(const pf_problem* p, int kind, double dt, bool be, const T* U, 
                               theta_bar, s);
     } else {
         pfk::launch_vjp_explicit<T>(g, p->model, f, p->kappa, p->mobility, dt, U, vbar, Ubar, L.V,
-                                    L.part, theta_bar, s);
+                                    L.part, L.part_len, theta_bar, s);
     }
     return check_launch("pf_vjp");
+}
+
+// Adjoint of nsteps explicit steps along stored states (see pf_vjp_explicit_trajectory)
+template <typename T>
+int vjp_trajectory_t(const pf_problem* p, double dt, int64_t nsteps, const T* states, T* lam, double* theta_bar,
+                     int flags, void* ws, hipStream_t s)
+{
+    const pfk::Geom g = geom_of(p);
+    const pfk::FreeEnergy f = pfk::make_free_energy(p->fe, p->W);
+    NWS<T> L = layout<T>(p, ws);
+    const long long nd = ndof(p);
+    const bool ch = p->model == PF_CAHN_HILLIARD;
+    T* other = L.V;       // Allen-Cahn: lam's second buffer
+    T* t = L.V + L.ld;    // Cahn-Hilliard
+    T* cur = lam;
+    int fresh = flags & PF_VJP_BEGIN ? 1 : 0;
+    for (int64_t k = nsteps - 1; k >= 0; --k) {
+        const T* U = states + k * nd;
+        T* out = ch ? cur : (cur == lam ? other : lam);
+        if (!pfk::launch_adjoint_step<T>(g, p->model, f, p->kappa, p->mobility, dt, U, U + (ch ? g.N : 0), cur, out,
+                                         nullptr, t, L.part, L.part_len, fresh, s))
+            return fail(PF_EUNSUPPORTED, "explicit adjoint trajectory: fields of 2 GiB or more");
+        cur = out;
+        fresh = 0;
+    }
+    if (cur != lam && hipMemcpyAsync(lam, cur, (size_t)g.N * sizeof(T), hipMemcpyDeviceToDevice, s) != hipSuccess)
+        return check_launch("adjoint copy-back");
+    if ((flags & PF_VJP_END) && !(fresh && nsteps == 0))
+        pfk::launch_adjoint_theta<T>(g, p->model, f, p->kappa, p->mobility, dt, L.part, L.part_len, theta_bar, s);
+    return check_launch("pf_vjp_explicit_trajectory");
 }
 
 // Adjoint of one backward-Euler step at its root U (II.5-II.6):
@@ -900,6 +930,29 @@ int pf_vjp(pf_ctx* ctx, const pf_problem* p, int kind, double dt, const void* U,
             hipStreamSynchronize(s) != hipSuccess)
             return check_launch("theta_bar download");
         return PF_OK;
+    });
+}
+
+int pf_vjp_explicit_trajectory(pf_ctx* ctx, const pf_problem* p, double dt, int64_t nsteps, const void* states,
+                               void* lam, double* theta_bar, int flags, void* ws, void* stream)
+{
+    return guarded("pf_vjp_explicit_trajectory", [&]() -> int {
+        if (int rc = check_ctx(ctx)) return rc;
+        if (int rc = validate(p)) return rc;
+        if (int rc = explicit_trajectory_ok(p, dt, nsteps)) return rc;
+        if (p->quad != PF_QUAD_GAUSS) return fail(PF_EUNSUPPORTED, "pf_vjp: Gauss-Lobatto quadrature not implemented");
+        if (flags & ~(PF_VJP_BEGIN | PF_VJP_END)) return fail(PF_EINVAL, "unknown flags 0x%x", flags);
+        if (int rc = check_ptr(states, p, "states")) return rc;
+        if (int rc = check_ptr(lam, p, "lam")) return rc;
+        if (!theta_bar || reinterpret_cast<uintptr_t>(theta_bar) % 8)
+            return fail(PF_EINVAL, "theta_bar is NULL or misaligned");
+        if (!ws || reinterpret_cast<uintptr_t>(ws) % 256) return fail(PF_EINVAL, "ws must be 256-byte aligned");
+        if (int rc = require_device(ctx)) return rc;
+        if (p->dtype == PF_F32)
+            return vjp_trajectory_t<float>(p, dt, nsteps, (const float*)states, (float*)lam, theta_bar, flags, ws,
+                                           (hipStream_t)stream);
+        return vjp_trajectory_t<double>(p, dt, nsteps, (const double*)states, (double*)lam, theta_bar, flags, ws,
+                                        (hipStream_t)stream);
     });
 }
 

@@ -170,6 +170,26 @@ def vjp(p: Problem, kind: int, dt: float, U: torch.Tensor, vbar: torch.Tensor,
                            _stream()))
 
 
+def step_trajectory(p: Problem, states: torch.Tensor, dt: float):
+    """states[1:] from states[0] by single explicit steps, every state kept
+    (states: steps + 1 rows of ndof)."""
+    n = states.shape[0] - 1
+    A.check(A.lib().pf_step_explicit_trajectory(A.ctx(), ct.byref(p.c()), float(dt), n,
+                                                _ptr(states, p, (n + 1) * p.ndof, "states"), _stream()))
+
+
+def vjp_trajectory(p: Problem, states: torch.Tensor, lam: torch.Tensor, theta_bar: torch.Tensor, dt: float,
+                   ws: torch.Tensor, begin: bool = True, end: bool = True):
+    """Adjoint of step_trajectory: lam (dO/d last state) becomes dO/d states[0]; the
+    gradient of theta accumulates in ws from begin and is added to theta_bar at end."""
+    n = states.shape[0] - 1
+    flags = (A.VJP_BEGIN if begin else 0) | (A.VJP_END if end else 0)
+    A.check(A.lib().pf_vjp_explicit_trajectory(A.ctx(), ct.byref(p.c()), float(dt), n,
+                                               _ptr(states, p, (n + 1) * p.ndof, "states"),
+                                               _ptr(lam, p, p.ndof, "lam"), _ptr(theta_bar, None, 3, "theta_bar"),
+                                               flags, ct.c_void_p(ws.data_ptr()), _stream()))
+
+
 def launch_shape(p: Problem):
     """(steps fused per launch, rows per wave, prefetch depth) that step_explicit
     uses for the 2-D problem p."""
@@ -195,15 +215,16 @@ class CheckpointedRun(torch.autograd.Function):
     Eqs. II.5-II.6).
 
     theta = (mobility, kappa, W) as a float64 tensor of 3.  Forward keeps a
-    snapshot every `every` steps; backward walks the segments in reverse,
-    recomputes each segment's states from its snapshot (bitwise the forward's:
-    every kernel is deterministic, and both passes advance with the same launches:
-    fused launches are bitwise single steps on periodic grids, and no-flux grids,
-    where a fused stage rounds the reflected rows differently, take single-step
-    launches in the forward pass too) and applies the step adjoint of the library
-    (pf_vjp: explicit-step VJP, or the transposed Newton solve at each root),
-    accumulating the gradient of theta in FP64.  For Cahn-Hilliard explicit
-    runs only the c plane of U_N is differentiated (mu is recomputed from c).
+    snapshot every `every` steps (explicit runs also the last segment's states);
+    backward walks the segments in reverse, recomputes each segment's states from
+    its snapshot (bitwise the forward's: every kernel is deterministic, and both
+    passes advance with the same launches: fused launches are bitwise single steps
+    on periodic grids, and no-flux grids, where a fused stage rounds the reflected
+    rows differently, take single-step launches in the forward pass too) and applies
+    the step adjoint of the library (the explicit trajectory's adjoint, or the
+    transposed Newton solve at each root), accumulating the gradient of theta in
+    FP64.  For Cahn-Hilliard explicit runs only the c plane of U_N is differentiated
+    (mu is recomputed from c).
     """
 
     @staticmethod
@@ -213,18 +234,30 @@ class CheckpointedRun(torch.autograd.Function):
         th = theta.detach().to("cpu", torch.float64).numpy()
         q = replace(p, mobility=float(th[0]), kappa=float(th[1]), W=float(th[2]))
         U = U0.detach().clone()
-        ws = workspace(q, A.OP_NEWTON if implicit else A.OP_STEP_EXPLICIT, U.device)
+        # the library's trajectory calls: both models, fields below 2 GiB
+        es = torch.empty((), dtype=q.dtype).element_size()
+        traj = not implicit and q.model in (A.ALLEN_CAHN, A.CAHN_HILLIARD) and q.nnodes * es < 1 << 31
+        nseg = nsteps // every
+        kept = 1 if traj and nseg else 0  # segments whose states are kept
         snaps = []
+        if nseg > kept:
+            ws = workspace(q, A.OP_NEWTON if implicit else A.OP_STEP_EXPLICIT, U.device)
         single = q.bc == A.NOFLUX  # match the single-step recomputation bitwise
-        for _ in range(nsteps // every):
+        for _ in range(nseg - kept):
             snaps.append(U.clone())
             if single:
                 for _ in range(every):
                     _advance(q, U, dt, 1, implicit, opts, ws)
             else:
                 _advance(q, U, dt, every, implicit, opts, ws)
+        ctx.last = None
+        if kept:
+            ctx.last = torch.empty((every + 1, U.numel()), dtype=q.dtype, device=U.device)
+            ctx.last[0].copy_(U)
+            step_trajectory(q, ctx.last, dt)
+            U = ctx.last[every].clone()
         ctx.q, ctx.dt, ctx.every, ctx.implicit, ctx.opts = q, dt, every, implicit, opts
-        ctx.snaps, ctx.theta_device = snaps, theta.device
+        ctx.snaps, ctx.theta_device, ctx.traj = snaps, theta.device, traj
         return U
 
     @staticmethod
@@ -235,8 +268,20 @@ class CheckpointedRun(torch.autograd.Function):
         if q.model == A.CAHN_HILLIARD and not implicit:
             lam[N:] = 0
         tb = torch.zeros(3, dtype=torch.float64, device=lam.device)
-        ws = workspace(q, A.OP_NEWTON if implicit else A.OP_STEP_EXPLICIT, lam.device)
         vws = workspace(q, A.OP_VJP, lam.device)
+        if ctx.traj:
+            seg = torch.empty_like(ctx.last) if ctx.snaps else None
+            for i in range(len(ctx.snaps), -1, -1):
+                states = ctx.last
+                if states is None:
+                    break  # no steps
+                if i < len(ctx.snaps):
+                    states = seg
+                    states[0].copy_(ctx.snaps[i])
+                    step_trajectory(q, states, dt)
+                vjp_trajectory(q, states, lam, tb, dt, vws, begin=i == len(ctx.snaps), end=i == 0)
+            return tb.to(ctx.theta_device), lam, None, None, None, None, None, None
+        ws = workspace(q, A.OP_NEWTON if implicit else A.OP_STEP_EXPLICIT, lam.device)
         seg = torch.empty((every + 1, lam.numel()), dtype=q.dtype, device=lam.device)
         Ubar = torch.empty_like(lam)
         kind = A.VJP_NEWTON_STEP if implicit else A.VJP_EXPLICIT_STEP

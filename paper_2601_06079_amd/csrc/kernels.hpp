@@ -135,6 +135,23 @@ inline bool launch_march(const Geom& g, int op, int epi, const FreeEnergy& f, co
     return g.dim == 3 ? launch_march3d<T>(g, op, epi, f, m, s, waves_out)
                       : launch_march2d<T>(g, op, epi, f, m, s, waves_out);
 }
+// S steps of ME_CHEB's iteration in one pass over a 2-D grid (k_cheb2d.hip), op MOP_JVP
+// (S <= 4) or MOP_SCHUR (S <= 2).  m: u, p0 (right-hand side), p1 (preconditioner), nq, kv,
+// kw, s0 as for ME_CHEB, and out; z, zm: the iterate and the one before (null: p1 p0 and 0).
+// product: the last stage is w = J z instead.  out and out2 (the iterate before the result;
+// may be null) must not be read by the pass.  False (nothing launched) where it does not
+// apply.
+constexpr int CHEB_MAXS = 4;
+template <typename T>
+struct ChebGroup {
+    const T *z = nullptr, *zm = nullptr;
+    T* out2 = nullptr;
+    double s1[CHEB_MAXS] = {}, s2[CHEB_MAXS] = {};
+    int product = 0;
+};
+template <typename T>
+bool launch_cheb2d(const Geom& g, int op, const FreeEnergy& f, const March<T>& m, const ChebGroup<T>& q, int S,
+                   hipStream_t s);
 // (block-)Jacobi inverse of dR/dU at U: N (Allen-Cahn) or 4N (Cahn-Hilliard) values
 // (Allen-Cahn: divided by theta)
 template <typename T>

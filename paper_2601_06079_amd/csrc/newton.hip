@@ -266,6 +266,51 @@ struct LinOp {
         }
         return z;
     }
+    // The same with several steps a pass (2-D): w = J z if w is given, else z, in the buffer
+    // returned; null where it does not apply (nothing is launched then).  Between passes the
+    // two iterates stand in z0 and zb or in c and d (needed from the third pass on, and from
+    // the second if w is null); the steps are spread evenly over as few passes as hold them.
+    bool fuses() const { return g.dim == 2 && !(schur && trans) && g.n[1] > pfk::CHEB_MAXS; }
+    T* poly_fused(const T* v, T* z0, T* w, T* c, T* d, hipStream_t s) const
+    {
+        if (!fuses()) return nullptr;
+        const int n = cheb.deg - 1 + (w ? 1 : 0), top = schur ? pfk::CHEB_MAXS / 2 : pfk::CHEB_MAXS;
+        const int passes = (n + top - 1) / top;
+        if (cheb.deg < 2 || (passes > (w ? 2 : 1) && !(c && d))) return nullptr;
+        T *in[2] = {nullptr, nullptr}, *nx[2] = {z0, zb};
+        double rho = cheb.delta / cheb.theta;
+        for (int i = 0, k = 0; i < passes; ++i) {
+            const bool last = i == passes - 1;
+            const int S = n / passes + (i < n % passes ? 1 : 0);
+            pfk::ChebGroup<T> q;
+            q.z = in[0];
+            q.zm = in[1];
+            q.product = last && w;
+            for (int j = 0; j < S && ++k < cheb.deg; ++j) {
+                const double rn = 1.0 / (2.0 * cheb.theta / cheb.delta - rho);
+                q.s1[j] = rho * rn;
+                q.s2[j] = 2.0 * rn * cheb.theta / cheb.delta;
+                rho = rn;
+            }
+            pfk::March<T> e;
+            e.u = U;
+            e.p0 = v;
+            e.p1 = pinv;
+            e.out = last && w ? w : nx[0];
+            q.out2 = last ? nullptr : nx[1];
+            e.s0 = inv_dt * mass();
+            e.nq = schur ? 1.0 / mass() : p->mobility;
+            e.kv = schur ? p->kappa / mass() : p->mobility * p->kappa;
+            e.kw = p->mobility;
+            if (!pfk::launch_cheb2d<T>(g, schur ? pfk::MOP_SCHUR : pfk::MOP_JVP, f, e, q, S, s)) return nullptr;
+            if (last) return e.out;
+            in[0] = nx[0];
+            in[1] = nx[1];
+            nx[0] = in[0] == z0 ? c : z0;
+            nx[1] = in[0] == z0 ? d : zb;
+        }
+        return nullptr;
+    }
     // out = S v (epi ME_OUT), or a step of the Chebyshev iteration (ME_CHEB, e: its inputs)
     void schur_pass(int epi, const T* v, T* out, hipStream_t s, pfk::March<T> b = {}) const
     {
@@ -407,7 +452,9 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
         // Arnoldi step i: w = J z_i, orthogonalise, v_{i+1} and z_{i+1}; its
         // column goes to pinned slot i % 2
         auto enqueue = [&](int i) -> int {
-            A.apply(A.poly(L.V + (long long)i * L.ld, L.z, s), L.w, s);
+            // (the basis vectors behind v_{i+1} serve as scratch until they are made)
+            T *vi = L.V + (long long)i * L.ld, *sc = i + 2 <= MAXM ? vi + L.ld : nullptr;
+            if (!A.poly_fused(vi, L.z, L.w, sc, sc ? sc + L.ld : nullptr, s)) A.apply(A.poly(vi, L.z, s), L.w, s);
             double* slot = rb->host_dev + (i & 1) * DEV_Y;
             const pfk::KrOut out{dh1, dh2, dnrm, slot + DEV_H1, slot + DEV_H2, slot + DEV_NRM};
             if (pfk::kr_cgs2<T>(model, L.V, L.ld, i + 1, L.w, L.V + (long long)(i + 1) * L.ld, L.z, pinv,
@@ -469,7 +516,9 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
                 return check_launch("GMRES solution coefficients");
             if (A.cheb.deg > 1) {
                 pfk::kr_combine<T>(L.V, L.ld, j, dy, pinv, L.w, L.z, n, s);  // w = V y, z = pinv w
-                pfk::kr_add<T>(L.x, A.poly(L.w, L.z, s), n, s);
+                // (the basis is made anew on the next cycle: scratch)
+                const T* z = A.poly_fused(L.w, L.z, nullptr, L.V, L.V + L.ld, s);
+                pfk::kr_add<T>(L.x, z ? z : A.poly(L.w, L.z, s), n, s);
             } else {
                 pfk::kr_update<T>(model, L.V, L.ld, j, dy, pinv, L.x, Nn, s, tr);
             }
@@ -489,10 +538,14 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
 // The upper end is the largest symbol of K (of K K for S) over its diagonal, 5% added.
 // Degree: the diagonal alone would take about P = sqrt(hi / lo) ln(2 / lin) / 2 products;
 // a product in the polynomial costs two to three vectors less than the Gram-Schmidt
-// sweeps of one more basis vector, so the basis is kept to about six vectors.  A loose
-// solve (the first correction, whose residual is mostly of short waves) stops at 2.
-// Measured, ms per step, degree 1 against this rule: 2048^2 Allen-Cahn 19.1 / 7.7,
-// 500 x 420 Cahn-Hilliard 15.4 / 7.2, 128^3 Cahn-Hilliard 5.8 / 4.7.
+// sweeps of one more basis vector, so the basis is kept to about six vectors and the
+// degree to 10; with several products a pass they cost a quarter of that: four vectors
+// and 20.  A loose solve (the first correction, whose residual is mostly of short waves)
+// stops at 2.
+// Measured, ms per step, degree 1 against six vectors, one product a pass: 2048^2
+// Allen-Cahn 19.1 / 6.1, 500 x 420 Cahn-Hilliard 15.4 / 7.2, 128^3 Cahn-Hilliard 5.8 / 4.1;
+// several products a pass, six vectors against four: 2048^2 Allen-Cahn 4.4 / 3.9, 1024^2
+// 1.50 / 1.40 (FP64 1.68 / 1.59), 500^2 1.05 / 0.84, 300^2 Cahn-Hilliard 2.18 / 2.12.
 template <typename T>
 Cheb choose_cheb(const LinOp<T>& A, double lin)
 {
@@ -514,9 +567,9 @@ Cheb choose_cheb(const LinOp<T>& A, double lin)
     hi *= 1.05;
     if (!(lo > 0.0) || !(lo < hi)) return c;
     const double products = 0.5 * std::sqrt(hi / lo) * std::log(2.0 / lin);
-    const int deg = (int)std::lround(products / 6.0);
+    const int deg = (int)std::lround(products / (A.fuses() ? 4.0 : 6.0));
     if (deg < 2) return c;
-    c.deg = std::min(deg, lin > 3e-3 ? 2 : 10);
+    c.deg = std::min(deg, lin > 3e-3 ? 2 : A.fuses() ? 20 : 10);
     c.theta = 0.5 * (hi + lo);
     c.delta = 0.5 * (hi - lo);
     return c;

@@ -202,7 +202,7 @@ int pf_fma_probe(pf_ctx* ctx, int blocks, int iters, float* out, void* stream);
  *                           2 = multigrid with every level launched separately;
  *                           v >= 3 = the multigrid's coarse grids of at most v
  *                           nodes run in one workgroup (default: 1200 in 2-D,
- *                           none in 3-D). */
+ *                           729 in 3-D). */
 enum { PF_TUNE_STREAM2D_ROWS = 0, PF_TUNE_STREAM2D_DEPTH = 1, PF_TUNE_STREAM2D_FUSE = 2,
        PF_TUNE_JVP3D_PLANES = 3, PF_TUNE_EL_PLANES = 4, PF_TUNE_EL_MG = 5, PF_TUNE_STREAM2D_SEAM = 6,
        PF_TUNE_NN_GROUP = 7, PF_TUNE_GS_REORTH = 8, PF_TUNE_GG_STREAM = 9,

@@ -105,6 +105,15 @@ __host__ __device__ __forceinline__ int reflect(int i, int n)
     return i < n ? i : p - i;
 }
 
+// Index i >= -1 where only [-1, n] is used: one step past an end wraps or reflects, what
+// lies further back is any index of the grid (no division, unlike % and reflect).
+template <bool MIRROR>
+__device__ __forceinline__ int near_index(int i, int n)
+{
+    if constexpr (MIRROR) return i < 0 ? 1 : (i < n ? i : (i == n ? n - 2 : n - 1));
+    return i < 0 ? n - 1 : (i < n ? i : (i == n ? 0 : n - 1));
+}
+
 // No-flux grids by reflection.  On the even extension of a field about the end
 // nodes, every ghost element is the mirror image of a real element and adds the
 // same contribution to the boundary node.  So at a node on b boundary faces the

@@ -207,32 +207,18 @@ __global__ __launch_bounds__(256) void k_march3d(March<T> p, ML3 L, MC3<T> k)
     const int zc = wave / L.wpc;
     const int z0 = zc * L.pz, z1 = min(L.nz, z0 + L.pz);
     const int lane = threadIdx.x & (WAVE - 1);
-    const int grp = min(lane / L.W, L.G - 1), col = lane - grp * L.W;  // col >= W past the last group
+    const int grp = min((lane >= L.W) + (lane >= 2 * L.W) + (lane >= 3 * L.W), L.G - 1);
+    const int col = lane - grp * L.W;  // col >= W past the last group
     const int item = (wave - zc * L.wpc) * L.G + grp;
     const bool live = item < L.items && col >= 1 && col < L.W - 1;
     const int it = min(item, L.items - 1);
     const int strip = it % L.nstrips, yb = it / L.nstrips;
     const int xl = strip * (L.W - 2) - 1 + col, y0 = yb * R;
-    int x;
-    if constexpr (MIRROR) {
-        x = reflect(xl, L.nx);
-    } else {
-        x = xl % L.nx;
-        if (x < 0) x += L.nx;
-    }
+    const int x = near_index<MIRROR>(xl, L.nx);
     constexpr int ES = (int)sizeof(T);
     int vo[R + 2];  // byte offset of each row inside a plane
 #pragma unroll
-    for (int j = 0; j < R + 2; ++j) {
-        int y = y0 - 1 + j;
-        if constexpr (MIRROR) {
-            y = reflect(y, L.ny);
-        } else {
-            y %= L.ny;
-            if (y < 0) y += L.ny;
-        }
-        vo[j] = (y * L.nx + x) * ES;
-    }
+    for (int j = 0; j < R + 2; ++j) vo[j] = (near_index<MIRROR>(y0 - 1 + j, L.ny) * L.nx + x) * ES;
     const bool colok = live && xl < L.nx;
     T xs = (T)1;  // no-flux: 1 / 2^b of the columns and rows
     if (MIRROR && p.rows) xs = edge_count(x, L.nx) ? (T)0.5 : (T)1;
@@ -251,7 +237,7 @@ __global__ __launch_bounds__(256) void k_march3d(March<T> p, ML3 L, MC3<T> k)
     if constexpr (ADJ && MIRROR) {
 #pragma unroll
         for (int j = 0; j < R + 2; ++j)
-            vf[j] = p.scale ? (T)(1 << (edge_count(x, L.nx) + edge_count(reflect(y0 - 1 + j, L.ny), L.ny))) : (T)1;
+            vf[j] = p.scale ? (T)(1 << (edge_count(x, L.nx) + edge_count(near_index<true>(y0 - 1 + j, L.ny), L.ny))) : (T)1;
     }
     double sA = 0.0, sB = 0.0;
     const auto ru = make_rsrc(HASU ? p.u : p.v, L.bytes);

@@ -360,12 +360,31 @@ void launch_reduce_pairs(const double* part, int nb, double* out, hipStream_t s)
         __VA_ARGS__;               \
     }
 
+// Where the marching kernels beat one thread per node for the weak forms without a
+// direction.  A march is a serial chain of rows or planes (5 us a pass in 2-D, 4-6 in 3-D
+// however small the grid), the node kernels evaluate every Gauss point 4 or 8 times in
+// parallel.  Measured, march / nodes, us, Gauss, no-flux:
+//   3-D step    64^3 FP32 Allen-Cahn 6.2 / 5.4, Cahn-Hilliard 11.4 / 9.5, FP64 15.7 / 15.4;
+//               72 x 65 x 60 6.2 / 6.7, 11.4 / 11.9, FP64 15.5 / 20.5
+//   3-D Cahn-Hilliard residual (two passes for one) FP32 72 x 65 x 60 9.1 / 7.7,
+//               80^3 11.2 / 11.2, 96^3 13.9 / 17.9; FP64 72 x 65 x 60 11.7 / 13.1
+//   2-D residual FP32 1001 x 777 Allen-Cahn 5.4 / 5.1, Cahn-Hilliard 6.3 / 6.5, 1400^2
+//               7.4 / 9.8, 8.7 / 12.9; FP64 500^2 5.2 / 3.9, 6.5 / 5.2, 1001 x 777 6.5 / 7.3,
+//               8.3 / 10.3
+// so: 2-D fields of at least 4 MiB, 3-D more than 64^3 nodes (2^19 where two FP32 passes
+// stand against one).
+bool march_pays(const Geom& g, size_t esz, bool two_passes)
+{
+    if (g.dim == 2) return (size_t)g.N * esz >= (size_t(4) << 20);
+    return g.N > (two_passes && esz == 4 ? 1ll << 19 : 1ll << 18);
+}
+
 template <typename T>
 void launch_residual(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,
                      const T* U, T* r, hipStream_t s, const T* Uold, double inv_dt)
 {
     const double detJ = std::pow(0.5 * g.h, g.dim), m = std::pow(g.h, g.dim);
-    if (!g.cm) {
+    if (!g.cm && march_pays(g, sizeof(T), g.dim == 3 && model == 1)) {
         // marching kernels: every Gauss point once.  In 3-D the Cahn-Hilliard rows take two
         // passes (they share no quadrature); both fit or neither does.
         March<T> a;
@@ -498,7 +517,7 @@ void launch_chem(const Geom& g, const FreeEnergy& f, double kappa, const T* c, T
     a.out = mu;
     a.nq = 1.0 / m;
     a.kv = kappa / m;
-    if (launch_march<T>(g, MOP_GRAD, ME_OUT, f, a, s)) return;
+    if (march_pays(g, sizeof(T), false) && launch_march<T>(g, MOP_GRAD, ME_OUT, f, a, s)) return;
     DIM_SWITCH(g, {
         k_chem<T, D><<<grid_for(g), 256, 0, s>>>(c, mu, g, cub_of<T>(f, 1.0), (T)detJ, (T)kappa,
                                                   (T)(1.0 / m));
@@ -514,7 +533,7 @@ void launch_ch_update(const Geom& g, double dtM, const T* c, const T* mu, T* c_o
     a.base = c;
     a.out = c_out;
     a.kv = dtM / m;
-    if (launch_march<T>(g, MOP_STIFF, ME_SUB, FreeEnergy{}, a, s)) return;
+    if (march_pays(g, sizeof(T), false) && launch_march<T>(g, MOP_STIFF, ME_SUB, FreeEnergy{}, a, s)) return;
     DIM_SWITCH(g, { k_ch_update<T, D><<<grid_for(g), 256, 0, s>>>(c, mu, c_out, g, (T)(dtM / m)); });
 }
 
@@ -528,7 +547,7 @@ void launch_ac_step(const Geom& g, const FreeEnergy& f, double kappa, double dtL
     a.out = eta_out;
     a.nq = dtL / m;
     a.kv = dtL * kappa / m;
-    if (launch_march<T>(g, MOP_GRAD, ME_SUB, f, a, s)) return;
+    if (march_pays(g, sizeof(T), false) && launch_march<T>(g, MOP_GRAD, ME_SUB, f, a, s)) return;
     DIM_SWITCH(g, {
         k_ac_step<T, D><<<grid_for(g), 256, 0, s>>>(eta, eta_out, g, cub_of<T>(f, 1.0), (T)detJ,
                                                      (T)kappa, (T)(dtL / m));

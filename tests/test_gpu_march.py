@@ -56,3 +56,21 @@ def test_many_nodes_per_lane(bc, quad, dtype):
     Ug = dev(U, dtype)
     S.step_explicit(g, Ug, 1e-3, 1)
     assert rel_l2(host(Ug), O.explicit(o, U, 1e-3, 1)) < TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", [F32, F64])
+@pytest.mark.parametrize("n,bc,quad", [((14, 141, 135), O.NOFLUX, 0), ((19, 120, 118), O.PERIODIC, 0),
+                                       ((30, 99, 90), O.NOFLUX, 1), ((62, 71, 62), O.NOFLUX, 0),
+                                       ((64, 65, 64), O.PERIODIC, 1), ((64, 64, 64), O.NOFLUX, 0),
+                                       ((1031, 1021), O.NOFLUX, 0), ((1025, 1030), O.PERIODIC, 1)])
+def test_just_above_the_node_kernels(n, bc, quad, dtype):
+    """The smallest grids that march, one lane-group count each (64^3: the largest that
+    does not); residual and, in 3-D, two explicit steps."""
+    announce("march from", n, bc, quad, dtype)
+    for model in (O.AC, O.CH):
+        g, o, U = case(n, model, bc, quad, dtype)
+        assert rel_l2(host(S.residual(g, dev(U, dtype))), O.residual(o, U)) < TOL[dtype]
+        if len(n) == 3:
+            Ug = dev(U, dtype)
+            S.step_explicit(g, Ug, 1e-3, 2)
+            assert rel_l2(host(Ug), O.explicit(o, U, 1e-3, 2)) < TOL[dtype]

@@ -169,7 +169,7 @@ int step_coupled_t(const pf_problem* p, int cus, double dt, int64_t nsteps, T* U
     T *cc = c, *co = ws, *ec = eta, *eo = ws + g.N;
     // 2-D: the fused streaming kernel (32-bit buffer offsets); else node-centric kernels
     const bool fused2d = p->dim == 2 && (size_t)g.N * sizeof(T) < (size_t(1) << 31);
-    const int rows = stream2d_rows(p, 1, cus);
+    const int rows = stream2d_rows(p, cus);
     for (int64_t st = 0; st < nsteps; ++st) {
         if (fused2d) {
             pfk::launch_cp_explicit2d<T>(g, p->kappa, p->mobility, p->mobility_eta, dt, cc, ec, co, eo,
@@ -221,18 +221,21 @@ int step_explicit_t(const pf_problem* p, int cus, double dt, int64_t nsteps, T* 
     // the fused 2-D kernel addresses a field with 32-bit buffer offsets
     const bool fused2d = p->dim == 2 && (size_t)g.N * sizeof(T) < (size_t(1) << 31);
     if (fused2d) {
-        // launches of ks fused steps, then the remainder one step at a time
-        const int ks = stream2d_fuse(p);
-        pfk::Stream2DConfig cfg{stream2d_rows(p, ks, cus), stream2d_depth(p), ks};
-        pfk::Stream2DConfig one{stream2d_rows(p, 1, cus), stream2d_depth(p), 1};
-        int64_t st = 0;
-        for (; ks > 1 && st + ks <= nsteps; st += ks) {
+        // the fewest launches of at most ks fused steps, of equal lengths to one step and an
+        // even number of them, so that the last ends in the caller's array (a set count:
+        // launches of that many, then single steps)
+        Stream2DPlan plan;
+        if (nsteps > 2) plan = stream2d_plan(p, cus);
+        else plan.ty[1] = stream2d_rows(p, cus);
+        int64_t n = (nsteps + plan.ks - 1) / plan.ks;
+        if (n % 2 && n < nsteps) ++n;
+        for (int64_t st = 0, i = 0; st < nsteps; ++i) {
+            const int ks = plan.fixed ? (st + plan.ks <= nsteps ? plan.ks : 1)
+                                      : (int)(nsteps / n + (i < nsteps % n ? 1 : 0));
+            const pfk::Stream2DConfig cfg{plan.ty[ks], stream2d_depth(p), ks};
             pfk::launch_explicit2d<T>(g, p->model, f, p->kappa, p->mobility, dt, cur, other, cfg, s);
             std::swap(cur, other);
-        }
-        for (; st < nsteps; ++st) {
-            pfk::launch_explicit2d<T>(g, p->model, f, p->kappa, p->mobility, dt, cur, other, one, s);
-            std::swap(cur, other);
+            st += ks;
         }
     } else if (p->model == PF_ALLEN_CAHN) {
         // node-centric path: 3-D, and 2-D fields of 2 GiB or more
@@ -269,7 +272,7 @@ int step_trajectory_t(const pf_problem* p, int cus, double dt, int64_t nsteps, T
     const pfk::FreeEnergy f = pfk::make_free_energy(p->fe, p->W);
     const long long nd = ndof(p);
     const bool ch = p->model == PF_CAHN_HILLIARD;
-    const pfk::Stream2DConfig one{stream2d_rows(p, 1, cus), stream2d_depth(p), 1};
+    const pfk::Stream2DConfig one{stream2d_rows(p, cus), stream2d_depth(p), 1};
     for (int64_t k = 0; k < nsteps; ++k) {
         T* in = states + k * nd;
         T* out = in + nd;

@@ -3,6 +3,7 @@
 // measurements on MI355X; pf_tune_set overrides them (the autotuner uses it).
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 
 #include "api_internal.hpp"
 
@@ -21,38 +22,20 @@ std::atomic<int> g_gg_stream{0};
 std::atomic<int> g_jvp2d_stream{0};
 }  // namespace
 
-int stream2d_fuse(const pf_problem* p)
+namespace {
+// The plan for a grid of many rounds of waves.  Measured on MI355X: enough chunks for
+// about four waves per SIMD hide latency, and stopping just below a whole number of waves
+// per SIMD avoids a partly filled last round.  Chunks are never shorter than 8 rows.
+// Longer chunks mean a grid of many rounds, where the measured best is 32 rows for single
+// steps and 48 for fused ones.  (The launch splits each strip into balanced chunks, whose
+// sizes differ by at most one row.)
+// (coupled model: six, measured at 512^2..2048^2; its pipeline is VALU-bound and light on
+// registers)
+int full_rows(const pf_problem* p, int ks, int S)
 {
-    const int ov = g_fuse_override.load();
-    if (ov > 0) return std::min(ov, 4);
-    // Measured on MI355X: four fused steps are fastest for Allen-Cahn from 128^2 to
-    // 2048^2 (128^2 FP64: 1.9 against 2.4 us/step for two; 2048^2: 5.8 against 6.8) and
-    // for Cahn-Hilliard below 2048^2, where launches dominate; at 2048^2 and above
-    // Cahn-Hilliard on the seam-sharing kernel is fastest with three or four (7.7
-    // us/step at 2048^2; two: 8.1, and 10% slower than three at 8192^2).  With nodal
-    // quadrature the step is a third of the arithmetic and four are fastest there too
-    // (2048^2: 3.9 us/step; three 4.1, two 4.9).
-    if (p->model == PF_CAHN_HILLIARD && p->quad == PF_QUAD_GAUSS && p->n[0] * p->n[1] >= (1ll << 22))
-        return 3;
-    return 4;
-}
-
-int stream2d_rows(const pf_problem* p, int ks, int cus)
-{
-    const int ov = g_rows_override.load();
-    if (ov > 0) return ov;
     const int HK = (p->model == PF_ALLEN_CAHN ? 1 : 2) * ks;  // Cahn-Hilliard and coupled: 2 per step
     const long long nx = p->n[0], ny = p->n[1];
     const long long strips = (nx + (64 - 2 * HK) - 1) / (64 - 2 * HK);
-    const long long S = 4LL * (cus > 0 ? cus : 256);  // SIMDs
-    // The launch splits each strip into balanced chunks (sizes differ by at most
-    // one row).  Measured on MI355X: enough chunks for about four waves per SIMD
-    // hide latency, and stopping just below a whole number of waves per SIMD
-    // avoids a partly filled last round.  Chunks are never shorter than 8 rows.
-    // Longer chunks mean a grid of many rounds, where the measured best is 32
-    // rows for single steps and 48 for fused ones.
-    // (coupled model: six, measured at 512^2..2048^2; its pipeline is VALU-bound and
-    // light on registers)
     const long long waves = p->model == PF_COUPLED ? 6 : 4;
     long long nch = std::max<long long>(1, waves * S / strips);
     // periodic fused launches run on the seam-sharing kernel, which rounds the chunks
@@ -63,6 +46,95 @@ int stream2d_rows(const pf_problem* p, int ks, int cus)
     const long long tmax = ks == 1 ? 32 : 48;
     if (ty > tmax) ty = tmax;
     return (int)std::max<long long>(ty, 1);
+}
+
+// Relative time per step of launches of ks fused steps with about ty rows per wave:
+//   [ launch + pushes (r + 0.6) + memory ] / ks
+// in units of one row through one stage.  pushes: the rows all stages of a wave take,
+// warm-up included -- with the seams shared ks (ty + 2H) and the top wave's H ks (ks - 1)
+// / 4, else whole groups of four rows less the stages' late starts; r: waves a SIMD takes
+// in turn (a last round that is not full counts 0.3 of what it lacks); 0.6: one wave alone
+// leaves a SIMD idle for three of eight cycles; launch and memory: fitted.  Against 24-step
+// runs at 16 sizes from 96^2 to 4096^2, both models, types, boundaries and quadratures,
+// 51 launch shapes each, its choice is 1.6% off the best on average (full_rows with four
+// steps: 18%) and at most 2% slower than the latter.  us per run before and after: 128^2
+// Allen-Cahn FP64 100 steps 187 / 145, 800 x 700 Cahn-Hilliard FP64 20 steps 123 / 86, 1200
+// x 1300 Allen-Cahn FP32 37 steps 180 / 114, 1448^2 Cahn-Hilliard FP32 30 steps 227 / 187.
+double plan_cost(const pf_problem* p, int ks, int ty, int S)
+{
+    const int H = p->model == PF_ALLEN_CAHN ? 1 : 2, HK = H * ks;
+    const int nx = (int)p->n[0], ny = (int)p->n[1];
+    const int strips = (nx + (64 - 2 * HK) - 1) / (64 - 2 * HK);
+    const int nch = (ny + ty - 1) / ty;
+    double waves = 0.0, pushes = 0.0;
+    if (!p->bc) {
+        // the seam kernel's own conditions (launch_seam)
+        const int n4 = (nch + 3) / 4 * 4, rmin = ny / (n4 / 4), sh = H * (ks - 1);
+        const int shortest = rmin - 3 * (rmin + sh) / 4;
+        if (shortest >= (2 * HK + 3) / 4 * 4 + 4 - 2 * H && shortest >= 8) {
+            waves = (double)strips * n4;
+            pushes = ks * ((ny + n4 - 1) / n4 + 2 * H) + 0.25 * H * ks * (ks - 1);
+        }
+    }
+    if (pushes == 0.0) {
+        waves = (double)strips * nch;
+        pushes = ks * (((ny + nch - 1) / nch + 2 * HK + 3) / 4 * 4) - H * ks * (ks - 1);
+    }
+    const bool lob = p->quad == PF_QUAD_LOBATTO;
+    const double w = waves / S, full = std::ceil(w), r = std::max(1.0, w + 0.3 * (full - w));
+    const double mb = 1e-6 * nx * ny * (p->dtype == PF_F64 ? 8 : 4);
+    return ((lob ? 80.0 : 50.0) + pushes * (r + 0.6) + (lob ? 10.0 : 2.0) * mb) / ks;
+}
+}  // namespace
+
+int stream2d_rows(const pf_problem* p, int cus)
+{
+    const int ov = g_rows_override.load();
+    return ov > 0 ? ov : full_rows(p, 1, 4 * (cus > 0 ? cus : 256));
+}
+
+Stream2DPlan stream2d_plan(const pf_problem* p, int cus)
+{
+    const int S = 4 * (cus > 0 ? cus : 256);  // SIMDs
+    const int rows = g_rows_override.load(), fuse = g_fuse_override.load();
+    Stream2DPlan q;
+    q.ty[1] = rows > 0 ? rows : full_rows(p, 1, S);
+    // The plan of grids of many rounds.  Four fused steps are fastest there for
+    // Allen-Cahn; Cahn-Hilliard on the seam-sharing kernel is fastest with three from
+    // 2048^2 (7.7 us/step; two: 8.1, and 10% slower than three at 8192^2); with nodal
+    // quadrature the step is a third of the arithmetic and four are fastest (2048^2: 3.9
+    // us/step; three 4.1, two 4.9).
+    const int kf = p->model == PF_CAHN_HILLIARD && p->quad == PF_QUAD_GAUSS && p->n[0] * p->n[1] >= (1ll << 22) ? 3 : 4;
+    q.fixed = fuse > 0;
+    static const int cand[] = {2, 4, 6, 8, 10, 12, 14, 16, 18, 20, 24, 28, 32, 36, 40, 48};
+    const int tf = full_rows(p, kf, S);
+    const double cf = plan_cost(p, kf, tf, S);
+    double best = 0.0;
+    int kb = kf;
+    for (int k = 2; k <= 4; ++k) {
+        q.ty[k] = full_rows(p, k, S);
+        double c = plan_cost(p, k, q.ty[k], S);
+        for (int t : cand) {
+            if (t > p->n[1]) break;
+            const double ct = plan_cost(p, k, t, S);
+            if (ct < c) {
+                c = ct;
+                q.ty[k] = t;
+            }
+        }
+        if (best == 0.0 || c < best) {
+            best = c;
+            kb = k;
+        }
+    }
+    // (that plan keeps its place where the estimate gains less than 3%)
+    if (best > 0.97 * cf) {
+        kb = kf;
+        q.ty[kf] = tf;
+    }
+    q.ks = fuse > 0 ? std::min(fuse, 4) : kb;
+    if (rows > 0) q.ty[2] = q.ty[3] = q.ty[4] = rows;
+    return q;
 }
 
 int stream2d_depth(const pf_problem* p)
@@ -123,8 +195,9 @@ int pf_launch_shape(const pf_ctx* ctx, const pf_problem* p, int* ks, int* ty, in
         if (int rc = check_ctx(ctx)) return rc;
         if (int rc = validate(p)) return rc;
         if (!ks || !ty || !depth) return fail(PF_EINVAL, "NULL output pointer");
-        *ks = stream2d_fuse(p);
-        *ty = stream2d_rows(p, *ks, ctx->cus);
+        const Stream2DPlan q = stream2d_plan(p, ctx->cus);
+        *ks = q.ks;
+        *ty = q.ty[q.ks];
         *depth = stream2d_depth(p);
         return PF_OK;
     });

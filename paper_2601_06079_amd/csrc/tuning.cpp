@@ -85,12 +85,46 @@ double plan_cost(const pf_problem* p, int ks, int ty, int S)
     const double mb = 1e-6 * nx * ny * (p->dtype == PF_F64 ? 8 : 4);
     return ((lob ? 80.0 : 50.0) + pushes * (r + 0.6) + (lob ? 10.0 : 2.0) * mb) / ks;
 }
+// Rows of single steps (explicit steps one at a time; the coupled model): the pushes of a
+// wave, in whole groups of four, times the waves a SIMD takes in turn (the last round as
+// above; for the coupled model, whose waves are longer, as a full one), with the share a
+// SIMD idles under one wave (fitted; smaller in FP64).  Single steps at the 16 sizes above:
+// 1.5% off the best on average (full_rows: 11%); with nodal quadrature, a third of the
+// arithmetic, it would be up to 10% slower than full_rows.  Coupled, us for 20 steps: 128^2
+// 135 / 105, 500^2 173 / 149, 900^2 252 / 212, FP64 768^2 272 / 230, 1024^2 346 / 307.
+int single_rows(const pf_problem* p, int S)
+{
+    const int H = p->model == PF_ALLEN_CAHN ? 1 : 2, outw = 64 - 2 * H;
+    const int strips = ((int)p->n[0] + outw - 1) / outw, ny = (int)p->n[1];
+    const bool cp = p->model == PF_COUPLED;
+    if (p->quad == PF_QUAD_LOBATTO) return full_rows(p, 1, S);
+    const double idle = p->dtype == PF_F64 ? (cp ? 0.7 : 0.3) : (cp ? 1.0 : 0.6), part = cp ? 1.0 : 0.3;
+    auto cost = [&](int ty) {
+        const int nch = (ny + ty - 1) / ty;
+        const double w = (double)strips * nch / S, r = std::max(1.0, w + part * (std::ceil(w) - w));
+        return (((ny + nch - 1) / nch + 2 * H + 3) / 4 * 4) * (r + idle);
+    };
+    const int full = full_rows(p, 1, S);
+    int best = full;
+    double c = 0.97 * cost(full);
+    for (int len = (2 * H + 2 + 3) / 4 * 4; len <= 36; len += 4) {
+        const int ty = std::min(len - 2 * H, ny);
+        const double ct = cost(ty);
+        if (ct < c) {
+            c = ct;
+            best = ty;
+        }
+        if (ty == ny) break;
+    }
+    return best;
+}
+
 }  // namespace
 
 int stream2d_rows(const pf_problem* p, int cus)
 {
     const int ov = g_rows_override.load();
-    return ov > 0 ? ov : full_rows(p, 1, 4 * (cus > 0 ? cus : 256));
+    return ov > 0 ? ov : single_rows(p, 4 * (cus > 0 ? cus : 256));
 }
 
 Stream2DPlan stream2d_plan(const pf_problem* p, int cus)
@@ -98,7 +132,7 @@ Stream2DPlan stream2d_plan(const pf_problem* p, int cus)
     const int S = 4 * (cus > 0 ? cus : 256);  // SIMDs
     const int rows = g_rows_override.load(), fuse = g_fuse_override.load();
     Stream2DPlan q;
-    q.ty[1] = rows > 0 ? rows : full_rows(p, 1, S);
+    q.ty[1] = rows > 0 ? rows : single_rows(p, S);
     // The plan of grids of many rounds.  Four fused steps are fastest there for
     // Allen-Cahn; Cahn-Hilliard on the seam-sharing kernel is fastest with three from
     // 2048^2 (7.7 us/step; two: 8.1, and 10% slower than three at 8192^2); with nodal

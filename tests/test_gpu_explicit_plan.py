@@ -44,3 +44,24 @@ def test_plan_against_single_steps(n, model, bc, quad, dtype):
         else:
             eps = torch.finfo(dtype).eps
             assert (a[:N] - b[:N]).abs().max() <= 16 * eps * b[:N].abs().max(), steps
+
+
+@pytest.mark.parametrize("dtype", [F32, F64])
+def test_batch_rows_do_not_matter(dtype):
+    """A batch large enough for chunks other than the shortest: the same bits as with 8 rows."""
+    announce("batch rows", dtype)
+    from paper_2601_06079_amd import batch as B
+
+    sizes = [(130 + 24 * i, 500 - 20 * i) for i in range(16)]
+    th = [(1.0 + 0.01 * i, 0.7, 1.0) for i in range(16)]
+    out = []
+    for ty in (0, 8):
+        b = B.Batch(sizes, th, 0.05, dtype=dtype, ty=ty)
+        assert (b.info.ty > 8) == (ty == 0)
+        U = b.empty()
+        for i, v in enumerate(b.views(U)):
+            v.copy_(dev(I.uniform_field(sizes[i], -0.3, 0.3, seed=i, base=0.0), dtype).view_as(v))
+        b.step(U, 6)
+        out.append([v.clone() for v in b.views(U)])
+    for x, y in zip(*out):
+        assert torch.equal(x, y)

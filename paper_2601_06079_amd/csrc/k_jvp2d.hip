@@ -257,13 +257,10 @@ bool launch_jvp2d_stream(const Geom& g, int model, const FreeEnergy& f, double k
         k.kw = (T)(mob * ks);
         k.mw = (T)m;
     }
-    // chunks for about four waves per SIMD, never shorter than 8 rows
     // (PF_TUNE_STREAM2D_ROWS sets the rows per chunk instead)
     const int nstrips = (nx + WAVE - 3) / (WAVE - 2);
-    long long nch = std::max<long long>(1, 16ll * device_cus() / nstrips);
-    nch = std::min<long long>(nch, std::max(1, ny / 8));
     const int tov = tune_stream2d_rows();
-    const int ty = tov > 0 ? std::min(tov, ny) : (int)((ny + nch - 1) / nch);
+    const int ty = tov > 0 ? std::min(tov, ny) : pass_rows(ny, nstrips, 1, device_cus());
     const int nchunks = (ny + ty - 1) / ty;
     const long long nwaves = (long long)nstrips * nchunks;
     if (nwaves > (1ll << 30)) return false;

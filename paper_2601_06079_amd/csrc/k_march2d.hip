@@ -164,11 +164,8 @@ bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
     const int nx = g.n[0], ny = g.n[1], outw = WAVE - 2 * H;
     if (ny < 2 * H) return false;
     const int nstrips = (nx + outw - 1) / outw;
-    // chunks for about four waves per SIMD, never shorter than 8 rows (as k_jvp2d)
-    long long nch = std::max<long long>(1, 16ll * march2_cus() / nstrips);
-    nch = std::min<long long>(nch, std::max(1, ny / 8));
     const int tov = tune_stream2d_rows();
-    const int ty = tov > 0 ? std::min(tov, ny) : (int)((ny + nch - 1) / nch);
+    const int ty = tov > 0 ? std::min(tov, ny) : pass_rows(ny, nstrips, H, march2_cus(), epi < ME_ADJ);
     const long long nwaves = (long long)nstrips * ((ny + ty - 1) / ty);
     if (nwaves > (1ll << 30)) return false;
     if (epi == ME_ADJ || epi == ME_ADJK) {

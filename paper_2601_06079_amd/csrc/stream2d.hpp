@@ -1,6 +1,7 @@
 // stream2d.hpp -- helpers of the row-streaming 2-D kernels (one 64-lane
 // wavefront per strip of columns, rows marched through registers).
 #pragma once
+#include <algorithm>
 #include "device.hpp"
 
 namespace pfk {
@@ -49,4 +50,22 @@ __device__ __forceinline__ int uniform_wave()
 }
 
 }  // namespace
+// Rows per wave of one row-streamed pass over ny rows and nstrips strips, H halo rows a
+// side, rows taken in groups of four.  Where one wave per SIMD covers the grid the shortest
+// chunks win (2-D products, FP32, us: 300 x 260 2 rows 2.7, 6 3.4, 8 4.1; 500^2 6 rows 3.6,
+// 8 4.2; FP64 500^2 4.5 / 5.4).  Else chunks for about four waves per SIMD, never shorter
+// than 8 rows, which nothing tried beats by more than it loses elsewhere.  any = false:
+// only the latter (waves with sums of their own, whose number a workspace bounds).
+inline int pass_rows(int ny, int nstrips, int H, int cus, bool any = true)
+{
+    const long long simds = 4ll * cus;
+    for (int len = 4; any && len <= 8; len += 4) {
+        const int ty = std::min(len - 2 * H, ny);
+        if (ty > 0 && (long long)nstrips * ((ny + ty - 1) / ty) <= simds) return ty;
+    }
+    long long nch = std::max<long long>(1, 4 * simds / nstrips);
+    nch = std::min<long long>(nch, std::max(1, ny / 8));
+    return (int)((ny + nch - 1) / nch);
+}
+
 }  // namespace pfk

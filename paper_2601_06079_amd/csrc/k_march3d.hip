@@ -378,47 +378,88 @@ int march_cus()
 
 }  // namespace
 
-// Lane groups and planes per chunk for an nx x ny x nz grid and R rows per lane: G with
-// the fewest waves per plane, then pz with the least time on the busiest SIMD, taken as
-// max(3, waves per SIMD) pushes of pz + 2 planes: below three waves per SIMD the plane
-// loads' latency shows (130 x 121 x 117, 4 rows: pz = 5 with two waves 25.0 us per
-// Cahn-Hilliard step, pz = 3 with three 23.3 us).
-static void march3d_shape(int nx, int ny, int nz, int R, int cus, int* G, int* pz)
+// How a grid is split: R rows per lane, G lane groups, pz planes per chunk.
+struct Shape3 {
+    int R, G, pz;
+};
+
+// G with the fewest waves per plane for R rows per lane; returns that number
+static long long plane_waves(const Geom& g, int R, int* G)
 {
-    int bg = 1;
-    long long bw = -1;
-    for (int g = 1; g <= 4; ++g) {
-        const int w = WAVE / g;
-        const long long items = (long long)((nx + w - 3) / (w - 2)) * ((ny + R - 1) / R);
-        const long long waves = (items + g - 1) / g;
-        if (bw < 0 || waves < bw) {
-            bw = waves;
-            bg = g;
+    long long best = -1;
+    for (int q = 1; q <= 4; ++q) {
+        const int w = WAVE / q;
+        const long long items = (long long)((g.n[0] + w - 3) / (w - 2)) * ((g.n[1] + R - 1) / R);
+        const long long waves = (items + q - 1) / q;
+        if (best < 0 || waves < best) {
+            best = waves;
+            *G = q;
         }
     }
-    const long long simds = 4ll * (cus < 1 ? 1 : cus);
-    int bp = 1;
+    return best;
+}
+
+// Kernels bound by memory or latency (K v, nodal quadrature) and the adjoint: R given, the
+// pz with the least time on the busiest SIMD, taken as max(3, waves per SIMD) pushes of
+// pz + 2 planes: below three waves per SIMD the plane loads' latency shows.
+static Shape3 shape_light(const Geom& g, int R)
+{
+    Shape3 p{R, 1, 1};
+    const long long bw = plane_waves(g, R, &p.G), simds = 4ll * march_cus();
     double bt = -1.0;
-    for (int q = 1; q <= std::min(nz, 64); ++q) {
-        const long long per = (bw * ((nz + q - 1) / q) + simds - 1) / simds;
+    for (int q = 1; q <= std::min(g.n[2], 64); ++q) {
+        const long long per = (bw * ((g.n[2] + q - 1) / q) + simds - 1) / simds;
         const double t = (double)std::max(3ll, per) * (q + 2);
         if (bt < 0.0 || t <= bt) {
             bt = t;
-            bp = q;
+            p.pz = q;
         }
     }
-    *G = bg;
-    *pz = bp;
+    return p;
+}
+
+// Gauss quadrature, bound by issue: a wave pushes pz + 2 planes (with 2 rows and JVP the
+// first one is cheaper), 2 rows per lane costing 0.6 (JVP 0.65) of 4, and a SIMD takes its
+// waves in turn, idling a share of one wave's time (idle), a last round that is not full
+// counting as part of one (part).  Fitted to 32 splits of 12 grids from 72 x 65 x 60 to 256
+// x 200 x 180: 0.3% off the best on average, where 4 rows from 2^20 nodes and the rule
+// above are 10% (FP32) to 20% (FP64) off.  us before and after: Allen-Cahn step 128^3 FP32
+// 17.1 / 14.7, FP64 23.4 / 18.4; product 128^3 21.5 / 18.4, FP64 28.1 / 24.8; 72 x 65 x 60
+// 7.4 / 6.5, FP64 9.8 / 7.5.  (Two fields in FP64 leave one wave per SIMD at 4 rows.)
+static Shape3 shape_gauss(const Geom& g, bool jvp, bool f64)
+{
+    static const int planes[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 16, 20, 24};
+    const double idle = jvp ? (f64 ? 0.2 : 0.8) : (f64 ? 0.4 : 1.0), part = jvp == f64 ? 0.5 : 1.0;
+    const double simds = 4.0 * march_cus();
+    Shape3 best{2, 1, 1};
+    double bt = -1.0;
+    for (int R = 2; R <= (jvp && f64 ? 2 : 4); R += 2) {
+        int G = 1;
+        const long long bw = plane_waves(g, R, &G);
+        const double push = R == 4 ? 1.0 : jvp ? 0.65 : 0.6, first = jvp && R == 2 ? 0.4 : 0.0;
+        for (int q : planes) {
+            if (q > g.n[2]) break;
+            const double w = (double)(bw * ((g.n[2] + q - 1) / q)) / simds;
+            const double t = push * (std::max(1.0, w + part * (std::ceil(w) - w)) + idle) * (q + 2 - first);
+            if (bt < 0.0 || t < bt) {
+                bt = t;
+                best = {R, G, q};
+            }
+        }
+    }
+    return best;
 }
 
 template <typename T, int R>
-bool launch_r(const Geom& g, int op, int epi, const FreeEnergy& f, const March<T>& m, hipStream_t s, int* waves_out)
+bool launch_r(const Geom& g, const Shape3& shape, int op, int epi, const FreeEnergy& f, const March<T>& m,
+              hipStream_t s, int* waves_out)
 {
     ML3 L{};
     L.nx = g.n[0];
     L.ny = g.n[1];
     L.nz = g.n[2];
-    march3d_shape(L.nx, L.ny, L.nz, R, march_cus(), &L.G, &L.pz);
+    L.G = shape.G;
+    L.pz = shape.pz;
     L.W = WAVE / L.G;
     L.nstrips = (L.nx + L.W - 3) / (L.W - 2);
     const long long items = (long long)L.nstrips * ((L.ny + R - 1) / R);
@@ -497,14 +538,14 @@ bool launch_march3d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
 {
     // 32-bit buffer offsets, and the Gauss-integrated mass has no marching form
     if (g.dim != 3 || g.cm || (size_t)g.N * sizeof(T) >= (size_t(1) << 31)) return false;
-    // rows per lane: 4 element rows' redundancy is 5/4 against 3/2 for 2, which pays once
-    // the grid fills the chip; below about a million nodes more waves matter (explicit
-    // Cahn-Hilliard step, FP32, 2 against 4 rows: 72 x 65 x 60 13.3 / 13.9 us, 130 x 121 x
-    // 117 23.7 / 23.3 us, 256 x 200 x 180 68 / 66 us; FP64 at the last 112 / 99 us)
-    if (epi == ME_ADJ) return launch_r<T, ADJ_ROWS<T>>(g, op, epi, f, m, s, waves_out);
-    // (two fields in FP64 leave one wave per SIMD at 4 rows)
-    return g.N >= (1ll << 20) && !(op == MOP_JVP && sizeof(T) == 8) ? launch_r<T, 4>(g, op, epi, f, m, s, waves_out)
-                                : launch_r<T, 2>(g, op, epi, f, m, s, waves_out);
+    if (epi == ME_ADJ)
+        return launch_r<T, ADJ_ROWS<T>>(g, shape_light(g, ADJ_ROWS<T>), op, epi, f, m, s, waves_out);
+    // rows per lane of the light kernels: 4 element rows' redundancy is 5/4 against 3/2 for
+    // 2, which pays once the grid fills the chip; below about a million nodes more waves matter
+    const bool f64 = sizeof(T) == 8, two = g.N < (1ll << 20) || (op == MOP_JVP && f64);
+    const Shape3 p = op != MOP_STIFF && !g.quad ? shape_gauss(g, op == MOP_JVP, f64) : shape_light(g, two ? 2 : 4);
+    return p.R == 4 ? launch_r<T, 4>(g, p, op, epi, f, m, s, waves_out)
+                    : launch_r<T, 2>(g, p, op, epi, f, m, s, waves_out);
 }
 
 template bool launch_march3d<float>(const Geom&, int, int, const FreeEnergy&, const March<float>&, hipStream_t, int*);

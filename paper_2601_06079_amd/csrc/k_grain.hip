@@ -463,8 +463,34 @@ void launch_gg_tile2d(const Geom& g, int P, double L, double kappa, double gamma
                                               (T)0);
 }
 
-// one launch of k_gg_stream2d<T, P, MIRROR>: chunks sized so that strips x chunks
-// just fills the waves the kernel's occupancy keeps resident (at least 8 rows each)
+// Chunks of rows for nstrips strips: a wave marches its rows and 2 more; a SIMD that holds
+// k waves takes its share of them k at a time, each batch lasting as long as its waves plus
+// the 0.8 of one that a single wave idles.  Starts from the chunks that just fill the
+// resident waves.  Fitted to 20 chunk lengths at 96^2 to 1024^2, 2 to 20 fields: 0.3% off
+// the best on average.  us per step, resident waves with at least 8 rows each / this rule:
+// 20 fields 96^2 27.7 / 9.0, 400^2 30.2 / 17.2, 1024^2 53.4 / 48.1; 8 fields 200^2 11.8 /
+// 5.9, 1024^2 26.0 / 20.6; 2 fields 96^2 5.8 / 3.5.
+static int gg_chunks(int ny, int nstrips, int k, int cus)
+{
+    const int simds = 4 * (cus > 0 ? cus : 256);
+    auto cost = [&](int nch) {
+        const int w = (int)(((long long)nstrips * nch + simds - 1) / simds), rem = w % k;
+        return ((ny + nch - 1) / nch + 2) * (w / k * (k + 0.8) + (rem ? rem + 0.8 : 0.0));
+    };
+    int best = (int)std::min<long long>(std::max<long long>(1, (long long)simds * k / nstrips), std::max(1, ny / 8));
+    double c = cost(best);
+    for (int ty = 1; ty <= std::min(ny, 40); ty += ty < 12 ? 1 : ty < 20 ? 2 : 4) {
+        const int nch = (ny + ty - 1) / ty;
+        const double ct = cost(nch);
+        if (ct < c) {
+            c = ct;
+            best = nch;
+        }
+    }
+    return best;
+}
+
+// one launch of k_gg_stream2d<T, P, MIRROR>
 template <typename T, int P, bool MIRROR>
 void gg_stream_launch(const Geom& g, const GGCoef<T>& k, const T* in, T* out, int cus, hipStream_t s)
 {
@@ -478,10 +504,7 @@ void gg_stream_launch(const Geom& g, const GGCoef<T>& k, const T* in, T* out, in
     }();
     const int nx = g.n[0], ny = g.n[1];
     const int nstrips = (nx + WAVE - 3) / (WAVE - 2);
-    const long long resident = 4ll * per_cu * (cus > 0 ? cus : 256);  // waves: 4 per block
-    long long nch = std::max<long long>(1, resident / nstrips);
-    nch = std::min<long long>(nch, std::max(1, ny / 8));
-    const int nchunks = (int)nch;
+    const int nchunks = gg_chunks(ny, nstrips, per_cu, cus);  // per_cu blocks of 4 waves: per_cu waves per SIMD
     const int nwaves = nstrips * nchunks;
     const int fbytes = (int)(g.N * sizeof(T));
     const unsigned bytes = (unsigned)((double)P * g.N * sizeof(T));

@@ -1328,14 +1328,17 @@ int resident_waves(K kernel)
 // Planes per work item: each item pays two warm-up planes and the grid holds at
 // most the resident waves, which loop over the items; pick the chunk length that
 // minimises (items per wave) x (planes + 2) (measured on MI355X: a grid just over
-// one round of resident waves runs ~1.3x slower than one just under it).
+// one round of resident waves runs ~1.3x slower than one just under it).  A grid whose
+// planes fill at most half the resident waves takes one plane an item: its time is the
+// serial march (33^3 4.1 -> 3.5 us, 17^3 4.0 -> 3.5).
 ApplyShape apply_shape(const Grid& g, int slots)
 {
     ApplyShape s{};
     s.nseg = (int)((g.P + EL_OUT - 1) / EL_OUT);
     int tz = 1;
     long long best = -1;
-    for (int t = 2; t <= 64; ++t) {
+    const int first = (long long)s.nseg * g.nz * 2 <= slots ? 1 : 2;
+    for (int t = first; t <= 64; ++t) {
         const long long items = (long long)s.nseg * ((g.nz + t - 1) / t);
         const long long cost = ((items + slots - 1) / slots) * (std::min(t, g.nz) + 2);
         if (best < 0 || cost < best) {

@@ -46,19 +46,32 @@ class Problem:
     def ndof(self):
         if self.model == A.GRAIN:
             return int(self.nfields) * self.nnodes
-        return {A.CAHN_HILLIARD: 2, A.COUPLED: 3}.get(self.model, 1) * self.nnodes
+        return _FIELDS.get(self.model, 1) * self.nnodes
 
     def c(self) -> A.pf_problem:
-        n3 = [int(v) for v in self.n] + [1] * (3 - len(self.n))
-        return A.pf_problem(self.dim, self.bc, self.model, self.fe,
-                            A.F64 if self.dtype == torch.float64 else A.F32, int(self.mass),
-                            (ct.c_int64 * 3)(*n3), float(self.h), float(self.W),
-                            float(self.kappa), float(self.mobility), float(self.mobility_eta),
-                            int(self.nfields), int(self.quad), float(self.gamma))
+        n = self.n
+        d = len(n)
+        n3 = _N3(int(n[0]), int(n[1]), int(n[2]) if d > 2 else 1) if d in (2, 3) else _N3(*(int(v) for v in n), 1, 1)
+        return A.pf_problem(d, self.bc, self.model, self.fe, A.F64 if self.dtype == torch.float64 else A.F32,
+                            int(self.mass), n3, float(self.h), float(self.W), float(self.kappa),
+                            float(self.mobility), float(self.mobility_eta), int(self.nfields), int(self.quad),
+                            float(self.gamma))
 
 
+_FIELDS = {A.CAHN_HILLIARD: 2, A.COUPLED: 3}
+_N3 = ct.c_int64 * 3
+
+
+# A small call's kernels take 8 us and its wrapper took 8 as well: the current device's
+# stream and context are looked up by index, without stream and device objects, and the
+# sizes worked out once a call (three operators at 1001 x 777: 33 us before).
 def _stream():
-    return ct.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+def _ctx():
+    device = torch.cuda.current_device()
+    return A._ctxs.get(device) or A.ctx(device)
 
 
 def _ptr(t: torch.Tensor, p: Problem = None, n: int = None, name="tensor"):
@@ -70,7 +83,7 @@ def _ptr(t: torch.Tensor, p: Problem = None, n: int = None, name="tensor"):
         raise ValueError(f"{name} has dtype {t.dtype}, problem says {p.dtype}")
     if n is not None and t.numel() != n:
         raise ValueError(f"{name} has {t.numel()} elements, expected {n}")
-    return ct.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def workspace(p: Problem, op: int, device=None) -> torch.Tensor:
@@ -82,8 +95,9 @@ def workspace(p: Problem, op: int, device=None) -> torch.Tensor:
 
 def residual(p: Problem, U: torch.Tensor, out: torch.Tensor = None) -> torch.Tensor:
     r = torch.empty_like(U) if out is None else out
-    A.check(A.lib().pf_residual(A.ctx(), ct.byref(p.c()), _ptr(U, p, p.ndof, "U"),
-                                _ptr(r, p, p.ndof, "r"), None, _stream()))
+    nd = p.ndof
+    A.check(A.lib().pf_residual(_ctx(), ct.byref(p.c()), _ptr(U, p, nd, "U"), _ptr(r, p, nd, "r"), None,
+                                _stream()))
     return r
 
 
@@ -92,9 +106,8 @@ def step_explicit(p: Problem, U: torch.Tensor, dt: float, nsteps: int,
     """nsteps explicit steps in place on U; returns U."""
     if ws is None:
         ws = workspace(p, A.OP_STEP_EXPLICIT, U.device)
-    A.check(A.lib().pf_step_explicit(A.ctx(), ct.byref(p.c()), float(dt), int(nsteps),
-                                     _ptr(U, p, p.ndof, "U"), ct.c_void_p(ws.data_ptr()),
-                                     _stream()))
+    A.check(A.lib().pf_step_explicit(_ctx(), ct.byref(p.c()), float(dt), int(nsteps),
+                                     _ptr(U, p, p.ndof, "U"), ws.data_ptr(), _stream()))
     return U
 
 
@@ -105,16 +118,17 @@ def energy(p: Problem, U: torch.Tensor, ws: torch.Tensor = None,
         ws = workspace(p, A.OP_ENERGY, U.device)
     if out is None:
         out = torch.empty(2, dtype=torch.float64, device=U.device)
-    A.check(A.lib().pf_energy(A.ctx(), ct.byref(p.c()), _ptr(U, p, p.ndof, "U"),
-                              ct.c_void_p(out.data_ptr()), ct.c_void_p(ws.data_ptr()), _stream()))
+    A.check(A.lib().pf_energy(_ctx(), ct.byref(p.c()), _ptr(U, p, p.ndof, "U"), out.data_ptr(), ws.data_ptr(),
+                              _stream()))
     return out
 
 
 def jvp(p: Problem, inv_dt: float, U: torch.Tensor, v: torch.Tensor,
         out: torch.Tensor = None) -> torch.Tensor:
     Jv = torch.empty_like(U) if out is None else out
-    A.check(A.lib().pf_jvp(A.ctx(), ct.byref(p.c()), float(inv_dt), _ptr(U, p, p.ndof, "U"),
-                           _ptr(v, p, p.ndof, "v"), _ptr(Jv, p, p.ndof, "Jv"), _stream()))
+    nd = p.ndof
+    A.check(A.lib().pf_jvp(_ctx(), ct.byref(p.c()), float(inv_dt), _ptr(U, p, nd, "U"), _ptr(v, p, nd, "v"),
+                           _ptr(Jv, p, nd, "Jv"), _stream()))
     return Jv
 
 

@@ -253,6 +253,7 @@ __global__ __launch_bounds__(KB) void k_axpy_normalize(const T* __restrict__ V, 
         for (int l = 0; l < VW; ++l) vc.v[l] = (T)((T)xc[l] * inv);
         stp<T, VW>(vnext + o, vc);
         if constexpr (MODEL == 0) {
+            if (!z) continue;
             Pack<T, VW> zc;
             if (pinv) {
                 const Pack<T, VW> pv = ldp<T, VW>(pinv + o);
@@ -477,7 +478,7 @@ __global__ __launch_bounds__(KB) void k_update(const T* __restrict__ V, long lon
     }
 }
 
-// w = V y, z = pinv w
+// w = V y, z = pinv w (z null: skipped)
 template <typename T>
 __global__ __launch_bounds__(KB) void k_combine(const T* __restrict__ V, long long ld, int k,
                                                 const double* __restrict__ y, const T* __restrict__ pinv,
@@ -489,7 +490,7 @@ __global__ __launch_bounds__(KB) void k_combine(const T* __restrict__ V, long lo
     for (int j = 0; j < k; ++j) s = fma(y[j], (double)V[j * ld + i], s);
     const T t = (T)s;
     w[i] = t;
-    z[i] = t * pinv[i];
+    if (z) z[i] = t * pinv[i];
 }
 
 // x += y

@@ -24,7 +24,7 @@ struct KrOut {
 //     nrm2[0] = ||w - V h1||^2, vnext = (w - V h1) / sqrt(nrm2[0]), w untouched;
 //   else: w <- w - V h1, h2[0..k) = V^T w, h2[k] = ||w||^2,
 //     nrm2[0] = ||w - V h2||^2, vnext = (w - V h2) / sqrt(nrm2[0]);
-//   (vnext = 0 if nrm2[0] is 0), z = P^-1 vnext.  The Hessenberg column is h1 + h2.
+//   (vnext = 0 if nrm2[0] is 0), z = P^-1 vnext (model 0: z null, skipped).  The Hessenberg column is h1 + h2.
 //   part: (k + 1) * krylov_blocks(n) doubles.  Returns -1 (nothing launched) for k
 //   outside 1..KR_MAXK.
 template <typename T>
@@ -44,7 +44,7 @@ void kr_normalize_prec(int model, const T* w, const double* nrm2, T* v, T* z, co
 template <typename T>
 void kr_update(int model, const T* V, long long ld, int k, const double* y, const T* pinv, T* x,
                long long N, hipStream_t s, int tr = 0);
-// w = V y, z = pinv w (n entries, point preconditioner)
+// w = V y, z = pinv w (n entries, point preconditioner; z null: skipped)
 template <typename T>
 void kr_combine(const T* V, long long ld, int k, const double* y, const T* pinv, T* w, T* z, long long n,
                 hipStream_t s);

@@ -271,12 +271,18 @@ struct LinOp {
     // two iterates stand in z0 and zb or in c and d (needed from the third pass on, and from
     // the second if w is null); the steps are spread evenly over as few passes as hold them.
     bool fuses() const { return g.dim == 2 && !(schur && trans) && g.n[1] > pfk::CHEB_MAXS; }
+    // passes of poly_fused with or without the product (0: it does not apply)
+    int fused_passes(bool product, bool scratch) const
+    {
+        if (!fuses() || cheb.deg < 2) return 0;
+        const int n = cheb.deg - 1 + (product ? 1 : 0), top = schur ? pfk::CHEB_MAXS / 2 : pfk::CHEB_MAXS;
+        const int passes = (n + top - 1) / top;
+        return passes > (product ? 2 : 1) && !scratch ? 0 : passes;
+    }
     T* poly_fused(const T* v, T* z0, T* w, T* c, T* d, hipStream_t s) const
     {
-        if (!fuses()) return nullptr;
-        const int n = cheb.deg - 1 + (w ? 1 : 0), top = schur ? pfk::CHEB_MAXS / 2 : pfk::CHEB_MAXS;
-        const int passes = (n + top - 1) / top;
-        if (cheb.deg < 2 || (passes > (w ? 2 : 1) && !(c && d))) return nullptr;
+        const int passes = fused_passes(w != nullptr, c && d), n = cheb.deg - 1 + (w ? 1 : 0);
+        if (passes == 0) return nullptr;
         T *in[2] = {nullptr, nullptr}, *nx[2] = {z0, zb};
         double rho = cheb.delta / cheb.theta;
         for (int i = 0, k = 0; i < passes; ++i) {
@@ -445,7 +451,9 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
             if (!std::isfinite(beta)) return fail(PF_ENONFINITE, "GMRES residual is not finite");
             if (beta <= tol_abs || total >= max_its) break;
         }
-        pfk::kr_normalize_prec<T>(model, first ? b : L.w, dnrm, L.V, L.z, pinv, Nn, 1.0, s, tr);
+        // (a fused polynomial forms P^-1 v itself)
+        auto z_of = [&](int i) { return A.fused_passes(true, i + 2 <= MAXM) ? nullptr : L.z; };
+        pfk::kr_normalize_prec<T>(model, first ? b : L.w, dnrm, L.V, z_of(0), pinv, Nn, 1.0, s, tr);
         first = false;
         std::fill(gv.begin(), gv.end(), 0.0);
         gv[0] = beta;
@@ -457,7 +465,7 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
             if (!A.poly_fused(vi, L.z, L.w, sc, sc ? sc + L.ld : nullptr, s)) A.apply(A.poly(vi, L.z, s), L.w, s);
             double* slot = rb->host_dev + (i & 1) * DEV_Y;
             const pfk::KrOut out{dh1, dh2, dnrm, slot + DEV_H1, slot + DEV_H2, slot + DEV_NRM};
-            if (pfk::kr_cgs2<T>(model, L.V, L.ld, i + 1, L.w, L.V + (long long)(i + 1) * L.ld, L.z, pinv,
+            if (pfk::kr_cgs2<T>(model, L.V, L.ld, i + 1, L.w, L.V + (long long)(i + 1) * L.ld, z_of(i + 1), pinv,
                                 Nn, L.part, out, s, tr))
                 return fail(PF_EINVAL, "Gram-Schmidt basis of %d vectors", i + 1);
             if (hipEventRecord(rb->ev[i & 1], s) != hipSuccess) return check_launch("GMRES column readback");
@@ -515,7 +523,8 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
             if (hipMemcpyAsync(dy, rb->y(), (size_t)j * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess)
                 return check_launch("GMRES solution coefficients");
             if (A.cheb.deg > 1) {
-                pfk::kr_combine<T>(L.V, L.ld, j, dy, pinv, L.w, L.z, n, s);  // w = V y, z = pinv w
+                // w = V y, z = pinv w
+                pfk::kr_combine<T>(L.V, L.ld, j, dy, pinv, L.w, A.fused_passes(false, true) ? nullptr : L.z, n, s);
                 // (the basis is made anew on the next cycle: scratch)
                 const T* z = A.poly_fused(L.w, L.z, nullptr, L.V, L.V + L.ld, s);
                 pfk::kr_add<T>(L.x, z ? z : A.poly(L.w, L.z, s), n, s);

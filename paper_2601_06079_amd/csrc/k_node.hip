@@ -101,6 +101,68 @@ __global__ __launch_bounds__(256) void k_prec_schur(const T* __restrict__ U, T* 
     pinv[idx] = (T)bfactor<D>(g, i, j, k) / (theta * d);
 }
 
+// What the Chebyshev polynomial needs to know of the field: an upper bound of the
+// preconditioned operator's spectrum (see launch_spectrum), one maximum per block of 256
+// nodes.  Bound by its Gauss points, as k_prec is.
+struct SpecCoef {
+    double a;           // inv_dt m
+    double jn;          // |J| times the mobility (nodal: m)
+    double kd, km;      // the stiffness: diagonal, and the diagonal that bounds it from above
+    double cn, cm;      // Cahn-Hilliard: of f'' in the diagonal, and in the bound
+};
+
+template <typename T, int D, int MODEL>
+__global__ __launch_bounds__(256) void k_spectrum(const T* __restrict__ U, double* __restrict__ part, Geom g,
+                                                  Lin<T> F, SpecCoef c)
+{
+    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    int i, j, k;
+    double hi = 0.0;
+    if (node_of<D>(g, idx, i, j, k)) {
+        T u[NB<D>::K];
+        gather<T, D>(U, g, i, j, k, u);
+        double top, diag;
+        if constexpr (MODEL == 0) {
+            T np = F(u[NB<D>::K / 2], (T)1), nd = np;
+            if (!g.quad) nd = quad_sum_sq_pos<T, D>(u, F, np);
+            top = c.a + c.jn * (double)np + c.km;
+            diag = c.a + c.jn * (double)nd + c.kd;
+        } else {
+            T f = (T)0;
+#pragma unroll
+            for (int q = 0; q < NB<D>::K; ++q) f = max(f, F(u[q], (T)1));
+            const double d0 = c.a + c.kd;
+            top = c.a + c.km + c.cm * (double)f;
+            diag = max(d0 + c.cn * (double)F(u[NB<D>::K / 2], (T)1), 0.1 * d0);
+        }
+        hi = diag > 0.0 ? top / diag : (double)INFINITY;
+    }
+    for (int o = WAVE / 2; o > 0; o >>= 1) hi = max(hi, __shfl_down(hi, o, WAVE));
+    __shared__ double sh[256 / WAVE];
+    if (threadIdx.x % WAVE == 0) sh[threadIdx.x / WAVE] = hi;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 256 / WAVE; ++w) hi = max(hi, sh[w]);
+        part[blockIdx.x] = hi;
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_spectrum_max(const double* __restrict__ part, int nb,
+                                                       double* __restrict__ out)
+{
+    __shared__ double sh[1024];
+    double hi = 0.0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nb; i += 1024) hi = max(hi, part[i]);
+    sh[threadIdx.x] = hi;
+    __syncthreads();
+    for (int st = 512; st > 0; st >>= 1) {
+        if ((int)threadIdx.x < st) sh[threadIdx.x] = max(sh[threadIdx.x], sh[threadIdx.x + st]);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) __hip_atomic_store(out, sh[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // y = scale 2^b x (2^b: the boundary factor of the node's rows)
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_unrow(const T* __restrict__ x, T* __restrict__ y, Geom g, T scale)
@@ -518,6 +580,37 @@ void launch_prec_schur(const Geom& g, const FreeEnergy& f, double kappa, double 
 }
 
 template <typename T>
+bool launch_spectrum(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double inv_dt,
+                     const T* U, double* part, long long part_max, double* out, hipStream_t s)
+{
+    const long long nb = (g.N + 255) / 256;
+    if (nb > part_max || nb > (1ll << 30)) return false;
+    const double m = std::pow(g.h, g.dim), hk = g.dim == 3 ? g.h : 1.0;
+    const StencilDiag d = stencil_diag(g);
+    const Lin<T> F{(T)f.b0, (T)f.b1, (T)f.b2};
+    SpecCoef c{};
+    c.a = inv_dt * m;
+    if (model == 0) {
+        c.jn = mob * (g.quad ? m : std::pow(0.5 * g.h, g.dim));
+        c.kd = mob * kappa * d.kd * hk;
+        c.km = mob * kappa * d.kmax * hk;
+    } else {
+        c.kd = mob / m * kappa * d.kk * hk * hk;
+        c.km = mob / m * kappa * d.kmax * d.kmax * hk * hk;
+        c.cn = mob * d.km * hk;
+        c.cm = mob * d.kmmax * hk;
+    }
+    DIM_SWITCH(g, {
+        if (model == 0)
+            k_spectrum<T, D, 0><<<(unsigned)nb, 256, 0, s>>>(U, part, g, F, c);
+        else
+            k_spectrum<T, D, 1><<<(unsigned)nb, 256, 0, s>>>(U, part, g, F, c);
+    });
+    k_spectrum_max<<<1, 1024, 0, s>>>(part, (int)nb, out);
+    return true;
+}
+
+template <typename T>
 void launch_unrow(const Geom& g, double scale, const T* x, T* y, hipStream_t s)
 {
     DIM_SWITCH(g, { k_unrow<T, D><<<grid_for(g), 256, 0, s>>>(x, y, g, (T)scale); });
@@ -588,6 +681,8 @@ void launch_energy(const Geom& g, const FreeEnergy& f, double kappa, const T* c,
                                  const T*, T*, hipStream_t, double);                              \
     template void launch_prec_schur<T>(const Geom&, const FreeEnergy&, double, double, double, double, const T*, \
                                        T*, hipStream_t);                                          \
+    template bool launch_spectrum<T>(const Geom&, int, const FreeEnergy&, double, double, double, const T*, \
+                                     double*, long long, double*, hipStream_t);                    \
     template void launch_unrow<T>(const Geom&, double, const T*, T*, hipStream_t);                 \
     template void launch_chem<T>(const Geom&, const FreeEnergy&, double, const T*, T*, hipStream_t); \
     template void launch_ch_update<T>(const Geom&, double, const T*, const T*, T*, hipStream_t);   \

@@ -158,24 +158,39 @@ template <typename T>
 void launch_prec(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,
                  double inv_dt, const T* U, T* pinv, hipStream_t s, double theta = 1.0);
 // Centre entries and sums of products of the unit Q1 stencils: K_aa, the diagonals of
-// K K and of K M (M the Gauss-integrated mass over m), and the largest symbol of K;
-// 2-D h-free, 3-D per h (K K: per h^2)
-struct StencilDiag { double kd, kk, km, kmax; };
+// K K and of K M (M the Gauss-integrated mass over m), and the largest symbols of K and
+// K M; 2-D h-free, 3-D per h (K K: per h^2)
+struct StencilDiag { double kd, kk, km, kmax, kmmax; };
 inline StencilDiag stencil_diag(const Geom& g)
 {
     // nodal: 5/7-point K, M the identity.  Gauss: 2-D entries 8/3, -1/3 (8 neighbours) and
     // mass (4 1 4 1 16 ...)/36; 3-D entries 8/3, 0 (faces), -1/6 (12 edges), -1/12 (8
     // corners) and mass 8/27, 2/27, 1/54, 1/216; the symbol is largest at one axis' Nyquist
-    // wave (4), nodal at all of them (8 / 12)
-    if (g.quad) return g.dim == 2 ? StencilDiag{4.0, 20.0, 4.0, 8.0} : StencilDiag{6.0, 42.0, 6.0, 12.0};
-    return g.dim == 2 ? StencilDiag{8.0 / 3.0, 8.0, 1.0, 4.0}
-                      : StencilDiag{8.0 / 3.0, 7.5, 8.0 / 3.0 * 8.0 / 27.0 - 2.0 / 54.0 - 8.0 / 12.0 / 216.0, 4.0};
+    // wave (4), nodal at all of them (8 / 12); that of K M at a wave of three nodes along one
+    // axis (3 / 2)
+    if (g.quad) return g.dim == 2 ? StencilDiag{4.0, 20.0, 4.0, 8.0, 8.0} : StencilDiag{6.0, 42.0, 6.0, 12.0, 12.0};
+    return g.dim == 2 ? StencilDiag{8.0 / 3.0, 8.0, 1.0, 4.0, 1.5}
+                      : StencilDiag{8.0 / 3.0, 7.5, 8.0 / 3.0 * 8.0 / 27.0 - 2.0 / 54.0 - 8.0 / 12.0 / 216.0, 4.0, 1.5};
 }
 
 // 1 / (theta diag S) of the Cahn-Hilliard Newton system with mu eliminated (N values)
 template <typename T>
 void launch_prec_schur(const Geom& g, const FreeEnergy& f, double kappa, double mob, double inv_dt, double theta,
                        const T* U, T* pinv, hipStream_t s);
+// out[0] (device or mapped) = an upper bound of the spectrum of D^-1 J, J the Allen-Cahn
+// Newton system at U (lumped mass) and D its diagonal.  K <= (kmax / kd) diag K, and a
+// Gauss point's share |J| f'' phi phi^T of N' is at most |J| max(f'', 0) diag phi (the
+// phi sum to 1), so J <= the diagonal of
+//   inv_dt m + L [sum_e sum_q |J| max(f''(u_q), 0) phi_a(q) + kappa (kmax / kd) K_aa]
+// and the bound is the largest quotient of that and D over the nodes, for any field.
+// (Nodal quadrature: N' is diagonal and stands in both.)
+// Cahn-Hilliard with mu eliminated: the same quotient of the largest symbols over
+// launch_prec_schur's diagonal, f'' the largest at the node and its neighbours: what the
+// short waves see where f'' varies over more than one node, an estimate elsewhere.
+// part: at most part_max doubles.  False (nothing launched) where they do not suffice.
+template <typename T>
+bool launch_spectrum(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double inv_dt,
+                     const T* U, double* part, long long part_max, double* out, hipStream_t s);
 // y = scale 2^b x over the nodes (b boundary faces of a no-flux grid)
 template <typename T>
 void launch_unrow(const Geom& g, double scale, const T* x, T* y, hipStream_t s);

@@ -97,6 +97,7 @@ struct ColReadback {
     }
 };
 constexpr size_t RB_DOUBLES = 2 * DEV_Y + MAXM + 8;
+constexpr int SCAL_SPEC = 6;  // of the scalars: the spectrum's bound (before it the norms and the CG's)
 
 ColReadback col_readback(const pf_ctx* ctx)
 {
@@ -197,6 +198,7 @@ bool poly_ok(const pf_problem* p, const pfk::Geom& g, const Opts& o)
 struct Cheb {
     int deg = 1;
     double theta = 1.0, delta = 0.0;
+    double rate = 0.0;  // log of the residual reduction an Arnoldi step should give
 };
 
 // The linear operator handed to GMRES: J = dR/dU at U (or its transpose), or, for
@@ -409,11 +411,15 @@ struct LinOp {
 // Solve J x = b (L.x overwritten, starting from 0; n unknowns) to ||b - J x|| <= tol_abs.
 // The preconditioner (if any) must already be in L.pinv.  Returns PF status;
 // *its receives the dimension of the Krylov space in J searched (Arnoldi steps, each
-// counting the polynomial's degree), *res the last residual estimate.
+// counting the polynomial's degree), *res the last residual estimate.  A polynomial under
+// which ten Arnoldi steps in a row give less than a quarter of the reduction its interval
+// promises is dropped: its interval does not hold the spectrum, and the diagonal alone
+// (a constant factor in it does not matter to GMRES) goes on from the residual reached.
 template <typename T>
-int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long long n, int m, int max_its, bool prec,
+int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n, int m, int max_its, bool prec,
           double bnorm, double tol_abs, int* its, double* res, hipStream_t s)
 {
+    constexpr int JUDGE = 10;
     // grain growth and the eliminated Cahn-Hilliard system: point Jacobi over all n unknowns
     // (the Krylov kernels' point model)
     const bool point = A.p->model == PF_GRAIN || A.schur;
@@ -432,6 +438,8 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
     int total = 0;
     double beta = bnorm;
     bool first = true;
+    int judged = 0;           // Arnoldi steps since the polynomial was last judged
+    double res_then = bnorm;  // and the residual there
     *res = bnorm;
     if (bnorm <= tol_abs) {
         *its = 0;
@@ -472,7 +480,7 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
             return PF_OK;
         };
         int j = 0;
-        bool done = false;
+        bool done = false, stuck = false;
         const int deg = A.cheb.deg;  // products with J per Arnoldi step
         const int steps = std::min(m, (max_its - total + deg - 1) / deg);
         if (steps > 0)
@@ -497,8 +505,13 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
                 hipStreamSynchronize(s);
                 return fail(PF_ENONFINITE, "GMRES Hessenberg is not finite");
             }
-            cs[j] = rr > 0.0 ? a / rr : 1.0;
-            sn[j] = rr > 0.0 ? bb / rr : 0.0;
+            if (rr == 0.0) {  // J maps this direction to nothing new: the residual stays
+                *res = std::fabs(gv[j]);
+                done = true;
+                break;
+            }
+            cs[j] = a / rr;
+            sn[j] = bb / rr;
             H[j * MAXM + j] = rr;
             H[(j + 1) * MAXM + j] = 0.0;
             gv[j + 1] = -sn[j] * gv[j];
@@ -508,6 +521,15 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
                 ++j;
                 done = true;
                 break;
+            }
+            if (deg > 1 && ++judged == JUDGE) {
+                stuck = std::log(res_then / *res) < 0.25 * JUDGE * A.cheb.rate;
+                judged = 0;
+                res_then = *res;
+                if (stuck) {
+                    ++j;
+                    break;
+                }
             }
         }
         // y = H^-1 g (upper triangular j x j), x += P^-1 V y
@@ -533,6 +555,7 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
             }
         }
         if (done || total >= max_its) break;
+        if (stuck) A.cheb = Cheb{};
     }
     *its = total;
     return check_launch("gmres");
@@ -544,7 +567,9 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
 // a symmetric operator whose eigenvalues are at least m/dt - M W^2 m / (4 kappa) (the
 // smallest value of k (kappa k - W m) M / m over the stiffness's eigenvalues k >= 0).
 // Elsewhere, and where the diagonal alone needs few iterations, the degree is 1.
-// The upper end is the largest symbol of K (of K K for S) over its diagonal, 5% added.
+// The upper end is launch_spectrum's bound at the field (Allen-Cahn 1% added for rounding;
+// S, where it is an estimate, 5%): beyond the interval the polynomial grows with the
+// degree's power, and f'' has no upper limit of its own.
 // Degree: the diagonal alone would take about P = sqrt(hi / lo) ln(2 / lin) / 2 products;
 // a product in the polynomial costs two to three vectors less than the Gram-Schmidt
 // sweeps of one more basis vector, so the basis is kept to about six vectors and the
@@ -555,32 +580,72 @@ int gmres(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, const T* b, long 
 // Allen-Cahn 19.1 / 6.1, 500 x 420 Cahn-Hilliard 15.4 / 7.2, 128^3 Cahn-Hilliard 5.8 / 4.1;
 // several products a pass, six vectors against four: 2048^2 Allen-Cahn 4.4 / 3.9, 1024^2
 // 1.50 / 1.40 (FP64 1.68 / 1.59), 500^2 1.05 / 0.84, 300^2 Cahn-Hilliard 2.18 / 2.12.
+struct Interval {
+    double lo = 0.0, hi = 0.0;
+};
+// without what the field adds to the upper end
 template <typename T>
-Cheb choose_cheb(const LinOp<T>& A, double lin)
+Interval base_interval(const LinOp<T>& A)
 {
     const pf_problem* p = A.p;
     const pfk::StencilDiag d = pfk::stencil_diag(A.g);
-    const double m = A.mass(), hk = A.g.dim == 3 ? A.g.h : 1.0, L = p->mobility;
+    const double m = A.mass(), hk = A.g.dim == 3 ? A.g.h : 1.0, mob = p->mobility;
+    if (!(mob > 0.0) || !(p->kappa > 0.0) || !(p->W >= 0.0)) return {};
+    if (A.schur)
+        return {(A.inv_dt - mob * p->W * p->W / (4.0 * p->kappa)) * m /
+                    (A.inv_dt * m + mob * p->kappa / m * d.kk * hk * hk),
+                d.kmax * d.kmax / d.kk};
+    return {(A.inv_dt - mob * p->W) * m / (A.inv_dt * m + mob * p->kappa * d.kd * hk), d.kmax / d.kd};
+}
+template <typename T>
+int cheb_degree(const LinOp<T>& A, const Interval& v, double lin)
+{
+    if (!(v.lo > 0.0) || !(v.lo < v.hi) || !std::isfinite(v.hi)) return 1;
+    const double products = 0.5 * std::sqrt(v.hi / v.lo) * std::log(2.0 / lin);
+    const int top = A.fuses() ? 20 : 10;
+    return (int)std::lround(std::min(products / (A.fuses() ? 4.0 : 6.0), (double)top));
+}
+// Whether a solve to lin may take a polynomial, and the field's part of the interval is to
+// be found (launch_spectrum): whatever it adds, a solve of few products stays one.
+template <typename T>
+bool may_take_cheb(const LinOp<T>& A, double lin)
+{
+    return cheb_degree<T>(A, base_interval<T>(A), lin) > 1;
+}
+template <typename T>
+bool queue_spectrum(const ColReadback* rb, const LinOp<T>& A, const NWS<T>& L, hipStream_t s)
+{
+    const pf_problem* p = A.p;
+    return pfk::launch_spectrum<T>(A.g, p->model, A.f, p->kappa, p->mobility, A.inv_dt, A.U, L.part, L.part_len,
+                                   rb->scal_dev() + SCAL_SPEC, s);
+}
+// The bound is found once for a Newton step and holds while the field moves little: where
+// f'' has changed by at most df, a quotient over the nodes grows from q to (q + r) / (1 - r)
+// at most, with r the share of df in the smallest diagonal.
+template <typename T>
+double spectrum_drift(const LinOp<T>& A, double df)
+{
+    const pf_problem* p = A.p;
+    const pfk::StencilDiag d = pfk::stencil_diag(A.g);
+    const double m = A.mass(), hk = A.g.dim == 3 ? A.g.h : 1.0, mob = p->mobility;
+    if (A.schur) return mob * d.kmmax * hk * df / (A.inv_dt * m + mob / m * p->kappa * d.kk * hk * hk);
+    return mob * m * df / ((A.inv_dt - mob * p->W) * m + mob * p->kappa * d.kd * hk);
+}
+constexpr double DRIFT_MAX = 0.02;  // beyond it the bound is found anew
+
+// bound: what queue_spectrum left (after a wait)
+template <typename T>
+Cheb choose_cheb(const LinOp<T>& A, double lin, double bound)
+{
+    Interval v = base_interval<T>(A);
+    v.hi = bound * (A.schur ? 1.05 : 1.01);
+    const int deg = cheb_degree<T>(A, v, lin);
     Cheb c;
-    if (!(L > 0.0) || !(p->kappa > 0.0) || !(p->W >= 0.0)) return c;
-    double lo, hi;
-    if (A.schur) {
-        lo = (A.inv_dt - L * p->W * p->W / (4.0 * p->kappa)) * m / (A.inv_dt * m + L * p->kappa / m * d.kk * hk * hk);
-        hi = std::max(1.0, d.kmax * d.kmax / d.kk);
-    } else {
-        lo = (A.inv_dt - L * p->W) * m / (A.inv_dt * m + L * p->kappa * d.kd * hk);
-        // (a mode of the nonlinear term alone, f'' up to 3 W, has (1 + 3 dt L W) over its diagonal)
-        const double w = 3.0 * L * p->W / A.inv_dt, wd = A.g.quad ? 1.0 : A.g.dim == 2 ? 4.0 / 9.0 : 8.0 / 27.0;
-        hi = std::max(d.kmax / d.kd, (1.0 + w) / (1.0 + w * wd));
-    }
-    hi *= 1.05;
-    if (!(lo > 0.0) || !(lo < hi)) return c;
-    const double products = 0.5 * std::sqrt(hi / lo) * std::log(2.0 / lin);
-    const int deg = (int)std::lround(products / (A.fuses() ? 4.0 : 6.0));
     if (deg < 2) return c;
-    c.deg = std::min(deg, lin > 3e-3 ? 2 : A.fuses() ? 20 : 10);
-    c.theta = 0.5 * (hi + lo);
-    c.delta = 0.5 * (hi - lo);
+    c.deg = lin > 3e-3 ? 2 : deg;
+    c.theta = 0.5 * (v.hi + v.lo);
+    c.delta = 0.5 * (v.hi - v.lo);
+    c.rate = std::min(0.5, 2.0 * c.deg * std::sqrt(v.lo / v.hi));
     return c;
 }
 
@@ -677,6 +742,13 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
     pf_newton_report R{};
     const ColReadback rbv = col_readback(ctx);
     const ColReadback* rb = &rbv;
+    LinOp<T> A{p, g, f, inv_dt, U, 0};
+    A.schur = schur_ok<T>(p, g, o);
+    A.pinv = L.pinv;
+    A.zb = A.schur ? L.R + g.N : L.R;
+    A.tmp = L.z + g.N;  // (with mu eliminated the solver's vectors fill half their space)
+    bool poly = (A.schur || poly_ok<T>(p, g, o)) && may_take_cheb<T>(A, o.lmin);
+    double bound = -1.0, moved = 0.0;  // of the spectrum (not found yet); the change of f'' since
     // ||R(U)||, read back together with whatever scalars were queued before it
     auto residual_norm = [&](double* out) -> int {
         if (p->model == PF_COUPLED)
@@ -686,8 +758,11 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
                                      inv_dt);
         else
             pfk::launch_residual<T>(g, p->model, f, p->kappa, p->mobility, U, L.R, s, Uold, inv_dt);
+        const bool spec = poly && bound < 0.0;
+        if (spec) poly = queue_spectrum<T>(rb, A, L, s);
         pfk::kr_norm2<T>(L.R, nullptr, n, L.part, dnrm, s, rb->scal_dev());
         if (int rc = rb->wait_scalars(s)) return rc;
+        if (spec) bound = rb->scal()[SCAL_SPEC];
         *out = std::sqrt(rb->scal()[0]);
         return PF_OK;
     };
@@ -701,12 +776,6 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
         R.reason = -2;
         status = fail(PF_ENONFINITE, "initial residual is not finite");
     }
-    LinOp<T> A{p, g, f, inv_dt, U, 0};
-    A.schur = schur_ok<T>(p, g, o);
-    const bool poly = A.schur || poly_ok<T>(p, g, o);
-    A.pinv = L.pinv;
-    A.zb = A.schur ? L.R + g.N : L.R;
-    A.tmp = L.z + g.N;  // (with mu eliminated the solver's vectors fill half their space)
     int k = 0;
     double dmax = 0.0, umax = 0.0;
     while (status == PF_OK) {
@@ -732,7 +801,17 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
         // correction beyond lin_rtol_max would resolve only noise
         double lin = std::min(o.lmax, std::max({o.lmin, 0.1 * rk / r0, 0.01 * std::max(o.rtol * r0, o.atol) / rk}));
         if (o.stagnation && k >= 3 && rk > 10.0 * (lres + rprev * rprev * (rprev / (rprev2 * rprev2)))) lin = o.lmax;
-        A.cheb = poly ? choose_cheb<T>(A, lin) : Cheb{};
+        A.cheb = Cheb{};
+        if (poly) {
+            double r = spectrum_drift<T>(A, moved);
+            if (!(r <= DRIFT_MAX)) {
+                if (queue_spectrum<T>(rb, A, L, s))
+                    if (int rc = rb->wait_scalars(s)) return rc;
+                bound = rb->scal()[SCAL_SPEC];
+                moved = r = 0.0;
+            }
+            A.cheb = choose_cheb<T>(A, lin, (bound + r) / (1.0 - r));
+        }
         if (o.precond == PF_PRECOND_JACOBI) {
             if (p->model == PF_COUPLED)
                 pfk::launch_cp_prec<T>(g, p->kappa, p->mobility, p->mobility_eta, inv_dt, U, L.pinv, s);
@@ -761,6 +840,7 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
         if (int rc = residual_norm(&rk)) return rc;
         dmax = rb->scal()[1];
         umax = rb->scal()[2];
+        moved += dmax * (std::fabs(f.b1) + std::fabs(f.b2) * (2.0 * umax + dmax));
         ++k;
         if (k <= 32) R.res_norm[k] = rk;
         if (!std::isfinite(rk)) {
@@ -859,7 +939,10 @@ int newton_adjoint_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T*
     At.zb = At.schur ? L.R + g.N : L.R;
     // the adjoint solve is taken to the field-precision floor, not an inexact-Newton tolerance
     const double lin = sizeof(T) == 4 ? 1e-6 : 1e-12;
-    if (At.schur || poly_ok<T>(p, g, o)) At.cheb = choose_cheb<T>(At, lin);
+    if ((At.schur || poly_ok<T>(p, g, o)) && may_take_cheb<T>(At, lin) && queue_spectrum<T>(&rbv, At, L, s)) {
+        if (int rc = rbv.wait_scalars(s)) return rc;
+        At.cheb = choose_cheb<T>(At, lin, rbv.scal()[SCAL_SPEC]);
+    }
     if (At.schur)
         pfk::launch_prec_schur<T>(g, f, p->kappa, p->mobility, inv_dt, At.cheb.theta, U, L.pinv, s);
     else if (o.precond == PF_PRECOND_JACOBI)
@@ -880,6 +963,10 @@ int newton_adjoint_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T*
                  : At.schur ? gmres_schur<T>(&rbv, At, L, o.m, o.max_its * 4, tol, &its, &res, s)
                             : gmres<T>(&rbv, At, L, L.b, n, o.m, o.max_its * 4, jac, bn, tol, &its, &res, s))
         return rc;
+    // a residual at the rounding floor, above the tolerance, is the best there is; one the
+    // solver did not bring down is no solution
+    if (!(res <= std::sqrt(lin) * bn))
+        return fail(PF_ENOCONV, "adjoint solve stopped after %d products at a relative residual of %.1e", its, res / bn);
     // Ubar (mass rows) += (m/dt) lambda ; theta_bar -= (dr/dtheta)^T lambda
     pfk::launch_mass_axpy<T>(g, inv_dt, L.x, Ubar, s);
     pfk::launch_dtheta<T>(g, p->model, f, p->kappa, p->mobility, U, L.x, -1.0, L.part, theta_bar, s);

@@ -218,6 +218,43 @@ __device__ __forceinline__ T quad_sum_sq(const T* u, Fn F)
     }
 }
 
+// The same, and in pos sum_q w_q max(F(u_q), 0): each point evaluated once
+template <typename T, int D, typename Fn>
+__device__ __forceinline__ T quad_sum_sq_pos(const T* u, Fn F, T& pos)
+{
+    const T w[4] = {(T)GM, (T)GP, (T)GP, (T)GM};
+    T sq = (T)0;
+    pos = (T)0;
+    T Xu[NB<D>::K / 3][4];
+#pragma unroll
+    for (int r = 0; r < NB<D>::K / 3; ++r) interp3to4(u[3 * r], u[3 * r + 1], u[3 * r + 2], Xu[r]);
+#pragma unroll
+    for (int qx = 0; qx < 4; ++qx) {
+        T Yu[NB<D>::K / 9][4];
+#pragma unroll
+        for (int c = 0; c < NB<D>::K / 9; ++c)
+            interp3to4(Xu[3 * c][qx], Xu[3 * c + 1][qx], Xu[3 * c + 2][qx], Yu[c]);
+#pragma unroll
+        for (int qy = 0; qy < 4; ++qy) {
+            if constexpr (D == 2) {
+                const T f = F(Yu[0][qy], (T)1), wt = w[qx] * w[qy];
+                sq = fmaT(wt * wt, f, sq);
+                pos = fmaT(wt, max(f, (T)0), pos);
+            } else {
+                T qu[4];
+                interp3to4(Yu[0][qy], Yu[1][qy], Yu[2][qy], qu);
+#pragma unroll
+                for (int qz = 0; qz < 4; ++qz) {
+                    const T f = F(qu[qz], (T)1), wt = w[qx] * w[qy] * w[qz];
+                    sq = fmaT(wt * wt, f, sq);
+                    pos = fmaT(wt, max(f, (T)0), pos);
+                }
+            }
+        }
+    }
+    return sq;
+}
+
 // sum_q w_q^2 F(u_q, v_q) over the 4^D points (w = phi of the centre node): the
 // diagonal entry of a two-field second-derivative operator (no |J|)
 template <typename T, int D, typename Fn>

@@ -1,0 +1,76 @@
+"""Newton steps and their adjoints at fields far outside the wells, where f'' has no upper
+limit (f'' = W (3 eta^2 - 1)): the polynomial preconditioner's interval has to hold the
+spectrum all the same, or its solves stagnate.
+
+Tolerances.  The adjoint is solved to a relative residual of 1e-12 (FP64) or 1e-6 (FP32).
+With |eta| between 1.2 and 4 the system's condition number is at most
+(1/dt + L W (3 16 - 1) + 8 L kappa / h^2) / (1/dt + L W) < 30, so its error is at most 3e-11
+and 3e-5; the bounds are ten times that, for rounding.  Steps: as for the other Newton
+tests, 1e-9 (rtol 1e-11) and 1e-5."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2601_06079_amd import _abi as A
+from paper_2601_06079_amd import inputs as I
+from paper_2601_06079_amd import solver as S
+from tests.gpu_util import announce, dev, host, pair, rel_l2, rounded
+
+pytestmark = pytest.mark.gpu
+
+F32, F64 = torch.float32, torch.float64
+GRIDS = [((32, 24), O.PERIODIC), ((29, 25), O.NOFLUX), ((10, 9, 8), O.PERIODIC), ((9, 10, 8), O.NOFLUX)]
+
+
+def setup(n, bc, base, amp, kappa, dtype):
+    g, o = pair(n, O.AC, O.F_SYM, dtype, h=1.0, W=1.0, kappa=kappa, mob=1.0, bc=bc)
+    return g, o, rounded(I.uniform_field(n, -amp, amp, seed=5, base=base), dtype)
+
+
+@pytest.mark.parametrize("dtype", [F64, F32])
+@pytest.mark.parametrize("base,amp,kappa,dt", [(1.8, 0.1, 0.1, 0.95), (1.8, 0.6, 0.05, 0.99), (3.0, 0.1, 0.1, 0.8),
+                                               (3.0, 0.6, 0.05, 0.95), (3.0, 0.1, 0.5, 0.95)])
+@pytest.mark.parametrize("n,bc", GRIDS)
+def test_adjoint_far_from_the_wells(n, bc, base, amp, kappa, dt, dtype):
+    announce("wide adjoint", n, bc, base, amp, kappa, dt, dtype)
+    g, o, U = setup(n, bc, base, amp, kappa, dtype)
+    v = rounded(np.random.default_rng(4).standard_normal(o.ndof), dtype)
+    ub, tb = torch.zeros(o.ndof, dtype=dtype, device="cuda"), torch.zeros(3, dtype=F64, device="cuda")
+    S.vjp(g, A.VJP_NEWTON_STEP, dt, dev(U, dtype), dev(v, dtype), ub, tb)
+    th, lam = O.newton_adjoint(o, dt, U, v, solver=0)
+    tol = 3e-10 if dtype == F64 else 3e-4
+    assert rel_l2(host(ub), lam) < tol
+    assert rel_l2(host(tb), th) < tol
+
+
+@pytest.mark.parametrize("dtype", [F64, F32])
+@pytest.mark.parametrize("base,amp,kappa,dt", [(1.8, 0.1, 0.1, 0.95), (3.0, 0.6, 0.1, 0.95), (0.0, 3.0, 0.1, 0.9)])
+@pytest.mark.parametrize("n,bc", GRIDS)
+def test_step_far_from_the_wells(n, bc, base, amp, kappa, dt, dtype):
+    announce("wide step", n, bc, base, amp, kappa, dt, dtype)
+    g, o, Uold = setup(n, bc, base, amp, kappa, dtype)
+    U = dev(Uold, dtype)
+    rep = S.newton_step(g, dt, dev(Uold, dtype), U, S.newton_opts(rtol=1e-11 if dtype == F64 else 1e-8))
+    assert rep.converged, rep
+    Uo, conv, _, _ = O.newton_be(o, dt, Uold, rtol=1e-13, maxit=40, solver=0)
+    assert conv
+    assert rel_l2(host(U), Uo) < (1e-9 if dtype == F64 else 1e-5)
+
+
+def test_unsolved_adjoint_is_an_error():
+    """Cahn-Hilliard noise at the unstable point with dt M W^2 = 25 kappa: hundreds of
+    eigenvalues on either side of zero, which no restarted solver gets through.  What it
+    leaves is not handed out as a gradient."""
+    n = (256, 256)
+    announce("unsolved adjoint")
+    g, _ = pair(n, O.CH, O.F_SYM, F32, h=1.0, W=1.0, kappa=2.0, mob=1.0)
+    c = I.uniform_field(n, -0.05, 0.05, seed=5, base=0.0)
+    U = dev(np.concatenate([c, np.zeros_like(c)]), F32)
+    S.step_explicit(g, U, 1e-6, 0)
+    v = np.random.default_rng(4).standard_normal(2 * c.size)
+    v[c.size:] = 0.0
+    ub, tb = torch.zeros(2 * c.size, dtype=F32, device="cuda"), torch.zeros(3, dtype=F64, device="cuda")
+    with pytest.raises(RuntimeError):
+        S.vjp(g, A.VJP_NEWTON_STEP, 50.0, U, dev(v, F32), ub, tb)
+    assert not ub.any() and not tb.any()

@@ -249,10 +249,21 @@ void launch_mass_axpy(const Geom& g, double inv_dt, const T* lam, T* ub, hipStre
 // 72 x 65 x 60 Cahn-Hilliard: 5 launches of 42 us (node-centric, every Gauss point 8 times
 // for each of two polynomials) -> 2 of 14 us.
 template <typename T>
+bool adjoint_marches(const Geom& g, int model, long long part_max)
+{
+    March<T> a, b;  // (no part: only whether the sums would fit)
+    a.part_max = part_max / 3;
+    b.part_max = part_max - part_max / 3;
+    return launch_march<T>(g, MOP_JVP, ME_ADJ, FreeEnergy{}, b, nullptr) &&
+           (model == 0 || launch_march<T>(g, MOP_STIFF, ME_ADJK, FreeEnergy{}, a, nullptr));
+}
+
+template <typename T>
 bool launch_adjoint_step(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double dt,
                          const T* U, const T* mu, const T* lam, T* lam_out, const T* add, T* t, double* part,
                          long long part_max, int fresh, hipStream_t s)
 {
+    if (!adjoint_marches<T>(g, model, part_max)) return false;
     const double m = std::pow(g.h, g.dim);
     const long long na = part_max / 3;
     March<T> a, b;
@@ -267,7 +278,6 @@ bool launch_adjoint_step(const Geom& g, int model, const FreeEnergy& f, double k
     b.fresh = fresh;
     b.scale = 1;
     b.rows = 1;
-    if (!launch_march<T>(g, MOP_JVP, ME_ADJ, f, b, s)) return false;  // would it fit
     if (model != 0) {
         a.v = lam;
         a.out = t;
@@ -316,7 +326,27 @@ __global__ __launch_bounds__(TB) void k_adjoint_theta(const double* __restrict__
         theta[2] += k.c[4] * sh[1][0];
     }
 }
+
+template <typename T>
+__global__ __launch_bounds__(AB) void k_zero(T* __restrict__ x, long long n)
+{
+    const long long i = (long long)blockIdx.x * AB + threadIdx.x;
+    if (i < n) x[i] = (T)0;
+}
+
+__global__ void k_add3(const double* __restrict__ x, double* __restrict__ y)
+{
+    if (threadIdx.x < 3) y[threadIdx.x] += x[threadIdx.x];
+}
 }  // namespace
+
+template <typename T>
+void launch_zero(T* x, long long n, hipStream_t s)
+{
+    k_zero<T><<<(unsigned)((n + AB - 1) / AB), AB, 0, s>>>(x, n);
+}
+
+void launch_add3(const double* x, double* y, hipStream_t s) { k_add3<<<1, WAVE, 0, s>>>(x, y); }
 
 template <typename T>
 void launch_adjoint_theta(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double dt,
@@ -345,15 +375,22 @@ void launch_vjp_explicit(const Geom& g, int model, const FreeEnergy& f, double k
                          double dt, const T* U, const T* vbar, T* ubar, T* scratch, double* part,
                          long long part_max, double* theta_bar, hipStream_t s)
 {
-    const double detJ = std::pow(0.5 * g.h, g.dim), m = std::pow(g.h, g.dim);
-    const unsigned nb = nblk(g);
     if (model != 0) launch_chem<T>(g, f, kappa, U, scratch, s);
     if (launch_adjoint_step<T>(g, model, f, kappa, mob, dt, U, scratch, vbar, ubar, ubar, scratch + g.N, part,
                                part_max, 1, s)) {
         launch_adjoint_theta<T>(g, model, f, kappa, mob, dt, part, part_max, theta_bar, s);
         return;
     }
-    // fields of 2 GiB and more: node-centric
+    launch_adjoint_nodes<T>(g, model, f, kappa, mob, dt, U, scratch, vbar, ubar, scratch + g.N, part, theta_bar, s);
+}
+
+template <typename T>
+void launch_adjoint_nodes(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double dt,
+                          const T* U, const T* mu, const T* vbar, T* ubar, T* t, double* part, double* theta_bar,
+                          hipStream_t s)
+{
+    const double detJ = std::pow(0.5 * g.h, g.dim), m = std::pow(g.h, g.dim);
+    const unsigned nb = nblk(g);
     const Lin<T> F2{(T)f.b0, (T)f.b1, (T)f.b2};
     if (model == 0) {
         DIM_SWITCH(g, {
@@ -363,8 +400,6 @@ void launch_vjp_explicit(const Geom& g, int model, const FreeEnergy& f, double k
         k_reduce3<<<1, AB, 0, s>>>(part, (int)nb, theta_bar);
         return;
     }
-    T* mu = scratch;
-    T* t = scratch + g.N;
     DIM_SWITCH(g, {
         k_vjp_ch_a<T, D><<<nb, AB, 0, s>>>(mu, vbar, t, g, (T)(dt / m), (T)mob, (T)(1.0 / m), part);
     });
@@ -387,8 +422,12 @@ void launch_vjp_explicit(const Geom& g, int model, const FreeEnergy& f, double k
     template bool launch_adjoint_step<T>(const Geom&, int, const FreeEnergy&, double, double, double, const T*, \
                                          const T*, const T*, T*, const T*, T*, double*, long long, int, \
                                          hipStream_t);                                           \
+    template bool adjoint_marches<T>(const Geom&, int, long long);                               \
     template void launch_adjoint_theta<T>(const Geom&, int, const FreeEnergy&, double, double, double, \
-                                          const double*, long long, double*, hipStream_t);
+                                          const double*, long long, double*, hipStream_t);       \
+    template void launch_adjoint_nodes<T>(const Geom&, int, const FreeEnergy&, double, double, double, const T*, \
+                                          const T*, const T*, T*, T*, double*, double*, hipStream_t); \
+    template void launch_zero<T>(T*, long long, hipStream_t);
 INST_ADJ(float)
 INST_ADJ(double)
 

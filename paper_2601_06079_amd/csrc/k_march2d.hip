@@ -164,7 +164,8 @@ bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
     const int nx = g.n[0], ny = g.n[1], outw = WAVE - 2 * H;
     if (ny < 2 * H) return false;
     const int nstrips = (nx + outw - 1) / outw;
-    const int tov = tune_stream2d_rows();
+    // (the adjoint's waves are the same in every call of a trajectory, whose sums they keep)
+    const int tov = epi < ME_ADJ ? tune_stream2d_rows() : 0;
     const int ty = tov > 0 ? std::min(tov, ny) : pass_rows(ny, nstrips, H, march2_cus(), epi < ME_ADJ);
     const long long nwaves = (long long)nstrips * ((ny + ty - 1) / ty);
     if (nwaves > (1ll << 30)) return false;

@@ -255,7 +255,10 @@ void launch_mass_axpy(const Geom& g, double inv_dt, const T* lam, T* ub, hipStre
 // Cahn-Hilliard: c planes, mu = [N + kappa K c] / m of U at mu): lam_out = S^T lam (+ add,
 // may be null), the theta sums of every wave added to part (set when fresh; at most
 // part_max doubles).  lam_out may be lam for Cahn-Hilliard only.  t: N values
-// (Cahn-Hilliard).  False (nothing launched) where it does not apply.
+// (Cahn-Hilliard).  False (nothing launched) where it does not apply: !adjoint_marches,
+// larger fields and grids so narrow that their waves' sums do not fit part.
+template <typename T>
+bool adjoint_marches(const Geom& g, int model, long long part_max);
 template <typename T>
 bool launch_adjoint_step(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double dt,
                          const T* U, const T* mu, const T* lam, T* lam_out, const T* add, T* t, double* part,
@@ -264,6 +267,16 @@ bool launch_adjoint_step(const Geom& g, int model, const FreeEnergy& f, double k
 template <typename T>
 void launch_adjoint_theta(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double dt,
                           const double* part, long long part_max, double* theta_bar, hipStream_t s);
+// The same step by the node kernels, for any field: ubar += S^T vbar, theta_bar += its
+// sums.  mu, t as above; part: 3 values per 256 nodes.
+template <typename T>
+void launch_adjoint_nodes(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double dt,
+                          const T* U, const T* mu, const T* vbar, T* ubar, T* t, double* part, double* theta_bar,
+                          hipStream_t s);
+// x[0..n) = 0, and y[0..3) += x[0..3) (kernels: their calls may be captured)
+template <typename T>
+void launch_zero(T* x, long long n, hipStream_t s);
+void launch_add3(const double* x, double* y, hipStream_t s);
 // one explicit step S at U: ubar += (dS/dU)^T vbar, theta_bar += (dS/dtheta)^T vbar
 // (Cahn-Hilliard: c planes only).  scratch: 2N values; part: part_max doubles.
 template <typename T>

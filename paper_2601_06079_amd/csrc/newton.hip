@@ -37,7 +37,8 @@ struct NWS {
     long long ld;
     double *part, *dev;  // dev: [h1(MAXM+1) | h2(MAXM+1) | nrm(2) | y(MAXM) | misc(8)]
     long long part_len;  // doubles in part
-    double* theta;       // device copy of a host theta_bar (pf_vjp with PF_VJP_THETA_HOST)
+    double* theta;       // device copy of a host theta_bar (pf_vjp with PF_VJP_THETA_HOST), or a
+                         // trajectory's sums (node kernels)
     size_t bytes;
 };
 
@@ -898,23 +899,36 @@ int vjp_trajectory_t(const pf_problem* p, double dt, int64_t nsteps, const T* st
     NWS<T> L = layout<T>(p, ws);
     const long long nd = ndof(p);
     const bool ch = p->model == PF_CAHN_HILLIARD;
-    T* other = L.V;       // Allen-Cahn: lam's second buffer
+    // the sums of a trajectory stay in part (marched, one or two a wave) or theta (node kernels)
+    const bool marched = pfk::adjoint_marches<T>(g, p->model, L.part_len);
+    T* other = L.V;       // lam's second buffer (marched Cahn-Hilliard: in place)
     T* t = L.V + L.ld;    // Cahn-Hilliard
     T* cur = lam;
     int fresh = flags & PF_VJP_BEGIN ? 1 : 0;
+    if (fresh && !marched) pfk::launch_zero<double>(L.theta, 3, s);
     for (int64_t k = nsteps - 1; k >= 0; --k) {
         const T* U = states + k * nd;
-        T* out = ch ? cur : (cur == lam ? other : lam);
-        if (!pfk::launch_adjoint_step<T>(g, p->model, f, p->kappa, p->mobility, dt, U, U + (ch ? g.N : 0), cur, out,
-                                         nullptr, t, L.part, L.part_len, fresh, s))
-            return fail(PF_EUNSUPPORTED, "explicit adjoint trajectory: fields of 2 GiB or more");
+        const T* mu = U + (ch ? g.N : 0);
+        T* out = ch && marched ? cur : (cur == lam ? other : lam);
+        if (marched) {
+            pfk::launch_adjoint_step<T>(g, p->model, f, p->kappa, p->mobility, dt, U, mu, cur, out, nullptr, t, L.part,
+                                        L.part_len, fresh, s);
+        } else {
+            pfk::launch_zero<T>(out, g.N, s);
+            pfk::launch_adjoint_nodes<T>(g, p->model, f, p->kappa, p->mobility, dt, U, mu, cur, out, t, L.part, L.theta,
+                                         s);
+        }
         cur = out;
         fresh = 0;
     }
     if (cur != lam && hipMemcpyAsync(lam, cur, (size_t)g.N * sizeof(T), hipMemcpyDeviceToDevice, s) != hipSuccess)
         return check_launch("adjoint copy-back");
-    if ((flags & PF_VJP_END) && !(fresh && nsteps == 0))
-        pfk::launch_adjoint_theta<T>(g, p->model, f, p->kappa, p->mobility, dt, L.part, L.part_len, theta_bar, s);
+    if ((flags & PF_VJP_END) && !(fresh && nsteps == 0)) {
+        if (marched)
+            pfk::launch_adjoint_theta<T>(g, p->model, f, p->kappa, p->mobility, dt, L.part, L.part_len, theta_bar, s);
+        else
+            pfk::launch_add3(L.theta, theta_bar, s);
+    }
     return check_launch("pf_vjp_explicit_trajectory");
 }
 

@@ -1,0 +1,89 @@
+"""The trajectory adjoint on grids so narrow that the sums of the marching kernels' waves do
+not fit the workspace, beside neighbours where they just do: against the oracle's discrete
+adjoint with the tolerances of the other trajectory tests (FP64 1e-10, FP32 1e-5), and in
+segments (bitwise)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2601_06079_amd import _abi as A
+from paper_2601_06079_amd import inputs as I
+from paper_2601_06079_amd import solver as S
+from tests.gpu_util import announce, dev, host, pair, rel_l2, rounded
+
+pytestmark = pytest.mark.gpu
+
+F32, F64 = torch.float32, torch.float64
+STEPS = 4
+
+
+def setup(n, model, bc, dtype):
+    g, o = pair(n, model, O.F_SYM if model == O.AC else O.F_01, dtype, h=0.9, W=1.2, kappa=0.7, mob=1.1, bc=bc)
+    c = I.uniform_field(n, -0.4, 0.4, seed=2, base=0.0 if model == O.AC else 0.5)
+    U0 = rounded(c if model == O.AC else np.concatenate([c, np.zeros(o.nnodes)]), dtype)
+    w = rounded(np.random.default_rng(3).standard_normal(o.ndof), dtype)
+    w[o.nnodes:] = 0.0
+    return g, o, U0, w
+
+
+@pytest.mark.parametrize("dtype", [F64, F32])
+@pytest.mark.parametrize("bc", [O.PERIODIC, O.NOFLUX])
+@pytest.mark.parametrize("model", [O.AC, O.CH])
+@pytest.mark.parametrize("n", [(2, 100), (2, 17), (5, 4, 12), (7, 9, 8), (2, 3, 40), (3, 2, 2), (2, 128, 96),
+                               (4, 64, 64)])
+def test_narrow_grids(n, model, bc, dtype):
+    announce("narrow trajectory", n, model, bc, dtype)
+    g, o, U0, w = setup(n, model, bc, dtype)
+    N, dt = o.nnodes, 0.01
+    states = torch.zeros((STEPS + 1, o.ndof), dtype=dtype, device="cuda")
+    states[0].copy_(dev(U0, dtype))
+    S.step_trajectory(g, states, dt)
+    ws = S.workspace(g, A.OP_VJP)
+    lam, tb = dev(w, dtype), torch.zeros(3, dtype=F64, device="cuda")
+    S.vjp_trajectory(g, states, lam, tb, dt, ws)
+    tref, uref = O.explicit_adjoint(o, dt, STEPS, U0, w[:N])
+    tol = 1e-10 if dtype == F64 else 1e-5
+    assert rel_l2(host(lam)[:N], uref) < tol
+    assert rel_l2(host(tb), tref) < tol
+    lam2, tb2 = dev(w, dtype), torch.zeros(3, dtype=F64, device="cuda")
+    S.vjp_trajectory(g, states[2:], lam2, torch.zeros_like(tb), dt, ws, begin=True, end=False)
+    S.vjp_trajectory(g, states[:3], lam2, tb2, dt, ws, begin=False, end=True)
+    assert torch.equal(lam, lam2) and torch.equal(tb, tb2)
+
+
+@pytest.mark.parametrize("model", [O.AC, O.CH])
+@pytest.mark.parametrize("n", [(2, 100), (7, 9, 8)])
+def test_narrow_checkpointed_run(n, model):
+    announce("narrow run", n, model)
+    g, o, U0, w = setup(n, model, O.PERIODIC, F64)
+    N, dt = o.nnodes, 0.01
+    th = torch.tensor([1.1, 0.7, 1.2], dtype=F64, requires_grad=True)
+    u = dev(U0, F64).requires_grad_(True)
+    U = S.checkpointed_run(th, u, g, dt, 6, 2)
+    (U[:N] * dev(w[:N], F64)).sum().backward()
+    tref, uref = O.explicit_adjoint(o, dt, 6, U0, w[:N])
+    assert rel_l2(host(u.grad)[:N], uref) < 1e-10 and rel_l2(host(th.grad), tref) < 1e-10
+
+
+def test_rows_set_by_hand_do_not_matter():
+    """The row count of the streaming kernels leaves the adjoint's waves as they are, so a
+    change between two segments does not mix up their sums."""
+    announce("narrow trajectory, rows set")
+    g, o, U0, w = setup((130, 61), O.AC, O.NOFLUX, F64)
+    dt = 0.01
+    states = torch.zeros((STEPS + 1, o.ndof), dtype=F64, device="cuda")
+    states[0].copy_(dev(U0, F64))
+    S.step_trajectory(g, states, dt)
+    ws = S.workspace(g, A.OP_VJP)
+    out = []
+    for rows in (0, 1):
+        lam, tb = dev(w, F64), torch.zeros(3, dtype=F64, device="cuda")
+        S.vjp_trajectory(g, states[2:], lam, tb, dt, ws, begin=True, end=False)
+        try:
+            S.tune_set(A.TUNE_STREAM2D_ROWS, rows)
+            S.vjp_trajectory(g, states[:3], lam, tb, dt, ws, begin=False, end=True)
+        finally:
+            S.tune_set(A.TUNE_STREAM2D_ROWS, 0)
+        out.append((lam, tb))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])

@@ -906,6 +906,7 @@ int vjp_trajectory_t(const pf_problem* p, double dt, int64_t nsteps, const T* st
     T* cur = lam;
     int fresh = flags & PF_VJP_BEGIN ? 1 : 0;
     if (fresh && !marched) pfk::launch_zero<double>(L.theta, 3, s);
+    if (fresh && marched && nsteps == 0) pfk::launch_zero<double>(L.part, L.part_len, s);  // (else the first step sets them)
     for (int64_t k = nsteps - 1; k >= 0; --k) {
         const T* U = states + k * nd;
         const T* mu = U + (ch ? g.N : 0);
@@ -923,7 +924,7 @@ int vjp_trajectory_t(const pf_problem* p, double dt, int64_t nsteps, const T* st
     }
     if (cur != lam && hipMemcpyAsync(lam, cur, (size_t)g.N * sizeof(T), hipMemcpyDeviceToDevice, s) != hipSuccess)
         return check_launch("adjoint copy-back");
-    if ((flags & PF_VJP_END) && !(fresh && nsteps == 0)) {
+    if (flags & PF_VJP_END) {
         if (marched)
             pfk::launch_adjoint_theta<T>(g, p->model, f, p->kappa, p->mobility, dt, L.part, L.part_len, theta_bar, s);
         else

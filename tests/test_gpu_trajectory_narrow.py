@@ -87,3 +87,28 @@ def test_rows_set_by_hand_do_not_matter():
             S.tune_set(A.TUNE_STREAM2D_ROWS, 0)
         out.append((lam, tb))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("model", [O.AC, O.CH])
+@pytest.mark.parametrize("n", [(64, 11), (2, 100)])
+def test_begin_without_steps(n, model):
+    """A first segment of no steps starts the sums like any other, whatever the workspace
+    held."""
+    announce("begin without steps", n, model)
+    g, o, U0, w = setup(n, model, O.PERIODIC, F64)
+    dt = 0.01
+    states = torch.zeros((STEPS + 1, o.ndof), dtype=F64, device="cuda")
+    states[0].copy_(dev(U0, F64))
+    S.step_trajectory(g, states, dt)
+    ws = S.workspace(g, A.OP_VJP)
+    lam, tb = dev(w, F64), torch.zeros(3, dtype=F64, device="cuda")
+    S.vjp_trajectory(g, states, lam, tb, dt, ws)
+    ws.fill_(0x41)
+    lam2, tb2 = dev(w, F64), torch.zeros(3, dtype=F64, device="cuda")
+    S.vjp_trajectory(g, states[STEPS:], lam2, tb2, dt, ws, begin=True, end=False)
+    S.vjp_trajectory(g, states, lam2, tb2, dt, ws, begin=False, end=True)
+    assert torch.equal(lam, lam2) and torch.equal(tb, tb2)
+    ws.fill_(0x41)
+    tb3 = torch.zeros(3, dtype=F64, device="cuda")
+    S.vjp_trajectory(g, states[STEPS:], lam2, tb3, dt, ws)
+    assert not tb3.any()

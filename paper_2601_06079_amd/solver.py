@@ -166,6 +166,11 @@ def newton_step(p: Problem, dt: float, U_old: torch.Tensor, U: torch.Tensor, opt
                         [rep.res_norm[i] for i in range(min(k, 32) + 1)])
 
 
+def _check_theta(theta_bar: torch.Tensor):
+    if theta_bar.dtype != torch.float64 or theta_bar.numel() != 3 or not theta_bar.is_contiguous():
+        raise ValueError("theta_bar must be a contiguous float64 tensor of 3 entries")
+
+
 def vjp(p: Problem, kind: int, dt: float, U: torch.Tensor, vbar: torch.Tensor,
         Ubar: torch.Tensor, theta_bar: torch.Tensor, ws: torch.Tensor = None,
         U_old: torch.Tensor = None):
@@ -174,8 +179,7 @@ def vjp(p: Problem, kind: int, dt: float, U: torch.Tensor, vbar: torch.Tensor,
     only) selects the backward-Euler residual M (U - U_old)/dt + r(U)."""
     if ws is None:
         ws = workspace(p, A.OP_VJP, U.device)
-    if theta_bar.dtype != torch.float64 or theta_bar.numel() != 3 or not theta_bar.is_contiguous():
-        raise ValueError("theta_bar must be a contiguous float64 tensor of 3 entries")
+    _check_theta(theta_bar)
     flags = 0 if theta_bar.is_cuda else A.VJP_THETA_HOST
     uold = None if U_old is None else _ptr(U_old, p, p.ndof, "U_old")
     A.check(A.lib().pf_vjp(A.ctx(), ct.byref(p.c()), int(kind), float(dt), _ptr(U, p, p.ndof, "U"),
@@ -195,7 +199,9 @@ def step_trajectory(p: Problem, states: torch.Tensor, dt: float):
 def vjp_trajectory(p: Problem, states: torch.Tensor, lam: torch.Tensor, theta_bar: torch.Tensor, dt: float,
                    ws: torch.Tensor, begin: bool = True, end: bool = True):
     """Adjoint of step_trajectory: lam (dO/d last state) becomes dO/d states[0]; the
-    gradient of theta accumulates in ws from begin and is added to theta_bar at end."""
+    gradient of theta accumulates in ws from begin and is added to theta_bar (float64[3], on
+    the device) at end."""
+    _check_theta(theta_bar)
     n = states.shape[0] - 1
     flags = (A.VJP_BEGIN if begin else 0) | (A.VJP_END if end else 0)
     A.check(A.lib().pf_vjp_explicit_trajectory(A.ctx(), ct.byref(p.c()), float(dt), n,

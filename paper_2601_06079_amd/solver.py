@@ -272,10 +272,12 @@ class CheckpointedRun(torch.autograd.Function):
                 _advance(q, U, dt, every, implicit, opts, ws)
         ctx.last = None
         if kept:
-            ctx.last = torch.empty((every + 1, U.numel()), dtype=q.dtype, device=U.device)
-            ctx.last[0].copy_(U)
-            step_trajectory(q, ctx.last, dt)
-            U = ctx.last[every].clone()
+            _ptr(U, q, q.ndof, "U")
+            last = torch.empty((every + 1, U.numel()), dtype=q.dtype, device=U.device)
+            last[0].copy_(U.view(-1))
+            step_trajectory(q, last, dt)
+            U.view(-1).copy_(last[every])
+            ctx.last = last
         ctx.q, ctx.dt, ctx.every, ctx.implicit, ctx.opts = q, dt, every, implicit, opts
         ctx.snaps, ctx.theta_device, ctx.traj = snaps, theta.device, traj
         return U
@@ -283,7 +285,7 @@ class CheckpointedRun(torch.autograd.Function):
     @staticmethod
     def backward(ctx, gU):
         q, dt, every, implicit = ctx.q, ctx.dt, ctx.every, ctx.implicit
-        lam = gU.detach().to(q.dtype).contiguous().clone()
+        lam = gU.detach().to(q.dtype).contiguous().clone().view(-1)
         N = q.nnodes
         if q.model == A.CAHN_HILLIARD and not implicit:
             lam[N:] = 0
@@ -297,16 +299,16 @@ class CheckpointedRun(torch.autograd.Function):
                     break  # no steps
                 if i < len(ctx.snaps):
                     states = seg
-                    states[0].copy_(ctx.snaps[i])
+                    states[0].copy_(ctx.snaps[i].view(-1))
                     step_trajectory(q, states, dt)
                 vjp_trajectory(q, states, lam, tb, dt, vws, begin=i == len(ctx.snaps), end=i == 0)
-            return tb.to(ctx.theta_device), lam, None, None, None, None, None, None
+            return tb.to(ctx.theta_device), lam.view(gU.shape), None, None, None, None, None, None
         ws = workspace(q, A.OP_NEWTON if implicit else A.OP_STEP_EXPLICIT, lam.device)
         seg = torch.empty((every + 1, lam.numel()), dtype=q.dtype, device=lam.device)
         Ubar = torch.empty_like(lam)
         kind = A.VJP_NEWTON_STEP if implicit else A.VJP_EXPLICIT_STEP
         for snap in reversed(ctx.snaps):
-            seg[0].copy_(snap)
+            seg[0].copy_(snap.view(-1))
             for k in range(every):  # seg[k + 1] = S(seg[k])
                 seg[k + 1].copy_(seg[k])
                 _advance(q, seg[k + 1], dt, 1, implicit, ctx.opts, ws)
@@ -315,7 +317,7 @@ class CheckpointedRun(torch.autograd.Function):
                 Ubar.zero_()
                 vjp(q, kind, dt, seg[k + 1] if implicit else seg[k], lam, Ubar, tb, vws)
                 lam, Ubar = Ubar, lam
-        return tb.to(ctx.theta_device), lam, None, None, None, None, None, None
+        return tb.to(ctx.theta_device), lam.view(gU.shape), None, None, None, None, None, None
 
 
 def _advance(q, U, dt, nsteps, implicit, opts, ws):

@@ -235,8 +235,8 @@ class CheckpointedRun(torch.autograd.Function):
     Eqs. II.5-II.6).
 
     theta = (mobility, kappa, W) as a float64 tensor of 3.  Forward keeps a
-    snapshot every `every` steps (explicit runs also the last segment's states);
-    backward walks the segments in reverse, recomputes each segment's states from
+    snapshot every `every` steps (explicit runs with keep also the last segment's
+    states, which the first backward takes over as its buffer); backward walks the segments in reverse, recomputes each segment's states from
     its snapshot (bitwise the forward's: every kernel is deterministic, and both
     passes advance with the same launches: fused launches are bitwise single steps
     on periodic grids, and no-flux grids, where a fused stage rounds the reflected
@@ -248,7 +248,7 @@ class CheckpointedRun(torch.autograd.Function):
     """
 
     @staticmethod
-    def forward(ctx, theta, U0, p, dt, nsteps, every, implicit, opts):
+    def forward(ctx, theta, U0, p, dt, nsteps, every, implicit, opts, keep=True):
         if nsteps % every:
             raise ValueError("nsteps must be a multiple of the checkpoint interval")
         th = theta.detach().to("cpu", torch.float64).numpy()
@@ -258,7 +258,7 @@ class CheckpointedRun(torch.autograd.Function):
         es = torch.empty((), dtype=q.dtype).element_size()
         traj = not implicit and q.model in (A.ALLEN_CAHN, A.CAHN_HILLIARD) and q.nnodes * es < 1 << 31
         nseg = nsteps // every
-        kept = 1 if traj and nseg else 0  # segments whose states are kept
+        kept = 1 if traj and nseg and keep else 0  # segments whose states are kept
         snaps = []
         if nseg > kept:
             ws = workspace(q, A.OP_NEWTON if implicit else A.OP_STEP_EXPLICIT, U.device)
@@ -270,14 +270,15 @@ class CheckpointedRun(torch.autograd.Function):
                     _advance(q, U, dt, 1, implicit, opts, ws)
             else:
                 _advance(q, U, dt, every, implicit, opts, ws)
-        ctx.last = None
+        ctx.last = []
         if kept:
             _ptr(U, q, q.ndof, "U")
+            snaps.append(U.clone())
             last = torch.empty((every + 1, U.numel()), dtype=q.dtype, device=U.device)
             last[0].copy_(U.view(-1))
             step_trajectory(q, last, dt)
             U.view(-1).copy_(last[every])
-            ctx.last = last
+            ctx.last.append(last)
         ctx.q, ctx.dt, ctx.every, ctx.implicit, ctx.opts = q, dt, every, implicit, opts
         ctx.snaps, ctx.theta_device, ctx.traj = snaps, theta.device, traj
         return U
@@ -292,17 +293,19 @@ class CheckpointedRun(torch.autograd.Function):
         tb = torch.zeros(3, dtype=torch.float64, device=lam.device)
         vws = workspace(q, A.OP_VJP, lam.device)
         if ctx.traj:
-            seg = torch.empty_like(ctx.last) if ctx.snaps else None
-            for i in range(len(ctx.snaps), -1, -1):
-                states = ctx.last
-                if states is None:
-                    break  # no steps
-                if i < len(ctx.snaps):
-                    states = seg
+            top = len(ctx.snaps) - 1
+            try:
+                states = ctx.last.pop()  # a later backward of the same graph forms it again
+                formed = top
+            except IndexError:
+                states = torch.empty((every + 1, lam.numel()), dtype=q.dtype, device=lam.device)
+                formed = top + 1
+            for i in range(top, -1, -1):
+                if i < formed:
                     states[0].copy_(ctx.snaps[i].view(-1))
                     step_trajectory(q, states, dt)
-                vjp_trajectory(q, states, lam, tb, dt, vws, begin=i == len(ctx.snaps), end=i == 0)
-            return tb.to(ctx.theta_device), lam.view(gU.shape), None, None, None, None, None, None
+                vjp_trajectory(q, states, lam, tb, dt, vws, begin=i == top, end=i == 0)
+            return tb.to(ctx.theta_device), lam.view(gU.shape), None, None, None, None, None, None, None
         ws = workspace(q, A.OP_NEWTON if implicit else A.OP_STEP_EXPLICIT, lam.device)
         seg = torch.empty((every + 1, lam.numel()), dtype=q.dtype, device=lam.device)
         Ubar = torch.empty_like(lam)
@@ -317,7 +320,7 @@ class CheckpointedRun(torch.autograd.Function):
                 Ubar.zero_()
                 vjp(q, kind, dt, seg[k + 1] if implicit else seg[k], lam, Ubar, tb, vws)
                 lam, Ubar = Ubar, lam
-        return tb.to(ctx.theta_device), lam.view(gU.shape), None, None, None, None, None, None
+        return tb.to(ctx.theta_device), lam.view(gU.shape), None, None, None, None, None, None, None
 
 
 def _advance(q, U, dt, nsteps, implicit, opts, ws):
@@ -332,4 +335,5 @@ def _advance(q, U, dt, nsteps, implicit, opts, ws):
 
 def checkpointed_run(theta, U0, p, dt, nsteps, every=100, implicit=False, opts=None):
     """Differentiable run of nsteps steps of problem p (see CheckpointedRun)."""
-    return CheckpointedRun.apply(theta, U0, p, dt, nsteps, every, implicit, opts)
+    keep = torch.is_grad_enabled() and (theta.requires_grad or U0.requires_grad)
+    return CheckpointedRun.apply(theta, U0, p, dt, nsteps, every, implicit, opts, keep)

@@ -1,5 +1,6 @@
 """Explicit checkpointed runs: what they accept (a field of the problem's type whose copy is
-contiguous, in any shape of its size)."""
+contiguous, in any shape of its size), the memory a run without a gradient
+takes, and a second backward of one graph (bitwise the first)."""
 import numpy as np
 import pytest
 import torch
@@ -53,3 +54,29 @@ def test_field_of_another_shape(nsteps, every):
         assert all(torch.equal(x, y) for x, y in zip(a, out[0]))
     tref, uref = O.explicit_adjoint(o, 0.01, nsteps, c, host(w))
     assert rel_l2(host(out[0][1]), uref) < 1e-10 and rel_l2(host(out[0][2]), tref) < 1e-10
+
+
+@pytest.mark.parametrize("model", [O.AC, O.CH])
+def test_second_backward(model):
+    announce("checkpointed twice", model)
+    g, o, c = problem(model=model)
+    U0 = c if model == O.AC else np.concatenate([c, np.zeros_like(c)])
+    w = dev(np.random.default_rng(1).standard_normal(o.ndof), F64)
+    th, u = theta(), dev(U0, F64).requires_grad_(True)
+    U = S.checkpointed_run(th, u, g, 0.01, 6, 2)
+    a = torch.autograd.grad((U * w).sum(), (th, u), retain_graph=True)
+    b = torch.autograd.grad((U * w).sum(), (th, u))
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+def test_run_without_a_gradient_keeps_no_states():
+    """50 steps in one segment: 51 states of 2 MB if they were kept, two or three if not."""
+    announce("checkpointed no grad")
+    g, o, c = problem((512, 512), F64)
+    U0 = dev(c, F64)
+    with torch.no_grad():
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        S.checkpointed_run(theta(), U0, g, 0.01, 50, 50)
+        assert torch.cuda.max_memory_allocated() - before < 6 * U0.numel() * 8

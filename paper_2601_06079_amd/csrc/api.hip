@@ -224,9 +224,7 @@ int step_explicit_t(const pf_problem* p, int cus, double dt, int64_t nsteps, T* 
         // the fewest launches of at most ks fused steps, of equal lengths to one step and an
         // even number of them, so that the last ends in the caller's array (a set count:
         // launches of that many, then single steps)
-        Stream2DPlan plan;
-        if (nsteps > 2) plan = stream2d_plan(p, cus);
-        else plan.ty[1] = stream2d_rows(p, cus);
+        const Stream2DPlan plan = stream2d_plan(p, cus, nsteps);
         int64_t n = (nsteps + plan.ks - 1) / plan.ks;
         if (n % 2 && n < nsteps) ++n;
         for (int64_t st = 0, i = 0; st < nsteps; ++i) {

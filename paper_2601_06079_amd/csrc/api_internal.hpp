@@ -41,13 +41,14 @@ int guarded(const char* name, F&& body) noexcept
 
 // launch shape of the 2-D explicit kernels for this problem on a device of `cus` compute
 // units: rows per wave of single steps; steps fused per launch and rows per wave for each
-// count of fused steps (fixed: the count was set by pf_tune_set); prefetch depth
+// count of fused steps (fixed: the count was set by pf_tune_set; else calls of one or two
+// steps are not fused); prefetch depth
 struct Stream2DPlan {
     int ks = 1, ty[5] = {};
     bool fixed = false;
 };
 int stream2d_rows(const pf_problem* p, int cus);
-Stream2DPlan stream2d_plan(const pf_problem* p, int cus);
+Stream2DPlan stream2d_plan(const pf_problem* p, int cus, int64_t nsteps);
 int stream2d_depth(const pf_problem* p);
 
 size_t newton_workspace_bytes(const pf_problem* p, int restart);

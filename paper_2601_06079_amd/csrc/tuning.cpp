@@ -127,12 +127,13 @@ int stream2d_rows(const pf_problem* p, int cus)
     return ov > 0 ? ov : single_rows(p, 4 * (cus > 0 ? cus : 256));
 }
 
-Stream2DPlan stream2d_plan(const pf_problem* p, int cus)
+Stream2DPlan stream2d_plan(const pf_problem* p, int cus, int64_t nsteps)
 {
     const int S = 4 * (cus > 0 ? cus : 256);  // SIMDs
     const int rows = g_rows_override.load(), fuse = g_fuse_override.load();
     Stream2DPlan q;
     q.ty[1] = rows > 0 ? rows : single_rows(p, S);
+    if (fuse == 0 && nsteps <= 2) return q;
     // The plan of grids of many rounds.  Four fused steps are fastest there for
     // Allen-Cahn; Cahn-Hilliard on the seam-sharing kernel is fastest with three from
     // 2048^2 (7.7 us/step; two: 8.1, and 10% slower than three at 8192^2); with nodal
@@ -229,7 +230,7 @@ int pf_launch_shape(const pf_ctx* ctx, const pf_problem* p, int* ks, int* ty, in
         if (int rc = check_ctx(ctx)) return rc;
         if (int rc = validate(p)) return rc;
         if (!ks || !ty || !depth) return fail(PF_EINVAL, "NULL output pointer");
-        const Stream2DPlan q = stream2d_plan(p, ctx->cus);
+        const Stream2DPlan q = stream2d_plan(p, ctx->cus, INT64_MAX);  // of a run of many steps
         *ks = q.ks;
         *ty = q.ty[q.ks];
         *depth = stream2d_depth(p);

@@ -306,7 +306,7 @@ typedef struct pf_newton_opts {
     double atol;            /* or ||R||_2 <= atol (default 0) */
     int32_t max_newton;     /* Newton corrections (default 20) */
     int32_t gmres_restart;  /* Krylov dimension m of GMRES(m), 1..64 (default 30) */
-    int32_t gmres_max_its;  /* Krylov iterations per Newton correction (default 600) */
+    int32_t gmres_max_its;  /* Arnoldi steps (or CG iterations) per Newton correction (default 600) */
     int32_t precond;        /* PF_PRECOND_* (default PF_PRECOND_JACOBI) */
     double lin_rtol_max;    /* inexact-Newton forcing: linear rtol = clamp(0.1 ||R_k||/||R_0||, */
     double lin_rtol_min;    /*   lin_rtol_min, lin_rtol_max) (defaults 1e-2, 1e-6), never below what

@@ -410,9 +410,9 @@ struct LinOp {
 };
 
 // Solve J x = b (L.x overwritten, starting from 0; n unknowns) to ||b - J x|| <= tol_abs.
-// The preconditioner (if any) must already be in L.pinv.  Returns PF status;
-// *its receives the dimension of the Krylov space in J searched (Arnoldi steps, each
-// counting the polynomial's degree), *res the last residual estimate.  A polynomial under
+// The preconditioner (if any) must already be in L.pinv.  At most max_its Arnoldi steps.
+// Returns PF status; *its receives the dimension of the Krylov space in J searched (Arnoldi
+// steps, each counting the polynomial's degree), *res the last residual estimate.  A polynomial under
 // which ten Arnoldi steps in a row give less than a quarter of the reduction its interval
 // promises is dropped: its interval does not hold the spectrum, and the diagonal alone
 // (a constant factor in it does not matter to GMRES) goes on from the residual reached.
@@ -436,7 +436,7 @@ int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n,
     std::array<double, (MAXM + 1) * MAXM> H{};
     std::array<double, MAXM> cs{}, sn{}, y{};
     std::array<double, MAXM + 1> gv{};
-    int total = 0;
+    int total = 0, products = 0;
     double beta = bnorm;
     bool first = true;
     int judged = 0;           // Arnoldi steps since the polynomial was last judged
@@ -483,7 +483,7 @@ int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n,
         int j = 0;
         bool done = false, stuck = false;
         const int deg = A.cheb.deg;  // products with J per Arnoldi step
-        const int steps = std::min(m, (max_its - total + deg - 1) / deg);
+        const int steps = std::min(m, max_its - total);
         if (steps > 0)
             if (int rc = enqueue(0)) return rc;
         for (; j < steps; ++j) {
@@ -491,7 +491,8 @@ int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n,
                 if (int rc = enqueue(j + 1)) return rc;
             if (hipEventSynchronize(rb->ev[j & 1]) != hipSuccess) return check_launch("GMRES column wait");
             const double* col = rb->host + (j & 1) * DEV_Y;
-            total += deg;
+            ++total;
+            products += deg;
             for (int i = 0; i <= j; ++i) H[i * MAXM + j] = col[DEV_H1 + i] + col[DEV_H2 + i];
             const double hn = std::sqrt(std::max(col[DEV_NRM], 0.0));
             H[(j + 1) * MAXM + j] = hn;
@@ -558,7 +559,7 @@ int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n,
         if (done || total >= max_its) break;
         if (stuck) A.cheb = Cheb{};
     }
-    *its = total;
+    *its = products;
     return check_launch("gmres");
 }
 

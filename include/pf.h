@@ -309,9 +309,7 @@ typedef struct pf_newton_opts {
     int32_t gmres_max_its;  /* Arnoldi steps (or CG iterations) per Newton correction (default 600) */
     int32_t precond;        /* PF_PRECOND_* (default PF_PRECOND_JACOBI) */
     double lin_rtol_max;    /* inexact-Newton forcing: linear rtol = clamp(0.1 ||R_k||/||R_0||, */
-    double lin_rtol_min;    /*   lin_rtol_min, lin_rtol_max) (defaults 1e-2, 1e-6), never below what
-                             * leaves 1/100 of the rtol / atol stop, and (stagnation = 1)
-                             * lin_rtol_max once ||R|| is at the field precision's rounding floor */
+    double lin_rtol_min;    /*   lin_rtol_min, lin_rtol_max) (defaults 1e-2, 1e-6) */
     int32_t stagnation;     /* 1: also stop at the field precision's rounding floor: after
                              * >= 2 corrections ||R_k|| > ||R_{k-1}||/2 while the last
                              * correction is <= 8 eps max|U|, or ||R_k|| > 0.9 ||R_{k-1}||

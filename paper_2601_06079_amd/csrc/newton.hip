@@ -773,7 +773,7 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
     R.res_norm[0] = r0;
     R.reason = -1;
     int status = PF_OK;
-    double rk = r0, rprev = r0, rprev2 = r0, lres = 0.0;
+    double rk = r0, rprev = r0;
     if (!std::isfinite(r0)) {
         R.reason = -2;
         status = fail(PF_ENONFINITE, "initial residual is not finite");
@@ -797,12 +797,7 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
             break;
         }
         if (k >= o.max_newton) break;
-        // a linear residual of a hundredth of the Newton stop is as good as a smaller one, and
-        // a residual ten times what the last linear solve and Newton's quadratic term
-        // (estimated from the correction before) leave is rounding noise: solving for its
-        // correction beyond lin_rtol_max would resolve only noise
-        double lin = std::min(o.lmax, std::max({o.lmin, 0.1 * rk / r0, 0.01 * std::max(o.rtol * r0, o.atol) / rk}));
-        if (o.stagnation && k >= 3 && rk > 10.0 * (lres + rprev * rprev * (rprev / (rprev2 * rprev2)))) lin = o.lmax;
+        const double lin = std::min(o.lmax, std::max(o.lmin, 0.1 * rk / r0));
         A.cheb = Cheb{};
         if (poly) {
             double r = spectrum_drift<T>(A, moved);
@@ -827,6 +822,7 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
         }
         pfk::kr_scale<T>(L.R, L.b, -1.0, n, s);  // b = -R
         int its = 0;
+        double lres = 0.0;
         const bool jac = o.precond == PF_PRECOND_JACOBI;
         if (int rc = o.krylov == PF_KRYLOV_CG ? pcg<T>(rb, A, L, n, o.max_its, jac, rk, lin * rk, &its, &lres, s)
                      : A.schur ? gmres_schur<T>(rb, A, L, o.m, o.max_its, lin * rk, &its, &lres, s)
@@ -837,7 +833,6 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
         }
         R.gmres_its += its;
         pfk::kr_add_maxabs<T>(U, L.x, n, L.part, dmisc, s, rb->scal_dev() + 1);
-        rprev2 = rprev;
         rprev = rk;
         if (int rc = residual_norm(&rk)) return rc;
         dmax = rb->scal()[1];

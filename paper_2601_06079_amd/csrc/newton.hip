@@ -416,9 +416,11 @@ struct LinOp {
 // which ten Arnoldi steps in a row give less than a quarter of the reduction its interval
 // promises is dropped: its interval does not hold the spectrum, and the diagonal alone
 // (a constant factor in it does not matter to GMRES) goes on from the residual reached.
+// verify: the residual of a solution is formed too, and the solver goes on where it is more
+// than ten times the tolerance and still falls; *res is that residual.
 template <typename T>
 int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n, int m, int max_its, bool prec,
-          double bnorm, double tol_abs, int* its, double* res, hipStream_t s)
+          double bnorm, double tol_abs, int* its, double* res, hipStream_t s, bool verify = false)
 {
     constexpr int JUDGE = 10;
     // grain growth and the eliminated Cahn-Hilliard system: point Jacobi over all n unknowns
@@ -438,7 +440,7 @@ int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n,
     std::array<double, MAXM + 1> gv{};
     int total = 0, products = 0;
     double beta = bnorm;
-    bool first = true;
+    bool first = true, claimed = false;
     int judged = 0;           // Arnoldi steps since the polynomial was last judged
     double res_then = bnorm;  // and the residual there
     *res = bnorm;
@@ -455,10 +457,11 @@ int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n,
             pfk::kr_rsub<T>(b, L.w, n, s);
             pfk::kr_norm2<T>(L.w, nullptr, n, L.part, dnrm, s, rb->scal_dev());
             if (int rc = rb->wait_scalars(s)) return rc;
+            const double before = beta;
             beta = std::sqrt(rb->scal()[0]);
             *res = beta;
             if (!std::isfinite(beta)) return fail(PF_ENONFINITE, "GMRES residual is not finite");
-            if (beta <= tol_abs || total >= max_its) break;
+            if (beta <= (claimed ? 10.0 : 1.0) * tol_abs || total >= max_its || (claimed && beta > 0.5 * before)) break;
         }
         // (a fused polynomial forms P^-1 v itself)
         auto z_of = [&](int i) { return A.fused_passes(true, i + 2 <= MAXM) ? nullptr : L.z; };
@@ -556,7 +559,8 @@ int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n,
                 pfk::kr_update<T>(model, L.V, L.ld, j, dy, pinv, L.x, Nn, s, tr);
             }
         }
-        if (done || total >= max_its) break;
+        claimed = done;
+        if (done ? !verify : total >= max_its) break;
         if (stuck) A.cheb = Cheb{};
     }
     *its = products;
@@ -656,7 +660,7 @@ Cheb choose_cheb(const LinOp<T>& A, double lin, double bound)
 // caller evaluates the residual anew afterwards).
 template <typename T>
 int gmres_schur(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, int m, int max_its, double tol_abs, int* its,
-                double* res, hipStream_t s)
+                double* res, hipStream_t s, bool verify = false)
 {
     const long long N = A.g.N;
     A.schur_rhs(L.b, L.R, s);
@@ -664,7 +668,7 @@ int gmres_schur(const ColReadback* rb, const LinOp<T>& A, NWS<T>& L, int m, int 
     if (int rc = rb->wait_scalars(s)) return rc;
     const double bn = std::sqrt(rb->scal()[0]);
     if (!std::isfinite(bn)) return fail(PF_ENONFINITE, "right-hand side is not finite");
-    if (int rc = gmres<T>(rb, A, L, L.R, N, m, max_its, true, bn, tol_abs, its, res, s)) return rc;
+    if (int rc = gmres<T>(rb, A, L, L.R, N, m, max_its, true, bn, tol_abs, its, res, s, verify)) return rc;
     A.schur_back(L.b, L.x, s);
     return check_launch("eliminated system");
 }
@@ -971,8 +975,8 @@ int newton_adjoint_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T*
     const bool jac = o.precond == PF_PRECOND_JACOBI;
     // (Allen-Cahn's Jacobian is symmetric: CG solves the transposed system as well)
     if (int rc = o.krylov == PF_KRYLOV_CG ? pcg<T>(&rbv, At, L, n, o.max_its * 4, jac, bn, tol, &its, &res, s)
-                 : At.schur ? gmres_schur<T>(&rbv, At, L, o.m, o.max_its * 4, tol, &its, &res, s)
-                            : gmres<T>(&rbv, At, L, L.b, n, o.m, o.max_its * 4, jac, bn, tol, &its, &res, s))
+                 : At.schur ? gmres_schur<T>(&rbv, At, L, o.m, o.max_its * 4, tol, &its, &res, s, true)
+                            : gmres<T>(&rbv, At, L, L.b, n, o.m, o.max_its * 4, jac, bn, tol, &its, &res, s, true))
         return rc;
     // a residual at the rounding floor, above the tolerance, is the best there is; one the
     // solver did not bring down is no solution

@@ -74,3 +74,25 @@ def test_unsolved_adjoint_is_an_error():
     with pytest.raises(RuntimeError):
         S.vjp(g, A.VJP_NEWTON_STEP, 50.0, U, dev(v, F32), ub, tb)
     assert not ub.any() and not tb.any()
+
+
+@pytest.mark.parametrize("dtype", [F64, F32])
+@pytest.mark.parametrize("base,amp,kappa", [(None, None, 10.0), (0.0, 0.3, 2.0), (0.0, 0.3, 10.0), (1.8, 0.3, 2.0),
+                                            (3.0, 0.1, 2.0), (3.0, 0.6, 10.0)])
+@pytest.mark.parametrize("n", [(256, 256), (40, 30), (12, 11, 10), (40, 40, 40)])
+def test_adjoint_residual_is_what_it_says(n, base, amp, kappa, dtype):
+    """dt L W = 0.99, uniform noise about base or (None) a drop: the residual of the adjoint,
+    formed in FP64 from the result, is at most the ten tolerances (1e-6, 1e-12) the solver
+    accepts of the one it forms itself, and 10% for the rounding of that."""
+    announce("adjoint residual", n, base, amp, kappa, dtype)
+    dt, kw = 0.99, dict(n=n, model=A.ALLEN_CAHN, fe=A.F_SYM, h=1.0, W=1.0, kappa=kappa, mobility=1.0, bc=A.PERIODIC)
+    if base is None:
+        x = np.meshgrid(*[np.arange(k) - 0.5 * (k - 1) for k in reversed(n)], indexing="ij")
+        U = np.tanh((0.3 * min(n) - np.sqrt(sum(a * a for a in x))) / (2.0 * kappa) ** 0.5).ravel()
+    else:
+        U = I.uniform_field(n, -amp, amp, seed=5, base=base)
+    U, v = dev(U, dtype), dev(np.random.default_rng(5).standard_normal(U.size), dtype)
+    ub, tb = torch.zeros_like(v), torch.zeros(3, dtype=F64, device="cuda")
+    S.vjp(S.Problem(dtype=dtype, **kw), A.VJP_NEWTON_STEP, dt, U, v, ub, tb)
+    res = S.jvp(S.Problem(dtype=F64, **kw), 1.0 / dt, U.double(), ub.double() * dt) - v.double()
+    assert (res.norm() / v.double().norm()).item() < 1.1 * 10.0 * (1e-12 if dtype == F64 else 1e-6)

@@ -102,28 +102,35 @@ __global__ __launch_bounds__(256) void k_prec_schur(const T* __restrict__ U, T* 
 }
 
 // What the Chebyshev polynomial needs to know of the field: an upper bound of the
-// preconditioned operator's spectrum (see launch_spectrum), one maximum per block of 256
-// nodes.  Bound by its Gauss points, as k_prec is.
+// preconditioned operator's spectrum (see launch_spectrum), one maximum per block, and the
+// mean of f'' over the block's tile of nodes.  Bound by its Gauss points, as k_prec is.
 struct SpecCoef {
     double a;           // inv_dt m
     double jn;          // |J| times the mobility (nodal: m)
     double kd, km;      // the stiffness: diagonal, and the diagonal that bounds it from above
     double cn, cm;      // Cahn-Hilliard: of f'' in the diagonal, and in the bound
 };
+template <int D>
+struct SpecTile {
+    static constexpr int S = D == 2 ? 16 : 8, THREADS = D == 2 ? 256 : 512;  // S^D nodes
+};
 
 template <typename T, int D, int MODEL>
-__global__ __launch_bounds__(256) void k_spectrum(const T* __restrict__ U, double* __restrict__ part, Geom g,
-                                                  Lin<T> F, SpecCoef c)
+__global__ __launch_bounds__(SpecTile<D>::THREADS) void k_spectrum(const T* __restrict__ U,
+                                                                   double* __restrict__ part, Geom g, Lin<T> F,
+                                                                   SpecCoef c, int tx, int ty)
 {
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-    int i, j, k;
-    double hi = 0.0;
-    if (node_of<D>(g, idx, i, j, k)) {
+    constexpr int S = SpecTile<D>::S, NW = SpecTile<D>::THREADS / WAVE;
+    const int t = blockIdx.x, th = threadIdx.x;
+    const int i = t % tx * S + th % S, j = t / tx % ty * S + th / S % S, k = D == 2 ? 0 : t / tx / ty * S + th / (S * S);
+    double hi = 0.0, fs = 0.0, cnt = 0.0;
+    if (i < g.n[0] && j < g.n[1] && (D == 2 || k < g.n[2])) {
         T u[NB<D>::K];
         gather<T, D>(U, g, i, j, k, u);
+        const T fc = F(u[NB<D>::K / 2], (T)1);
         double top, diag;
         if constexpr (MODEL == 0) {
-            T np = F(u[NB<D>::K / 2], (T)1), nd = np;
+            T np = fc, nd = fc;
             if (!g.quad) nd = quad_sum_sq_pos<T, D>(u, F, np);
             top = c.a + c.jn * (double)np + c.km;
             diag = c.a + c.jn * (double)nd + c.kd;
@@ -133,34 +140,57 @@ __global__ __launch_bounds__(256) void k_spectrum(const T* __restrict__ U, doubl
             for (int q = 0; q < NB<D>::K; ++q) f = max(f, F(u[q], (T)1));
             const double d0 = c.a + c.kd;
             top = c.a + c.km + c.cm * (double)f;
-            diag = max(d0 + c.cn * (double)F(u[NB<D>::K / 2], (T)1), 0.1 * d0);
+            diag = max(d0 + c.cn * (double)fc, 0.1 * d0);
         }
         hi = diag > 0.0 ? top / diag : (double)INFINITY;
+        fs = (double)fc;
+        cnt = 1.0;
     }
-    for (int o = WAVE / 2; o > 0; o >>= 1) hi = max(hi, __shfl_down(hi, o, WAVE));
-    __shared__ double sh[256 / WAVE];
-    if (threadIdx.x % WAVE == 0) sh[threadIdx.x / WAVE] = hi;
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        hi = max(hi, __shfl_down(hi, o, WAVE));
+        fs += __shfl_down(fs, o, WAVE);
+        cnt += __shfl_down(cnt, o, WAVE);
+    }
+    __shared__ double sh[3][NW];
+    if (th % WAVE == 0) {
+        sh[0][th / WAVE] = hi;
+        sh[1][th / WAVE] = fs;
+        sh[2][th / WAVE] = cnt;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 256 / WAVE; ++w) hi = max(hi, sh[w]);
-        part[blockIdx.x] = hi;
+    if (th == 0) {
+        for (int w = 1; w < NW; ++w) {
+            hi = max(hi, sh[0][w]);
+            fs += sh[1][w];
+            cnt += sh[2][w];
+        }
+        part[2 * t] = hi;
+        part[2 * t + 1] = fs / cnt;
     }
 }
 
-__global__ __launch_bounds__(1024) void k_spectrum_max(const double* __restrict__ part, int nb,
-                                                       double* __restrict__ out)
+__global__ __launch_bounds__(1024) void k_spectrum_ends(const double* __restrict__ part, int nb,
+                                                        double* __restrict__ out)
 {
-    __shared__ double sh[1024];
-    double hi = 0.0;
+    __shared__ double sh[2][1024];
+    double hi = 0.0, f = (double)INFINITY;
 #pragma unroll 4
-    for (int i = threadIdx.x; i < nb; i += 1024) hi = max(hi, part[i]);
-    sh[threadIdx.x] = hi;
+    for (int i = threadIdx.x; i < nb; i += 1024) {
+        hi = max(hi, part[2 * i]);
+        f = min(f, part[2 * i + 1]);
+    }
+    sh[0][threadIdx.x] = hi;
+    sh[1][threadIdx.x] = f;
     __syncthreads();
     for (int st = 512; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) sh[threadIdx.x] = max(sh[threadIdx.x], sh[threadIdx.x + st]);
+        if ((int)threadIdx.x < st) {
+            sh[0][threadIdx.x] = max(sh[0][threadIdx.x], sh[0][threadIdx.x + st]);
+            sh[1][threadIdx.x] = min(sh[1][threadIdx.x], sh[1][threadIdx.x + st]);
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) __hip_atomic_store(out, sh[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x < 2)
+        __hip_atomic_store(out + threadIdx.x, sh[threadIdx.x][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // y = scale 2^b x (2^b: the boundary factor of the node's rows)
@@ -583,8 +613,10 @@ template <typename T>
 bool launch_spectrum(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double inv_dt,
                      const T* U, double* part, long long part_max, double* out, hipStream_t s)
 {
-    const long long nb = (g.N + 255) / 256;
-    if (nb > part_max || nb > (1ll << 30)) return false;
+    const int ts = g.dim == 2 ? SpecTile<2>::S : SpecTile<3>::S;
+    const long long tx = (g.n[0] + ts - 1) / ts, ty = (g.n[1] + ts - 1) / ts;
+    const long long nb = tx * ty * (g.dim == 3 ? (g.n[2] + ts - 1) / ts : 1);
+    if (2 * nb > part_max || nb > (1ll << 30)) return false;
     const double m = std::pow(g.h, g.dim), hk = g.dim == 3 ? g.h : 1.0;
     const StencilDiag d = stencil_diag(g);
     const Lin<T> F{(T)f.b0, (T)f.b1, (T)f.b2};
@@ -602,11 +634,11 @@ bool launch_spectrum(const Geom& g, int model, const FreeEnergy& f, double kappa
     }
     DIM_SWITCH(g, {
         if (model == 0)
-            k_spectrum<T, D, 0><<<(unsigned)nb, 256, 0, s>>>(U, part, g, F, c);
+            k_spectrum<T, D, 0><<<(unsigned)nb, SpecTile<D>::THREADS, 0, s>>>(U, part, g, F, c, (int)tx, (int)ty);
         else
-            k_spectrum<T, D, 1><<<(unsigned)nb, 256, 0, s>>>(U, part, g, F, c);
+            k_spectrum<T, D, 1><<<(unsigned)nb, SpecTile<D>::THREADS, 0, s>>>(U, part, g, F, c, (int)tx, (int)ty);
     });
-    k_spectrum_max<<<1, 1024, 0, s>>>(part, (int)nb, out);
+    k_spectrum_ends<<<1, 1024, 0, s>>>(part, (int)nb, out);
     return true;
 }
 

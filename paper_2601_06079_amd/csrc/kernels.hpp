@@ -159,8 +159,8 @@ void launch_prec(const Geom& g, int model, const FreeEnergy& f, double kappa, do
                  double inv_dt, const T* U, T* pinv, hipStream_t s, double theta = 1.0);
 // Centre entries and sums of products of the unit Q1 stencils: K_aa, the diagonals of
 // K K and of K M (M the Gauss-integrated mass over m), and the largest symbols of K and
-// K M; 2-D h-free, 3-D per h (K K: per h^2)
-struct StencilDiag { double kd, kk, km, kmax, kmmax; };
+// K M; 2-D h-free, 3-D per h (K K: per h^2); mm: the centre entry of M
+struct StencilDiag { double kd, kk, km, kmax, kmmax, mm; };
 inline StencilDiag stencil_diag(const Geom& g)
 {
     // nodal: 5/7-point K, M the identity.  Gauss: 2-D entries 8/3, -1/3 (8 neighbours) and
@@ -168,9 +168,10 @@ inline StencilDiag stencil_diag(const Geom& g)
     // corners) and mass 8/27, 2/27, 1/54, 1/216; the symbol is largest at one axis' Nyquist
     // wave (4), nodal at all of them (8 / 12); that of K M at a wave of three nodes along one
     // axis (3 / 2)
-    if (g.quad) return g.dim == 2 ? StencilDiag{4.0, 20.0, 4.0, 8.0, 8.0} : StencilDiag{6.0, 42.0, 6.0, 12.0, 12.0};
-    return g.dim == 2 ? StencilDiag{8.0 / 3.0, 8.0, 1.0, 4.0, 1.5}
-                      : StencilDiag{8.0 / 3.0, 7.5, 8.0 / 3.0 * 8.0 / 27.0 - 2.0 / 54.0 - 8.0 / 12.0 / 216.0, 4.0, 1.5};
+    if (g.quad) return g.dim == 2 ? StencilDiag{4.0, 20.0, 4.0, 8.0, 8.0, 1.0} : StencilDiag{6.0, 42.0, 6.0, 12.0, 12.0, 1.0};
+    return g.dim == 2 ? StencilDiag{8.0 / 3.0, 8.0, 1.0, 4.0, 1.5, 4.0 / 9.0}
+                      : StencilDiag{8.0 / 3.0, 7.5, 8.0 / 3.0 * 8.0 / 27.0 - 2.0 / 54.0 - 8.0 / 12.0 / 216.0, 4.0, 1.5,
+                                    8.0 / 27.0};
 }
 
 // 1 / (theta diag S) of the Cahn-Hilliard Newton system with mu eliminated (N values)
@@ -187,6 +188,8 @@ void launch_prec_schur(const Geom& g, const FreeEnergy& f, double kappa, double 
 // Cahn-Hilliard with mu eliminated: the same quotient of the largest symbols over
 // launch_prec_schur's diagonal, f'' the largest at the node and its neighbours: what the
 // short waves see where f'' varies over more than one node, an estimate elsewhere.
+// out[1] = the least mean of f'' over a tile of 16 x 16 or 8 x 8 x 8 nodes (those of a
+// shorter axis: its nodes).
 // part: at most part_max doubles.  False (nothing launched) where they do not suffice.
 template <typename T>
 bool launch_spectrum(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double inv_dt,

@@ -98,7 +98,7 @@ struct ColReadback {
     }
 };
 constexpr size_t RB_DOUBLES = 2 * DEV_Y + MAXM + 8;
-constexpr int SCAL_SPEC = 6;  // of the scalars: the spectrum's bound (before it the norms and the CG's)
+constexpr int SCAL_SPEC = 6;  // of the scalars: launch_spectrum's two (before them the norms and the CG's)
 
 ColReadback col_readback(const pf_ctx* ctx)
 {
@@ -568,14 +568,18 @@ int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n,
 }
 
 // The polynomial for a linear solve to the relative residual lin: the interval and the
-// degree.  It needs a positive spectrum: Allen-Cahn's Jacobian is symmetric with
-// f'' >= -W, so D^-1 J has eigenvalues of at least (1/dt - L W) m / max D; S is similar to
-// a symmetric operator whose eigenvalues are at least m/dt - M W^2 m / (4 kappa) (the
-// smallest value of k (kappa k - W m) M / m over the stiffness's eigenvalues k >= 0).
-// Elsewhere, and where the diagonal alone needs few iterations, the degree is 1.
-// The upper end is launch_spectrum's bound at the field (Allen-Cahn 1% added for rounding;
-// S, where it is an estimate, 5%): beyond the interval the polynomial grows with the
-// degree's power, and f'' has no upper limit of its own.
+// degree.
+// Upper end: launch_spectrum's bound at the field (Allen-Cahn 1% added for rounding; S,
+// where it is an estimate, 5%): beyond the interval the polynomial grows with the degree's
+// power, and f'' has no upper limit of its own.
+// Lower end: Allen-Cahn's Jacobian is symmetric and, where f'' >= f, its eigenvalues are at
+// least (1/dt + L f) m; S is similar to a symmetric operator whose eigenvalues are at least
+// m/dt, less M f^2 m / (4 kappa) if f < 0 (the least value of k (kappa k + f m) M / m over
+// the stiffness's eigenvalues k >= 0).  f = -W holds everywhere but is far too low for a
+// developed field, in which f'' is 2 W but for walls a few nodes thick, whose own modes lie
+// near f = 0.  So f is the least mean of f'' over a tile, less 0.1 W for what a mean hides;
+// a tile is wider than the walls of the grids where it matters (with thicker ones the
+// diagonal alone takes products by the hundred, whatever f is).  An eigenvalue below the interval does no harm: GMRES finds it.
 // Degree: the diagonal alone would take about P = sqrt(hi / lo) ln(2 / lin) / 2 products;
 // a product in the polynomial costs two to three vectors less than the Gram-Schmidt
 // sweeps of one more basis vector, so the basis is kept to about six vectors and the
@@ -588,20 +592,25 @@ int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n,
 // 1.50 / 1.40 (FP64 1.68 / 1.59), 500^2 1.05 / 0.84, 300^2 Cahn-Hilliard 2.18 / 2.12.
 struct Interval {
     double lo = 0.0, hi = 0.0;
+    double indefinite = HUGE_VAL;  // Cahn-Hilliard: dt M f^2 / (4 kappa), f < 0; lo > 0 below 1
 };
-// without what the field adds to the upper end
+// the interval of a field with f'' = f on average in its lowest tile and the given upper
+// bound (0: what every field has at least)
 template <typename T>
-Interval base_interval(const LinOp<T>& A)
+Interval interval_of(const LinOp<T>& A, double f, double bound)
 {
     const pf_problem* p = A.p;
     const pfk::StencilDiag d = pfk::stencil_diag(A.g);
-    const double m = A.mass(), hk = A.g.dim == 3 ? A.g.h : 1.0, mob = p->mobility;
+    const double m = A.mass(), hk = A.g.dim == 3 ? A.g.h : 1.0, mob = p->mobility, fp = std::max(f, 0.0);
     if (!(mob > 0.0) || !(p->kappa > 0.0) || !(p->W >= 0.0)) return {};
-    if (A.schur)
-        return {(A.inv_dt - mob * p->W * p->W / (4.0 * p->kappa)) * m /
-                    (A.inv_dt * m + mob * p->kappa / m * d.kk * hk * hk),
-                d.kmax * d.kmax / d.kk};
-    return {(A.inv_dt - mob * p->W) * m / (A.inv_dt * m + mob * p->kappa * d.kd * hk), d.kmax / d.kd};
+    if (p->model == PF_CAHN_HILLIARD) {
+        const double fm = std::min(f, 0.0), q = mob * fm * fm / (4.0 * p->kappa * A.inv_dt);
+        return {(1.0 - q) * A.inv_dt * m /
+                    (A.inv_dt * m + mob * p->kappa / m * d.kk * hk * hk + mob * d.km * hk * fp),
+                bound > 0.0 ? 1.05 * bound : d.kmax * d.kmax / d.kk, q};
+    }
+    return {(A.inv_dt + mob * f) * m / (A.inv_dt * m + mob * p->kappa * d.kd * hk + mob * m * d.mm * fp),
+            bound > 0.0 ? 1.01 * bound : d.kmax / d.kd, 0.0};
 }
 template <typename T>
 int cheb_degree(const LinOp<T>& A, const Interval& v, double lin)
@@ -611,40 +620,9 @@ int cheb_degree(const LinOp<T>& A, const Interval& v, double lin)
     const int top = A.fuses() ? 20 : 10;
     return (int)std::lround(std::min(products / (A.fuses() ? 4.0 : 6.0), (double)top));
 }
-// Whether a solve to lin may take a polynomial, and the field's part of the interval is to
-// be found (launch_spectrum): whatever it adds, a solve of few products stays one.
 template <typename T>
-bool may_take_cheb(const LinOp<T>& A, double lin)
+Cheb choose_cheb(const LinOp<T>& A, const Interval& v, double lin)
 {
-    return cheb_degree<T>(A, base_interval<T>(A), lin) > 1;
-}
-template <typename T>
-bool queue_spectrum(const ColReadback* rb, const LinOp<T>& A, const NWS<T>& L, hipStream_t s)
-{
-    const pf_problem* p = A.p;
-    return pfk::launch_spectrum<T>(A.g, p->model, A.f, p->kappa, p->mobility, A.inv_dt, A.U, L.part, L.part_len,
-                                   rb->scal_dev() + SCAL_SPEC, s);
-}
-// The bound is found once for a Newton step and holds while the field moves little: where
-// f'' has changed by at most df, a quotient over the nodes grows from q to (q + r) / (1 - r)
-// at most, with r the share of df in the smallest diagonal.
-template <typename T>
-double spectrum_drift(const LinOp<T>& A, double df)
-{
-    const pf_problem* p = A.p;
-    const pfk::StencilDiag d = pfk::stencil_diag(A.g);
-    const double m = A.mass(), hk = A.g.dim == 3 ? A.g.h : 1.0, mob = p->mobility;
-    if (A.schur) return mob * d.kmmax * hk * df / (A.inv_dt * m + mob / m * p->kappa * d.kk * hk * hk);
-    return mob * m * df / ((A.inv_dt - mob * p->W) * m + mob * p->kappa * d.kd * hk);
-}
-constexpr double DRIFT_MAX = 0.02;  // beyond it the bound is found anew
-
-// bound: what queue_spectrum left (after a wait)
-template <typename T>
-Cheb choose_cheb(const LinOp<T>& A, double lin, double bound)
-{
-    Interval v = base_interval<T>(A);
-    v.hi = bound * (A.schur ? 1.05 : 1.01);
     const int deg = cheb_degree<T>(A, v, lin);
     Cheb c;
     if (deg < 2) return c;
@@ -653,6 +631,76 @@ Cheb choose_cheb(const LinOp<T>& A, double lin, double bound)
     c.delta = 0.5 * (v.hi - v.lo);
     c.rate = std::min(0.5, 2.0 * c.deg * std::sqrt(v.lo / v.hi));
     return c;
+}
+
+// What the field says of the interval.  It is found once for a Newton step and holds while
+// the field moves little: where f'' has changed by at most df, a quotient over the nodes
+// grows from q to (q + r) / (1 - r) at most, with r the share of df in the least diagonal.
+template <typename T>
+struct FieldEnds {
+    bool wanted = false, found = false;
+    double bound = 0.0, f = 0.0, moved = 0.0;
+
+    // wanted: a solve to lin may take a polynomial, or be eliminated, depending on the field
+    FieldEnds(const LinOp<T>& A, bool candidate, double lin) : f(-A.p->W)
+    {
+        const Interval v = interval_of<T>(A, f, 0.0);
+        wanted = candidate && v.hi > 0.0 && (!(v.lo > 0.0) || cheb_degree<T>(A, v, lin) > 1);  // (hi 0: no such system)
+    }
+    // before a wait for the scalars, and after it
+    void queue(const ColReadback* rb, const LinOp<T>& A, const NWS<T>& L, hipStream_t s)
+    {
+        const pf_problem* p = A.p;
+        wanted = pfk::launch_spectrum<T>(A.g, p->model, A.f, p->kappa, p->mobility, A.inv_dt, A.U, L.part, L.part_len,
+                                         rb->scal_dev() + SCAL_SPEC, s);
+    }
+    void take(const ColReadback* rb, const LinOp<T>& A)
+    {
+        if (!wanted) return;
+        bound = rb->scal()[SCAL_SPEC];
+        f = std::max(-A.p->W, rb->scal()[SCAL_SPEC + 1] - 0.1 * A.p->W);
+        moved = 0.0;
+        found = true;
+    }
+    double drift(const LinOp<T>& A) const
+    {
+        const pf_problem* p = A.p;
+        const pfk::StencilDiag d = pfk::stencil_diag(A.g);
+        const double m = A.mass(), hk = A.g.dim == 3 ? A.g.h : 1.0, mob = p->mobility;
+        if (p->model == PF_CAHN_HILLIARD)
+            return mob * d.kmmax * hk * moved / (A.inv_dt * m + mob / m * p->kappa * d.kk * hk * hk);
+        const double least = (A.inv_dt - mob * p->W * d.mm) * m + mob * p->kappa * d.kd * hk;
+        return least > 0.0 ? mob * m * moved / least : HUGE_VAL;
+    }
+    // the interval at A.U; a new pass over the field where it has moved too far
+    int interval(const ColReadback* rb, const LinOp<T>& A, const NWS<T>& L, Interval* v, hipStream_t s)
+    {
+        *v = interval_of<T>(A, f, HUGE_VAL);  // (without an upper end: no polynomial)
+        if (!wanted) return PF_OK;
+        double r = drift(A);
+        if (!found || !(r <= 0.02)) {
+            queue(rb, A, L, s);
+            if (int rc = rb->wait_scalars(s)) return rc;
+            take(rb, A);
+            r = 0.0;
+        }
+        if (wanted) *v = interval_of<T>(A, f, (bound + r) / (1.0 - r));
+        return PF_OK;
+    }
+};
+
+// The system and the polynomial of a solve.  Cahn-Hilliard whose spectrum reaches far below
+// zero (large steps from the unstable point) keeps both planes and their 2x2 blocks.  ms a
+// step, eliminated / blocks, by dt M f^2 / (4 kappa), kappa / h^2 = 2: noise of 0.05 at 1.06
+// 120 / none (256^2), 119 / none (64^3); of 0.05 about 0.3 at 1.03 36 / 103, 30 / 107; of
+// 0.7 at 1.25 146 / none (256^2); of 0.05 about 0.3 at 1.38 none / 286, none / 107 (none: no
+// convergence in 20 corrections).
+template <typename T>
+void choose_system(LinOp<T>& A, const Interval& v, bool schur, double lin, const NWS<T>& L)
+{
+    A.schur = schur && v.indefinite < 1.3;
+    A.zb = A.schur ? L.R + A.g.N : L.R;
+    A.cheb = !schur || A.schur ? choose_cheb<T>(A, v, lin) : Cheb{};
 }
 
 // The whole Cahn-Hilliard correction (or adjoint) J x = L.b through the eliminated
@@ -749,12 +797,10 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
     const ColReadback rbv = col_readback(ctx);
     const ColReadback* rb = &rbv;
     LinOp<T> A{p, g, f, inv_dt, U, 0};
-    A.schur = schur_ok<T>(p, g, o);
     A.pinv = L.pinv;
-    A.zb = A.schur ? L.R + g.N : L.R;
     A.tmp = L.z + g.N;  // (with mu eliminated the solver's vectors fill half their space)
-    bool poly = (A.schur || poly_ok<T>(p, g, o)) && may_take_cheb<T>(A, o.lmin);
-    double bound = -1.0, moved = 0.0;  // of the spectrum (not found yet); the change of f'' since
+    const bool schur = schur_ok<T>(p, g, o), poly = schur || poly_ok<T>(p, g, o);
+    FieldEnds<T> ends(A, poly, o.lmin);
     // ||R(U)||, read back together with whatever scalars were queued before it
     auto residual_norm = [&](double* out) -> int {
         if (p->model == PF_COUPLED)
@@ -764,11 +810,11 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
                                      inv_dt);
         else
             pfk::launch_residual<T>(g, p->model, f, p->kappa, p->mobility, U, L.R, s, Uold, inv_dt);
-        const bool spec = poly && bound < 0.0;
-        if (spec) poly = queue_spectrum<T>(rb, A, L, s);
+        const bool first = ends.wanted && !ends.found;
+        if (first) ends.queue(rb, A, L, s);
         pfk::kr_norm2<T>(L.R, nullptr, n, L.part, dnrm, s, rb->scal_dev());
         if (int rc = rb->wait_scalars(s)) return rc;
-        if (spec) bound = rb->scal()[SCAL_SPEC];
+        if (first) ends.take(rb, A);
         *out = std::sqrt(rb->scal()[0]);
         return PF_OK;
     };
@@ -802,16 +848,10 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
         }
         if (k >= o.max_newton) break;
         const double lin = std::min(o.lmax, std::max(o.lmin, 0.1 * rk / r0));
-        A.cheb = Cheb{};
         if (poly) {
-            double r = spectrum_drift<T>(A, moved);
-            if (!(r <= DRIFT_MAX)) {
-                if (queue_spectrum<T>(rb, A, L, s))
-                    if (int rc = rb->wait_scalars(s)) return rc;
-                bound = rb->scal()[SCAL_SPEC];
-                moved = r = 0.0;
-            }
-            A.cheb = choose_cheb<T>(A, lin, (bound + r) / (1.0 - r));
+            Interval v;
+            if (int rc = ends.interval(rb, A, L, &v, s)) return rc;
+            choose_system<T>(A, v, schur, lin, L);
         }
         if (o.precond == PF_PRECOND_JACOBI) {
             if (p->model == PF_COUPLED)
@@ -841,7 +881,7 @@ int newton_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T* Uold, T
         if (int rc = residual_norm(&rk)) return rc;
         dmax = rb->scal()[1];
         umax = rb->scal()[2];
-        moved += dmax * (std::fabs(f.b1) + std::fabs(f.b2) * (2.0 * umax + dmax));
+        ends.moved += dmax * (std::fabs(f.b1) + std::fabs(f.b2) * (2.0 * umax + dmax));
         ++k;
         if (k <= 32) R.res_norm[k] = rk;
         if (!std::isfinite(rk)) {
@@ -948,15 +988,15 @@ int newton_adjoint_t(const pf_ctx* ctx, const pf_problem* p, double dt, const T*
     NWS<T> L = layout<T>(p, ws);
     const double inv_dt = 1.0 / dt;
     LinOp<T> At{p, g, f, inv_dt, U, 1};
-    At.schur = schur_ok<T>(p, g, o);
     At.tmp = L.z + g.N;
     At.pinv = L.pinv;
-    At.zb = At.schur ? L.R + g.N : L.R;
+    const bool schur = schur_ok<T>(p, g, o);
     // the adjoint solve is taken to the field-precision floor, not an inexact-Newton tolerance
     const double lin = sizeof(T) == 4 ? 1e-6 : 1e-12;
-    if ((At.schur || poly_ok<T>(p, g, o)) && may_take_cheb<T>(At, lin) && queue_spectrum<T>(&rbv, At, L, s)) {
-        if (int rc = rbv.wait_scalars(s)) return rc;
-        At.cheb = choose_cheb<T>(At, lin, rbv.scal()[SCAL_SPEC]);
+    if (schur || poly_ok<T>(p, g, o)) {
+        Interval v;
+        if (int rc = FieldEnds<T>(At, true, lin).interval(&rbv, At, L, &v, s)) return rc;
+        choose_system<T>(At, v, schur, lin, L);
     }
     if (At.schur)
         pfk::launch_prec_schur<T>(g, f, p->kappa, p->mobility, inv_dt, At.cheb.theta, U, L.pinv, s);

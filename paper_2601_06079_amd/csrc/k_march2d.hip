@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void k_march2d(March<T> p, int nx, int ny, int
             const T v1 = lw.v1;  // ME_CHRES: v at the output row
             T lapv = 0;
             if constexpr (EPI == ME_CHRES) lapv = lw.push(v);
-            T o = HASU ? fmaT(k.kv, lap, s) : k.kv * lap;
+            T o = add_stiffness(k, lap, s);
             if constexpr (OP == MOP_SCHUR) o = k.kw * lw.push(o);
             const T cc = H == 2 ? c2 : c1;
             c2 = c1;

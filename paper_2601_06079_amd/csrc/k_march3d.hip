@@ -34,7 +34,7 @@ namespace {
 template <typename T>
 struct MC3 {           // coefficients in the field type
     T a, b, c;         // GRAD: q (a + q (b + c q)); JVP: (a + q (b + c q)) v  (|J| folded in)
-    T kv;              // times Lap3 (h / 12 folded in), nodal: times LapN3 (h folded in)
+    T kv, kl;          // times Lap3 (h / 12 folded in), nodal: times LapN3 (h folded in); its rest
     T s0, s1, s2;
     T g1, g2, g3;      // ME_ADJ: f' at W = 1
 };
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256) void k_march3d(March<T> p, ML3 L, MC3<T> k)
                 if (y0 + j >= L.ny) break;
                 T ib = zs;
                 if (MIRROR && p.rows) ib = edge_count(y0 + j, L.ny) ? zs * (T)0.5 : zs;
-                const T o = HASU ? fmaT(k.kv, lap[j], s[j]) : k.kv * lap[j];
+                const T o = add_stiffness(k, lap[j], HASU ? s[j] : (T)0);
                 const T c = p.base ? eb[j] : (HASV ? vc[j] : uc[j]);
                 T r;
                 if constexpr (EPI == ME_OUT) r = (k.s0 != (T)0 ? fmaT(k.s0, c - e1[j], o) : o) * ib;
@@ -482,7 +482,9 @@ bool launch_r(const Geom& g, const Shape3& shape, int op, int epi, const FreeEne
     } else {
         k.a = (T)(w * f.b0); k.b = (T)(w * f.b1); k.c = (T)(w * f.b2);
     }
-    k.kv = (T)(m.kv * (g.quad ? g.h : g.h / 12.0));
+    const double kv = m.kv * (g.quad ? g.h : g.h / 12.0);
+    k.kv = (T)kv;
+    k.kl = (T)(kv - (double)k.kv);
     k.s0 = (T)m.s0;
     k.s1 = (T)m.s1;
     k.s2 = (T)m.s2;

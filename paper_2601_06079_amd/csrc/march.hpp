@@ -57,4 +57,16 @@ struct March {
     int rows = 0;             // divide the rows of boundary nodes by 2^b (no-flux)
 };
 
+// s + kv K v (lap: K v without its coefficient).  The coefficient folds kappa, dt and the
+// like into one number, whose rounding (up to 6e-8 in FP32) would act on every step of a run
+// alike; what it leaves is applied too, one operation a node.
+template <typename T, typename Coefs>
+__device__ __forceinline__ T add_stiffness(const Coefs& k, T lap, T s)
+{
+    if constexpr (sizeof(T) == 4)
+        return __builtin_fmaf(k.kv, lap, __builtin_fmaf(k.kl, lap, s));
+    else
+        return __builtin_fma(k.kv, lap, s);
+}
+
 }  // namespace pfk

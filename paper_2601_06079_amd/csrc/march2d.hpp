@@ -14,6 +14,7 @@ template <typename T>
 struct MC2 {
     T a, b, c;  // GRAD: q (a + q (b + c q)); JVP, SCHUR: (a + q (b + c q)) v  (|J| folded in)
     T kv;       // times (9 v - box v), nodal: (4 v - nbrs)
+    T kl;       // what the rounding of kv leaves (add_stiffness)
     T kw;       // SCHUR: the outer stencil
     T s0, s1, s2;
     T g1, g2, g3;  // ME_ADJ: f' at W = 1
@@ -124,6 +125,7 @@ MC2<T> march2_coef(const Geom& g, int op, const FreeEnergy& f, double nq, double
         k.a = (T)(w * f.b0); k.b = (T)(w * f.b1); k.c = (T)(w * f.b2);
     }
     k.kv = (T)(kv * ks);
+    k.kl = (T)(kv * ks - (double)k.kv);
     k.kw = (T)(kw * ks);
     return k;
 }

@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256) void k_cheb2d(ChebP<T> p, int nx, int ny, int 
 // a Newton step; 19 rows, 3.97 waves: 4.53; 54 rows, 1.3 waves: 4.91; 78 rows, 0.95: 5.10.
 int cheb_rows(int ny, int nstrips, int H)
 {
-    const double simds = 4.0 * march2_cus();
+    const double simds = 4.0 * device_cus();
     int best = 1;
     double cost = 0.0;
     for (int len = (2 * H + 4 + MPF - 1) / MPF * MPF; len <= 128; len += MPF) {

@@ -20,6 +20,7 @@
 // With nodal (Gauss-Lobatto) quadrature N'(u) v = m f''(u_a) v_a at the node and K
 // is the 5-point stencil 4 v - (axis neighbours) (h-free in 2-D).
 #include <algorithm>
+#include <atomic>
 
 #include "device.hpp"
 #include "kernels.hpp"
@@ -216,19 +217,21 @@ __global__ __launch_bounds__(256) void k_jvp2d(const T* __restrict__ U, const T*
     }
 }
 
+}  // namespace
+
 int device_cus()
 {
-    static const int n = [] {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-            return 256;
-        return cus;
-    }();
-    return n;
+    static std::atomic<int> known[64];
+    int dev = 0, cus = 0;
+    const bool ok = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64;
+    if (ok && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
+    if (!ok || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
+        (void)hipGetLastError();
+        return 256;
+    }
+    known[dev].store(cus, std::memory_order_relaxed);
+    return cus;
 }
-
-}  // namespace
 
 template <typename T>
 bool launch_jvp2d_stream(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,

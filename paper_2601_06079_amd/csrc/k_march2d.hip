@@ -166,7 +166,7 @@ bool launch_march2d(const Geom& g, int op, int epi, const FreeEnergy& f, const M
     const int nstrips = (nx + outw - 1) / outw;
     // (the adjoint's waves are the same in every call of a trajectory, whose sums they keep)
     const int tov = epi < ME_ADJ ? tune_stream2d_rows() : 0;
-    const int ty = tov > 0 ? std::min(tov, ny) : pass_rows(ny, nstrips, H, march2_cus(), epi < ME_ADJ);
+    const int ty = tov > 0 ? std::min(tov, ny) : pass_rows(ny, nstrips, H, device_cus(), epi < ME_ADJ);
     const long long nwaves = (long long)nstrips * ((ny + ty - 1) / ty);
     if (nwaves > (1ll << 30)) return false;
     if (epi == ME_ADJ || epi == ME_ADJK) {

@@ -15,11 +15,11 @@
 // 900 VALU per node), the LDS tile kernel once but with 2 barriers per plane and 30
 // staged words per element (261 VALU per wave and plane).  Here a plane costs about 90
 // VALU per node row (110 with a direction) and R + 1 element rows serve R node rows.
-// Halo lanes cost (W - 2) / W and the two warm-up planes of a chunk (pz + 2) / pz; the
-// launcher picks G in 1..4 for the fewest waves and pz for the least work on the busiest
-// SIMD.  Measured, explicit Cahn-Hilliard step (chemical potential, then update): FP32
-// 130 x 121 x 117 40.5 -> 23.3 us, 256 x 200 x 180 66 us; the potential alone there takes
-// 36 us of about 29 us VALU issue.
+// Halo lanes cost W / (W - 2) and the two warm-up planes of a chunk (pz + 2) / pz; the
+// launcher picks G in 1..4 for the fewest waves, and R and pz by shape_gauss or
+// shape_light.  Measured, explicit Cahn-Hilliard step (chemical potential, then update):
+// FP32 130 x 121 x 117 40.5 -> 23.7 us, 256 x 200 x 180 66 us; the potential alone there
+// takes 36 us of about 29 us VALU issue.
 #include <algorithm>
 #include <cmath>
 
@@ -362,20 +362,6 @@ __global__ __launch_bounds__(256) void k_march3d(March<T> p, ML3 L, MC3<T> k)
 template <typename T>
 constexpr int ADJ_ROWS = sizeof(T) == 4 ? 2 : 1;
 
-int march_cus()
-{
-    static const int n = [] {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
-            (void)hipGetLastError();
-            return 256;
-        }
-        return cus;
-    }();
-    return n;
-}
-
 }  // namespace
 
 // How a grid is split: R rows per lane, G lane groups, pz planes per chunk.
@@ -405,7 +391,7 @@ static long long plane_waves(const Geom& g, int R, int* G)
 static Shape3 shape_light(const Geom& g, int R)
 {
     Shape3 p{R, 1, 1};
-    const long long bw = plane_waves(g, R, &p.G), simds = 4ll * march_cus();
+    const long long bw = plane_waves(g, R, &p.G), simds = 4ll * device_cus();
     double bt = -1.0;
     for (int q = 1; q <= std::min(g.n[2], 64); ++q) {
         const long long per = (bw * ((g.n[2] + q - 1) / q) + simds - 1) / simds;
@@ -430,7 +416,7 @@ static Shape3 shape_gauss(const Geom& g, bool jvp, bool f64)
 {
     static const int planes[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 16, 20, 24};
     const double idle = jvp ? (f64 ? 0.2 : 0.8) : (f64 ? 0.4 : 1.0), part = jvp == f64 ? 0.5 : 1.0;
-    const double simds = 4.0 * march_cus();
+    const double simds = 4.0 * device_cus();
     Shape3 best{2, 1, 1};
     double bt = -1.0;
     for (int R = 2; R <= (jvp && f64 ? 2 : 4); R += 2) {

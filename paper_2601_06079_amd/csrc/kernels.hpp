@@ -78,6 +78,7 @@ int tune_nn_group();       // samples per forward group of the surrogate (0: aut
 int tune_gs_reorth();      // Gram-Schmidt re-orthogonalisation threshold (0: default)
 int tune_gg_stream();      // 1: grain steps on the tile kernel
 int tune_jvp2d_stream();   // 1: 2-D Jacobian products on the node-centric kernel
+int device_cus();          // compute units of the current device
 int tune_stream2d_rows();  // rows per wave of the 2-D streaming kernels (0: automatic)
 // Row-streaming 2-D Jacobian product (k_jvp2d.hip): Gauss quadrature, lumped
 // mass, periodic or no-flux; the non-transposed product, which for Allen-Cahn is
@@ -112,7 +113,7 @@ void launch_gg_jvp2d(const Geom& g, int P, double L, double kappa, double gamma,
 // out[0] = E_h, out[1] = sum m sum_i eta_i; partials: 2 * energy_blocks(g) doubles
 template <typename T>
 void launch_gg_energy2d(const Geom& g, int P, double kappa, double gamma, const T* U, double* part,
-                        double* out, hipStream_t s);  // z-planes per wave of the elasticity operator (0 = automatic)
+                        double* out, hipStream_t s);
 // 3-D Jv (acc = 0) by element-wise sum factorisation through z-marching LDS tiles
 template <typename T>
 void launch_jvp3d(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob,

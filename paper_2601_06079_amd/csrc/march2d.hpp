@@ -99,20 +99,6 @@ struct Quad2 {
 
 constexpr int MPF = 4;  // rows in flight per field
 
-inline int march2_cus()
-{
-    static const int n = [] {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
-            (void)hipGetLastError();
-            return 256;
-        }
-        return cus;
-    }();
-    return n;
-}
-
 // the kernels' coefficients of an operator (epilogue coefficients s0 .. s2 apart)
 template <typename T>
 MC2<T> march2_coef(const Geom& g, int op, const FreeEnergy& f, double nq, double kv, double kw)

@@ -522,10 +522,10 @@ def lobatto_record(stream, n=2048, steps=2000):
 
 def implicit2d_record(stream, model, n, steps=10, dt=0.05, mass=0, krylov=0, quad=0):
     """The paper's 2-D implicit benchmark shapes (backward Euler, Newton + GMRES(30)
-    with block Jacobi, FP32 fields): [0, 100]^2 with n^2 nodes, no-flux,
+    with the default preconditioner, FP32 fields): [0, 100]^2 with n^2 nodes, no-flux,
     f' = 4c(c-1)(c-1/2) (W = 1), M = 1, kappa = 2 (Allen-Cahn) or 1.5 (Cahn-Hilliard);
-    initial field 0.5 + U(-0.05, 0.05).  dt = 0.05: block-Jacobi GMRES iterations grow
-    with dt kappa / h^2 (34 per Newton iteration at 2048^2, 57 at dt = 0.2)."""
+    initial field 0.5 + U(-0.05, 0.05).  dt = 0.05.  The counts per Newton iteration are
+    products (each step of a polynomial preconditioner is one)."""
     import numpy as np
     import torch
 
@@ -561,7 +561,9 @@ def implicit2d_record(stream, model, n, steps=10, dt=0.05, mass=0, krylov=0, qua
     mname = "consistent mass (all terms Gauss-integrated)" if mass else "lumped mass"
     if quad == A.QUAD_LOBATTO:
         mname = "Gauss-Lobatto (nodal) quadrature"
-    lin = "CG with point Jacobi" if krylov == A.KRYLOV_CG else "GMRES(30) with block-Jacobi"
+    lin = ("CG with point Jacobi" if krylov == A.KRYLOV_CG else
+           "GMRES(30) with 2x2 block-Jacobi" if mass and ch else "GMRES(30) with point Jacobi" if mass else
+           "GMRES(30) with a Chebyshev polynomial over point Jacobi" + (", mu eliminated" if ch else ""))
     return {"workload": f"2D {name} {n}x{n} on [0,100]^2, no-flux, backward Euler dt={dt}, {mname}, "
                         f"Newton + {lin}, FP32 fields",
             "dof": dof, "steps": steps, "converged_steps": ok, "ms_per_step": 1e3 * el / steps,
@@ -881,8 +883,9 @@ def surrogate_record(stream, n=512, Bn=16, K=20, dt=0.01):
 
 def implicit_record(steps, stream):
     """Backward-Euler Newton steps of 128^3 periodic Cahn-Hilliard (c, mu both
-    unknowns: 4 194 304 DOF), dt = 0.5, matrix-free JVP + GMRES(30) with 2x2
-    block-Jacobi, FP32 fields and FP64 reductions (Eqs. 13-14)."""
+    unknowns: 4 194 304 DOF), dt = 0.5, matrix-free JVP + GMRES(30) on the system with mu
+    eliminated, with a Chebyshev polynomial over point Jacobi, FP32 fields and FP64
+    reductions (Eqs. 13-14)."""
     import numpy as np
     import torch
 
@@ -915,7 +918,7 @@ def implicit_record(steps, stream):
     el = time.perf_counter() - t0
     dof = 2 * int(np.prod(n))
     return {"workload": "3D Cahn-Hilliard 128^3 periodic, backward Euler dt=0.5, Newton + GMRES(30) "
-                        "with 2x2 block-Jacobi, FP32 fields, FP64 reductions",
+                        "with a Chebyshev polynomial over point Jacobi, mu eliminated, FP32 fields, FP64 reductions",
             "dof": dof, "steps": steps, "converged_steps": ok, "ms_per_step": 1e3 * el / steps,
             "dof_steps_per_s": dof * steps / el,
             "newton_its_per_step": float(np.mean(newton)),

@@ -182,7 +182,8 @@ int pf_fma_probe(pf_ctx* ctx, int blocks, int iters, float* out, void* stream);
  *                           the row-streaming 2-D Jacobian product;
  *   PF_TUNE_STREAM2D_DEPTH: rows it keeps in flight per wavefront (<=4, <=8, else 16);
  *   PF_TUNE_STREAM2D_FUSE:  explicit steps fused per launch by temporal blocking (1..4);
- *   PF_TUNE_JVP3D_PLANES:   z-planes per block of the 3-D Jacobian product;
+ *   PF_TUNE_JVP3D_PLANES:   z-planes per block of the 3-D Jacobian product of both
+ *                           Cahn-Hilliard planes (Allen-Cahn: of fields of 2 GiB and more);
  *   PF_TUNE_EL_PLANES:      z-planes (2-D: rows) per wave of the elasticity operator;
  *   PF_TUNE_STREAM2D_SEAM:  1 = fused 2-D launches recompute the rows where chunks meet
  *                           (each wave alone); 0 = the waves of a workgroup share them
@@ -197,7 +198,9 @@ int pf_fma_probe(pf_ctx* ctx, int blocks, int iters, float* out, void* stream);
  *   PF_TUNE_JVP2D_STREAM:   1 = 2-D Jacobian products (pf_jvp, the Newton Krylov
  *                           solves) on the node-centric kernel; 0 = the row-streaming
  *                           kernel where it applies (default: Gauss quadrature,
- *                           lumped mass, Allen-Cahn and Cahn-Hilliard);
+ *                           lumped mass, Allen-Cahn and Cahn-Hilliard).  The products of
+ *                           the eliminated Cahn-Hilliard system and of a polynomial
+ *                           preconditioner have the streaming form only;
  *   PF_TUNE_EL_MG:          1 = plain CG for the elasticity solves (no multigrid);
  *                           2 = multigrid with every level launched separately;
  *                           v >= 3 = the multigrid's coarse grids of at most v
@@ -290,9 +293,10 @@ int pf_jvp(pf_ctx* ctx, const pf_problem* p, double inv_dt, const void* U, const
 /* Backward-Euler Newton step (Eqs. 13-14, Sec. 2.3)                        */
 /* ---------------------------------------------------------------------- */
 /* PF_PRECOND_JACOBI: the point (AC), 2x2 (CH) or 3x3 block (coupled) diagonal.  With the
- * lumped mass and GMRES, Cahn-Hilliard eliminates mu and takes the point diagonal of what
- * remains, and both models raise the diagonal to a Chebyshev polynomial where the spectrum
- * is known to be positive (AC: dt L W < 1; CH: dt M W^2 < 4 kappa; positive parameters). */
+ * lumped mass, GMRES, mobility > 0, kappa > 0 and W >= 0, Cahn-Hilliard eliminates mu and
+ * takes the point diagonal of what remains unless its spectrum reaches far below zero, and
+ * both models raise the diagonal to a Chebyshev polynomial where the field's f'' leaves
+ * the spectrum positive (everywhere for AC with dt L W < 1, CH with dt M W^2 < 4 kappa). */
 enum { PF_PRECOND_NONE = 0, PF_PRECOND_JACOBI = 1 };
 /* Linear solver of each Newton correction.  PF_KRYLOV_CG (preconditioned
  * conjugate gradients, device-resident scalars) needs a symmetric positive
@@ -366,7 +370,10 @@ enum { PF_VJP_BEGIN = 1, PF_VJP_END = 2 }; /* flags of the adjoints that run in 
  *   PF_VJP_NEWTON_STEP:    U is the converged root of one backward-Euler step:
  *                          solve (dR/dU)^T lambda = vbar (GMRES, same opts as
  *                          the forward step), then Ubar(U_old) += (M/dt) lambda,
- *                          theta_bar -= (dr/dtheta)^T lambda   (II.5-II.6).
+ *                          theta_bar -= (dr/dtheta)^T lambda   (II.5-II.6).  lambda is
+ *                          solved to a relative residual of 1e-12 (PF_F64) or 1e-6;
+ *                          PF_ENOCONV, and nothing accumulated, if it stays above the
+ *                          square root of that.
  * U_old is read only by PF_VJP_RESIDUAL (see there) and may be NULL otherwise.
  * theta_bar accumulates in FP64 with a fixed reduction order.  dt is ignored
  * for PF_VJP_RESIDUAL without U_old.  ws: pf_workspace_size(PF_OP_VJP).

@@ -468,8 +468,8 @@ void launch_gg_tile2d(const Geom& g, int P, double L, double kappa, double gamma
 // the 0.8 of one that a single wave idles.  Starts from the chunks that just fill the
 // resident waves.  Fitted to 20 chunk lengths at 96^2 to 1024^2, 2 to 20 fields: 0.3% off
 // the best on average.  us per step, resident waves with at least 8 rows each / this rule:
-// 20 fields 96^2 27.7 / 9.0, 400^2 30.2 / 17.2, 1024^2 53.4 / 48.1; 8 fields 200^2 11.8 /
-// 5.9, 1024^2 26.0 / 20.6; 2 fields 96^2 5.8 / 3.5.
+// 20 fields 96^2 27.7 / 9.0, 400^2 30.2 / 17.2 (1024^2: the same chunks, 50.3); 8 fields
+// 200^2 11.8 / 5.9, 1024^2 26.0 / 20.6; 2 fields 96^2 5.8 / 3.5.
 static int gg_chunks(int ny, int nstrips, int k, int cus)
 {
     const int simds = 4 * (cus > 0 ? cus : 256);

@@ -132,7 +132,7 @@ struct PlaneRing {
     }
 };
 
-// MODEL 0 (Allen-Cahn): fields {c, v};  Jv = inv_dt m v + L (N'(c) v + kappa K v)
+// MODEL 0 (Allen-Cahn, fields of 2 GiB and more; smaller ones march): fields {c, v};  Jv = inv_dt m v + L (N'(c) v + kappa K v)
 // MODEL 1 (Cahn-Hilliard): fields {c, v_c, v_mu};
 //   TRANS 0: [inv_dt m v_c + M K v_mu ;  m v_mu - (N'(c) v_c + kappa K v_c)]
 //   TRANS 1: [inv_dt m v_c - (N'(c) v_mu + kappa K v_mu) ;  M K v_c + m v_mu]

@@ -11,8 +11,8 @@
 // is queued before the host waits for the current column, so the device never
 // idles on the round trip; a step queued past convergence is discarded.
 //
-// GMRES(m) variant: right preconditioning (the residual it monitors is the true
-// one), classical Gram-Schmidt with one re-orthogonalisation, x0 = 0, restart
+// GMRES(m) variant: right preconditioning (it monitors an estimate of the true
+// residual), classical Gram-Schmidt with one re-orthogonalisation, x0 = 0, restart
 // from the true residual b - J x.  Inexact Newton: the linear tolerance is
 // clamp(0.1 ||R_k|| / ||R_0||, lin_rtol_min, lin_rtol_max) relative to ||R_k||.
 #include <cmath>

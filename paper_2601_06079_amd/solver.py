@@ -236,15 +236,15 @@ class CheckpointedRun(torch.autograd.Function):
 
     theta = (mobility, kappa, W) as a float64 tensor of 3.  Forward keeps a
     snapshot every `every` steps (explicit runs with keep also the last segment's
-    states, which the first backward takes over as its buffer); backward walks the segments in reverse, recomputes each segment's states from
-    its snapshot (bitwise the forward's: every kernel is deterministic, and both
-    passes advance with the same launches: fused launches are bitwise single steps
-    on periodic grids, and no-flux grids, where a fused stage rounds the reflected
-    rows differently, take single-step launches in the forward pass too) and applies
-    the step adjoint of the library (the explicit trajectory's adjoint, or the
-    transposed Newton solve at each root), accumulating the gradient of theta in
-    FP64.  For Cahn-Hilliard explicit runs only the c plane of U_N is differentiated
-    (mu is recomputed from c).
+    states, which the first backward takes over as its buffer); backward walks the
+    segments in reverse, recomputes each segment's states from its snapshot (bitwise
+    the forward's: every kernel is deterministic, and both passes advance with the
+    same launches: fused launches are bitwise single steps on periodic grids, and
+    no-flux grids, where a fused stage rounds the reflected rows differently, take
+    single-step launches in the forward pass too) and applies the step adjoint of the
+    library (the explicit trajectory's adjoint, or the transposed Newton solve at each
+    root), accumulating the gradient of theta in FP64.  For Cahn-Hilliard explicit
+    runs only the c plane of U_N is differentiated (mu is recomputed from c).
     """
 
     @staticmethod

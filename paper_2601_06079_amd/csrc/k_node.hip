@@ -169,15 +169,56 @@ __global__ __launch_bounds__(SpecTile<D>::THREADS) void k_spectrum(const T* __re
     }
 }
 
-__global__ __launch_bounds__(1024) void k_spectrum_ends(const double* __restrict__ part, int nb,
+// The largest of the tiles' bounds, and the least of (mean of f'' + the stiffness energy of a
+// mode that lives there) over windows of one tile and of 2, 4, ... tiles a side (means of
+// the windows below, kept behind the tiles' pairs): kh (pi / side)^2 for every axis longer
+// than the window.  (kh 0: the least tile.)  One block, bound by the latency of the levels:
+// 2048^2 (16384 tiles) 20 us.
+struct SpecWindows {
+    int d[3], n[3];  // tiles and nodes of each axis
+    double kh;       // kappa / h^2, or 0
+};
+__global__ __launch_bounds__(1024) void k_spectrum_ends(double* part, int nb, SpecWindows w, int side, int dim,
                                                         double* __restrict__ out)
 {
     __shared__ double sh[2][1024];
-    double hi = 0.0, f = (double)INFINITY;
+    auto energy = [&](int len) {
+        double e = 0.0;
+        for (int a = 0; a < dim; ++a) e += w.n[a] > len ? 9.869604401089358 / ((double)len * len) : 0.0;
+        return w.kh * e;
+    };
+    double hi = 0.0, f = (double)INFINITY, e = energy(side);
 #pragma unroll 4
     for (int i = threadIdx.x; i < nb; i += 1024) {
         hi = max(hi, part[2 * i]);
-        f = min(f, part[2 * i + 1]);
+        f = min(f, part[2 * i + 1] + e);
+    }
+    const double* src = part + 1;
+    double* dst = part + 2 * (long long)nb;
+    int stride = 2, d0 = w.d[0], d1 = w.d[1], d2 = w.d[2];
+    while (w.kh > 0.0 && (d0 > 1 || d1 > 1 || d2 > 1)) {
+        const int e0 = (d0 + 1) / 2, e1 = (d1 + 1) / 2, e2 = (d2 + 1) / 2;
+        side *= 2;
+        e = energy(side);
+        for (int i = threadIdx.x; i < e0 * e1 * e2; i += 1024) {
+            const int x = i % e0 * 2, y = i / e0 % e1 * 2, z = i / e0 / e1 * 2;
+            double sum = 0.0, cnt = 0.0;
+            for (int c = 0; c < 8; ++c) {
+                const int cx = x + (c & 1), cy = y + (c >> 1 & 1), cz = z + (c >> 2);
+                if (cx >= d0 || cy >= d1 || cz >= d2) continue;
+                sum += src[(long long)stride * (cx + (long long)d0 * (cy + (long long)d1 * cz))];
+                cnt += 1.0;
+            }
+            dst[i] = sum / cnt;
+            f = min(f, sum / cnt + e);
+        }
+        __syncthreads();
+        src = dst;
+        dst += e0 * e1 * e2;
+        stride = 1;
+        d0 = e0;
+        d1 = e1;
+        d2 = e2;
     }
     sh[0][threadIdx.x] = hi;
     sh[1][threadIdx.x] = f;
@@ -615,8 +656,15 @@ bool launch_spectrum(const Geom& g, int model, const FreeEnergy& f, double kappa
 {
     const int ts = g.dim == 2 ? SpecTile<2>::S : SpecTile<3>::S;
     const long long tx = (g.n[0] + ts - 1) / ts, ty = (g.n[1] + ts - 1) / ts;
-    const long long nb = tx * ty * (g.dim == 3 ? (g.n[2] + ts - 1) / ts : 1);
-    if (2 * nb > part_max || nb > (1ll << 30)) return false;
+    const long long tz = g.dim == 3 ? (g.n[2] + ts - 1) / ts : 1, nb = tx * ty * tz;
+    long long room = 2 * nb;  // and the windows of every size
+    for (long long a = tx, b = ty, c = tz; a > 1 || b > 1 || c > 1;) {
+        a = (a + 1) / 2;
+        b = (b + 1) / 2;
+        c = (c + 1) / 2;
+        room += a * b * c;
+    }
+    if (room > part_max || nb > (1ll << 30)) return false;
     const double m = std::pow(g.h, g.dim), hk = g.dim == 3 ? g.h : 1.0;
     const StencilDiag d = stencil_diag(g);
     const Lin<T> F{(T)f.b0, (T)f.b1, (T)f.b2};
@@ -638,7 +686,10 @@ bool launch_spectrum(const Geom& g, int model, const FreeEnergy& f, double kappa
         else
             k_spectrum<T, D, 1><<<(unsigned)nb, SpecTile<D>::THREADS, 0, s>>>(U, part, g, F, c, (int)tx, (int)ty);
     });
-    k_spectrum_ends<<<1, 1024, 0, s>>>(part, (int)nb, out);
+    const SpecWindows w{{(int)tx, (int)ty, (int)tz},
+                        {g.n[0], g.n[1], g.dim == 3 ? g.n[2] : 1},
+                        model == 0 ? kappa / (g.h * g.h) : 0.0};
+    k_spectrum_ends<<<1, 1024, 0, s>>>(part, (int)nb, w, ts, g.dim, out);
     return true;
 }
 

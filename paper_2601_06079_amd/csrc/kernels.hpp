@@ -189,8 +189,11 @@ void launch_prec_schur(const Geom& g, const FreeEnergy& f, double kappa, double 
 // Cahn-Hilliard with mu eliminated: the same quotient of the largest symbols over
 // launch_prec_schur's diagonal, f'' the largest at the node and its neighbours: what the
 // short waves see where f'' varies over more than one node, an estimate elsewhere.
-// out[1] = the least mean of f'' over a tile of 16 x 16 or 8 x 8 x 8 nodes (those of a
-// shorter axis: its nodes).
+// out[1] = Cahn-Hilliard: the least mean of f'' over a tile of 16 x 16 or 8 x 8 x 8 nodes
+// (those of a shorter axis: its nodes).  Allen-Cahn: an estimate of the least eigenvalue of
+// f'' + kappa K / m: the least, over such tiles and windows of twice, four times, ... their
+// side up to the whole grid, of the mean of f'' and the energy kappa (pi / side)^2 per axis
+// that a mode confined there has.
 // part: at most part_max doubles.  False (nothing launched) where they do not suffice.
 template <typename T>
 bool launch_spectrum(const Geom& g, int model, const FreeEnergy& f, double kappa, double mob, double inv_dt,

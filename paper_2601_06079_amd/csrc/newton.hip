@@ -577,9 +577,9 @@ int gmres(const ColReadback* rb, LinOp<T> A, NWS<T>& L, const T* b, long long n,
 // m/dt, less M f^2 m / (4 kappa) if f < 0 (the least value of k (kappa k + f m) M / m over
 // the stiffness's eigenvalues k >= 0).  f = -W holds everywhere but is far too low for a
 // developed field, in which f'' is 2 W but for walls a few nodes thick, whose own modes lie
-// near f = 0.  So f is the least mean of f'' over a tile, less 0.1 W for what a mean hides;
-// a tile is wider than the walls of the grids where it matters (with thicker ones the
-// diagonal alone takes products by the hundred, whatever f is).  An eigenvalue below the interval does no harm: GMRES finds it.
+// near f = 0, and pockets too small for a mode of their own.  So f is launch_spectrum's
+// estimate, less 0.1 W for what a mean hides.  An eigenvalue below the interval does no
+// harm: GMRES finds it.
 // Degree: the diagonal alone would take about P = sqrt(hi / lo) ln(2 / lin) / 2 products;
 // a product in the polynomial costs two to three vectors less than the Gram-Schmidt
 // sweeps of one more basis vector, so the basis is kept to about six vectors and the
@@ -594,7 +594,7 @@ struct Interval {
     double lo = 0.0, hi = 0.0;
     double indefinite = HUGE_VAL;  // Cahn-Hilliard: dt M f^2 / (4 kappa), f < 0; lo > 0 below 1
 };
-// the interval of a field with f'' = f on average in its lowest tile and the given upper
+// the interval of a field with launch_spectrum's estimate f and the given upper
 // bound (0: what every field has at least)
 template <typename T>
 Interval interval_of(const LinOp<T>& A, double f, double bound)

@@ -41,6 +41,22 @@ def test_allen_cahn_drop(n, kappa, dt, its):
     assert rep.converged and rep.gmres_its <= 2 * its, rep
 
 
+@pytest.mark.parametrize("kappa,its", [(1.0, 126), (4.0, 317)])
+def test_allen_cahn_half_developed(kappa, its):
+    """Six time units after noise: pockets still below the wells, a few nodes wide, too small
+    for a mode that f'' < 0 could carry.  The diagonal alone: 126 and 317 products."""
+    announce("half developed ac", kappa)
+    n = (96, 96, 96)
+    g, _ = pair(n, O.AC, O.F_SYM, F32, h=1.0, W=1.0, kappa=kappa, mob=1.0)
+    q, _ = pair(n, O.AC, O.F_SYM, F64, h=1.0, W=1.0, kappa=kappa, mob=1.0)
+    u = dev(np.random.default_rng(3).uniform(-0.05, 0.05, 96**3), F64)
+    S.step_explicit(q, u, 0.02, 300)
+    U0 = u.to(F32)
+    U = U0.clone()
+    rep = S.newton_step(g, 0.99, U0, U)
+    assert rep.converged and rep.gmres_its <= 2 * its, rep
+
+
 @pytest.mark.parametrize("n,its", [((256, 256), 396), ((64, 64, 64), 390)])
 def test_cahn_hilliard_drop_at_large_steps(n, its):
     announce("developed ch", n)

@@ -69,6 +69,26 @@ def test_cahn_hilliard_drop_at_large_steps(n, its):
     assert rep.converged and its < rep.gmres_its <= 3 * its, rep  # (a polynomial: cheaper products)
 
 
+def test_cahn_hilliard_half_developed_at_a_large_step():
+    """Thirty time units after noise, dt M W^2 / (4 kappa) = 5: the 2x2 blocks converge in 8
+    corrections (none of them solved), the eliminated system alone not in 20."""
+    announce("half developed ch")
+    n, N = (256, 256), 256 * 256
+    g, _ = pair(n, O.CH, O.F_SYM, F32, h=1.0, W=1.0, kappa=1.0, mob=1.0)
+    q, _ = pair(n, O.CH, O.F_SYM, F64, h=1.0, W=1.0, kappa=1.0, mob=1.0)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    c = 0.05 * (2 * torch.rand(N, generator=gen, device="cuda", dtype=F64) - 1)
+    u = torch.cat([c, torch.zeros_like(c)])
+    S.step_explicit(q, u, 1.0 / 320, 9600)
+    c = u[:N].to(F32)
+    U0 = torch.cat([c, torch.zeros_like(c)])
+    S.step_explicit(g, U0, 1e-6, 0)
+    U = U0.clone()
+    rep = S.newton_step(g, 20.0, U0, U)
+    assert rep.converged and rep.newton_its <= 14, rep
+
+
 @pytest.mark.parametrize("dtype", [F64, F32])
 @pytest.mark.parametrize("model,n,dt", [(O.AC, (28, 24), 0.99), (O.AC, (10, 9, 8), 0.99), (O.AC, (28, 24), 3.0),
                                         (O.CH, (22, 18), 20.0), (O.CH, (7, 6, 8), 20.0)])
